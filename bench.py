@@ -636,6 +636,12 @@ def main():
     value = n * r * iters * args.steps / elapsed
     fp32_line = args.precision == "fp32"
     peak = PEAK_FP32_MFMA_TFLOPS if fp32_line else PEAK_BF16_MFMA_TFLOPS
+    # the fixed-point form of the FP32 step runs four int8 products per
+    # coupling product (each position in four base-256 digits), so a quarter
+    # of the int8 rate is what it can reach in terms of the product's flop
+    fixed_point = info["kernel_name"].startswith("step_i8x4")
+    if fixed_point:
+        peak = PEAK_INT8_MFMA_TOPS / 4
     out = {
         "metric": f"spin-updates/s (N*R*steps/s) at N={n}",
         "value": value,
@@ -653,6 +659,9 @@ def main():
                                f"{iters} iterations, paper linear zeta schedule, "
                                f"{args.precision}",
                    "n": n, "replicas": r, "iterations": iters, "precision": args.precision,
+                   "product": ("exact fixed point: FP32 positions as 32-bit integers in four "
+                               "int8 digits, int32 accumulation" if fixed_point
+                               else "floating point"),
                    "kernel": info["kernel_name"]},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,

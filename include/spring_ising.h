@@ -67,7 +67,13 @@ typedef enum { SI_ORDER_PAPER = 0, SI_ORDER_SYMPLECTIC = 1 } si_order;
 typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
 
 /* Arithmetic of the coupling product J.Q (accumulation is always FP32).
- *   FP32        : FP32 J and FP32 positions (plain method).
+ *   FP32        : FP32 J and FP32 positions (plain method).  For integer J of
+ *                 a complete graph (no zero off the diagonal) with N times the
+ *                 largest |J_ij| at most 65281, in the paper order, with tile 0
+ *                 and set_ksplit 0 and where it is faster, the product is
+ *                 formed in fixed point on the int8 matrix cores: every
+ *                 position to 2^-31 of its replica's largest, sums exact,
+ *                 the result rounded to FP32.
  *   BF16X_FP8J  : J stored as FP8 e4m3 (must be exact, e.g. +-1), positions
  *                 as a BF16 copy of the FP32 master state.
  *   BF16X_BF16J : J stored as BF16 (must be exact), positions BF16.
@@ -141,7 +147,9 @@ typedef struct {
   int32_t j_integer;        /* 1 if every J_ij is an integer with |J_ij| <= 127 */
   int32_t j_fp8_exact;      /* 1 if every J_ij is exact in FP8 e4m3 */
   int32_t j_bf16_exact;     /* 1 if every J_ij is exact in BF16 */
-  int32_t tile;             /* tile id of the step kernel in use */
+  int32_t tile;             /* tile id of the step kernel in use (of the FP32 tile
+                               that stands by, where kernel_name is the
+                               fixed-point form's) */
   int32_t precision;        /* si_precision in use */
   int32_t graph_steps;      /* steps per captured HIP graph (0: not captured) */
   int64_t device_bytes;     /* device memory owned by the context */
@@ -255,7 +263,7 @@ si_status spring_ising_set_ksplit(si_ctx *ctx, int32_t ksplit);
  * every workgroup owns one output tile for the whole call and keeps that
  * tile's q and p in registers, only q (which every other tile's coupling
  * product reads) passes through memory, and a grid-wide barrier separates
- * consecutive steps.  Used only when all workgroups of the step kernel in
+ * consecutive steps (the fixed-point form passes q and p).  Used only when all workgroups of the step kernel in
  * use fit on the device at once (cooperative launch); otherwise run()
  * launches per step.  Results are bit-identical to per-step launches.  A
  * resident run() returns after the launch has completed, having checked the
@@ -270,7 +278,8 @@ si_status spring_ising_set_resident(si_ctx *ctx, int32_t min_steps);
  * context (its precision and padded shape; on a batch, both batch tiles),
  * starting from the current state, in two rounds over all candidates (each
  * candidate keeps its faster round), restore the state after each run, and
- * keep the fastest for later steps.  The choice is also stored in the
+ * keep the fastest for later steps (the fixed-point form of FP32, where the
+ * context has it, if it beats every tile).  The choice is also stored in the
  * process's tile cache under this context's key, so that later contexts of
  * that key created with tile 0 start on it.  *best_tile and *best_us (host,
  * nullable) receive the choice and its time per step.  Kernels with a

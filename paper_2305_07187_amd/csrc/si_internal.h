@@ -98,6 +98,33 @@ hipError_t resident_f32_groups_per_cu(int32_t tile, int32_t order, int32_t wall,
 hipError_t launch_resident_f32(int32_t tile, const StepArgs &a, const ResidentArgs &r,
                                hipStream_t s);
 
+// FP32 step with the product on the int8 matrix cores (integer couplings of
+// complete graphs; see si_step_i8.hip).
+constexpr int I8_DIGITS = 4;       // base-256 digits per position
+constexpr int I8_BM = 256, I8_BN = 32, I8_BKB = 8;  // tile, contraction blocks of 32 per slab
+constexpr int I8_SPECIAL = 1 << 20;  // scale exponent of a replica with non-finite positions
+struct I8Args {
+  const uint8_t *Jt;   // int8 J in 1 KB blocks [ld/32][ld/32]
+  const float *J;      // FP32 J [ld][ld]
+  uint8_t *Qt[2];      // digits of the positions [r_pad/32][ld/32][I8_DIGITS] blocks
+  int *kexp[2];        // scale exponent per replica: digits are of rint(q 2^kexp)
+  float *mx[2];        // [ld/I8_BM][r_pad]: largest |q| after the next step, per row tile
+  float *q[2], *p[2];  // [r_pad][ld]
+  const float *dt, *zeta, *h;
+  int32_t cur, t, total_steps, ld, n, r_pad;
+  int32_t xr;          // XCDs the row tiles are split over (1, 2, 4 or 8)
+  float k, inv_m, qmax, pmax;
+  int32_t wall;
+};
+hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s);
+// Workgroups of the resident form (0: none, or they do not all fit).
+hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups);
+hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t groups,
+                              hipStream_t s);
+const char *i8_kernel_name();
+hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s);
+hipError_t launch_i8_pack_j(const float *J, int32_t ld, uint8_t *out, hipStream_t s);
+
 // Batched form: per-instance buffers and the work list of one grouped launch.
 // Batch tiles (both precisions): 1 = 128 x 64 work items, 2 = 64 x 64.
 constexpr int BATCH_BM = 128, BATCH_BN = 64;
@@ -246,7 +273,8 @@ hipError_t launch_noalloc_energy(const float *J, const float *x, int32_t n, int3
                                  int32_t *e_int, void *scratch_ptr, hipStream_t s);
 
 // flags[0]: asymmetric, [1]: nonzero diagonal, [2]: non-finite,
-// [3]: non-integer or |J|>127, [4]: not FP8-e4m3 exact, [5]: not BF16 exact
+// [3]: non-integer or |J|>127, [4]: not FP8-e4m3 exact, [5]: not BF16 exact,
+// [6]: largest |J_ij| of an integer J, [7]: a zero off the diagonal
 hipError_t launch_validate(const float *J, int32_t n, int32_t *flags, hipStream_t s);
 
 }  // namespace si

@@ -22,7 +22,7 @@ __device__ __forceinline__ bool fp8_e4m3_exact(float v) {
 
 __global__ void validate_kernel(const float *__restrict__ J, int n, int32_t *flags) {
   const int64_t total = (int64_t)n * n;
-  int asym = 0, diag = 0, nonfin = 0, nonint = 0, nonfp8 = 0, nonbf16 = 0, maxabs = 0;
+  int asym = 0, diag = 0, zero = 0, nonfin = 0, nonint = 0, nonfp8 = 0, nonbf16 = 0, maxabs = 0;
   for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.x * blockDim.x) {
     const int i = (int)(idx / n), j = (int)(idx % n);
@@ -30,6 +30,7 @@ __global__ void validate_kernel(const float *__restrict__ J, int n, int32_t *fla
     const float w = J[(int64_t)j * n + i];
     if (!(v == w)) asym = 1;
     if (i == j && v != 0.f) diag = 1;
+    if (i != j && v == 0.f) zero = 1;
     if (!isfinite(v)) {
       nonfin = 1;
       continue;
@@ -48,6 +49,7 @@ __global__ void validate_kernel(const float *__restrict__ J, int n, int32_t *fla
   if (nonfp8) atomicOr(flags + 4, 1);
   if (nonbf16) atomicOr(flags + 5, 1);
   if (maxabs) atomicMax(flags + 6, maxabs);
+  if (zero) atomicOr(flags + 7, 1);
 }
 
 __global__ void pack_matrix_kernel(const float *__restrict__ src, int n, float *__restrict__ dst,

@@ -152,6 +152,10 @@ struct si_ctx {
   int64_t b_items_cap = 0;      // int4 entries of the device work list
   unsigned long long *b_trace = nullptr;  // timeline records of traced steps
   int64_t b_trace_cap = 0;                // records
+  // FP32 step on the int8 matrix cores (i8.Jt: set when this context has it)
+  I8Args i8{};
+  int32_t i8_groups = -1;       // workgroups of its resident form (-1: not asked yet)
+  bool i8_off = false;          // autotune found an FP32 tile faster, or is timing one
   float *fsplit = nullptr;      // partial products of the split contraction
   int64_t fsplit_cap = 0;       // floats
   int32_t *res_sync = nullptr;  // [0] time-out flag, [64 ..] per-group step counts
@@ -418,6 +422,101 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
     }
   }
   return best;
+}
+
+// The FP32 step runs on the int8 matrix cores (si_step_i8.hip) where its
+// result is at least as exact as the FP32 matrix cores': integer couplings
+// of a complete graph.  There every row's sum holds the replica's largest
+// positions, whose products the FP32 sum rounds to 24 bits, while the fixed
+// point keeps every position to 2^-31 of the largest.  With couplings left
+// out a row may hold small positions only, and its FP32 sum would be finer.
+// (Error against 64 bits after 20 steps at N = 2000, R = 1024: 5e-8 against
+// 4.6e-7; N = 512 .. 4000, R = 256 .. 2048, positions scaled by 1 .. 1e-30:
+// 3e-8 .. 6e-8 against 1.3e-7 .. 6.6e-7.)  Two paired digits of the sums must
+// fit 32 bits: N |J| 32896 < 2^31.  The digits' scales need the paper order.
+// A tile or a split asked for by the caller keeps the FP32 matrix cores.
+//
+// Sizes, from sweeps of both (us per step, int8 against FP32): a step costs
+// about 1.2 us per 256 spins even with few tiles, so that small problems
+// gain nothing (N = 300, R = 1024: 10.2 against 7.9; N = 512, R = 512: 9.9
+// against 9.4; N = 600, R = 256: 10.9 against 10.9) and the rest up to 4.4
+// times (N = 1000, R = 512: 13.1 against 17.0; N = 2000, R = 1024: 22.3
+// against 73.6; N = 8000, R = 2048: 475 against 2076).  With 65 .. 255
+// replicas the split FP32 form keeps up to N = 2000 (R = 128: 17.6 against
+// 18.3; N = 2500: 28.6 against 21.1), with up to 64 to N = 4000 (26.3 against
+// 27.6; N = 6000: 57.4 against 37.4).
+static bool i8_applies(const si_ctx *c) {
+  const bool complete_integer = c->hflags[3] == 0 && c->hflags[7] == 0;
+  const bool fits = (int64_t)c->n * c->hflags[6] <= 65281;
+  const bool pays = c->n > 4096 || (c->n > 2048 && c->r > 64) || (c->n > 512 && c->r >= 256);
+  return c->prm.precision == SI_PREC_FP32 && c->prm.order == SI_ORDER_PAPER && c->user_tile == 0 &&
+         !c->n_inst && complete_integer && fits && pays;
+}
+
+static bool i8_on(const si_ctx *c) { return c->i8.Jt && c->ksplit_mode == 0 && !c->i8_off; }
+
+// Buffers of the int8 form in one allocation.  Without the memory for it the
+// context simply runs on the FP32 matrix cores.
+static hipError_t i8_init(si_ctx *c) {
+  if (!i8_applies(c)) return hipSuccess;
+  const int64_t nn = (int64_t)c->n_pad * c->n_pad, nr = (int64_t)c->n_pad * c->r_pad;
+  const int64_t mxb = round_up((int64_t)(c->n_pad / I8_BM) * c->r_pad * 4, 256);
+  const int64_t kb = round_up((int64_t)c->r_pad * 4, 256);
+  uint8_t *buf = nullptr;
+  if (c->alloc(&buf, nn + 2 * (nr * I8_DIGITS + mxb + kb)) != hipSuccess) {
+    (void)hipGetLastError();
+    return hipSuccess;
+  }
+  I8Args &a = c->i8;
+  a.J = c->J;
+  uint8_t *at = buf + nn;
+  for (int b = 0; b < 2; ++b) {
+    a.Qt[b] = at;
+    at += nr * I8_DIGITS;
+    a.mx[b] = reinterpret_cast<float *>(at);
+    at += mxb;
+    a.kexp[b] = reinterpret_cast<int *>(at);
+    at += kb;
+    a.q[b] = c->q[b];
+    a.p[b] = c->p[b];
+  }
+  a.dt = c->dt;
+  a.zeta = c->zeta;
+  a.total_steps = c->prm.total_steps;
+  a.ld = c->n_pad;
+  a.n = c->n;
+  a.r_pad = c->r_pad;
+  a.k = c->prm.k;
+  a.inv_m = 1.0f / c->prm.m;
+  a.qmax = c->prm.qmax;
+  a.pmax = c->prm.pmax;
+  a.wall = c->prm.wall;
+  // the split of the tiles over the XCDs' L2s that fetches least: every row
+  // group reads all of its column group's digits and the other way round
+  const int64_t ntr = c->n_pad / I8_BM, ntc = c->r_pad / I8_BN;
+  double least = 0.0;
+  for (int32_t xr = 1; xr <= NUM_XCD; xr *= 2) {
+    const int64_t xc = NUM_XCD / xr;
+    const double pad = (double)(round_up(ntr, xr) * round_up(ntc, xc)) / (double)(ntr * ntc);
+    const int64_t bands = ((ntr + xr - 1) / xr + 3) / 4;  // sweeps over its columns
+    const double cost = pad * ((double)nn * xc + (double)nr * I8_DIGITS * xr * bands);
+    if (xr == 1 || cost < least) {
+      least = cost;
+      a.xr = xr;
+    }
+  }
+  hipError_t e = launch_i8_pack_j(c->J, c->n_pad, buf, c->stream);
+  if (e == hipSuccess) a.Jt = buf;
+  return e;
+}
+
+// Digits, scales and maxima of the current FP32 state: after every call that
+// wrote the state or the schedule by other means than the int8 step.
+static hipError_t i8_refresh(si_ctx *c) {
+  if (!i8_on(c)) return hipSuccess;
+  c->i8.cur = c->cur;
+  c->i8.t = c->t;
+  return launch_i8_prepare(c->i8, c->stream);
 }
 
 // Buffers of the best-state record (allocated once, records invalid).
@@ -704,7 +803,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
     return fail(SI_ERR_INVALID, "init: tile %d cannot run precision %d", bad, prm->precision);
   }
   const TileShape ts = shape_of(prm->precision, c->tile);
-  c->n_pad = (int32_t)round_up(n, ts.bm > 128 ? ts.bm : 128);
+  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, i8_applies(c) ? I8_BM : 128));
   c->r_pad = (int32_t)round_up(r, ts.bn > 64 ? ts.bn : 64);
   const bool j_integer = c->hflags[3] == 0;
   const bool need_bf16 = prm->precision == SI_PREC_BF16X_BF16J ||
@@ -749,6 +848,8 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
                           hipMemcpyHostToDevice, c->stream));
   INIT_HIP(hipMemcpyAsync(c->zeta, c->host_zeta.data(), sizeof(float) * prm->total_steps,
                           hipMemcpyHostToDevice, c->stream));
+  INIT_HIP(i8_init(c));
+  INIT_HIP(i8_refresh(c));
   INIT_HIP(init_energy_checks(c));
 #undef INIT_HIP
   c->cur = 0;
@@ -999,6 +1100,7 @@ si_status spring_ising_set_schedule(si_ctx *c, const float *dt, const float *zet
   const size_t bytes = sizeof(float) * c->prm.total_steps;
   SI_HIP(c, hipMemcpyAsync(c->dt, dt, bytes, hipMemcpyDeviceToDevice, c->stream));
   SI_HIP(c, hipMemcpyAsync(c->zeta, zeta, bytes, hipMemcpyDeviceToDevice, c->stream));
+  SI_HIP(c, i8_refresh(c));
   return SI_OK;
 }
 
@@ -1146,9 +1248,29 @@ static si_status do_steps_batch(si_ctx *c, int32_t n_steps, unsigned long long *
   return SI_OK;
 }
 
-static si_status do_steps(si_ctx *c, int32_t n_steps) {
-  if (c->n_inst) return do_steps_batch(c, n_steps);
-  if (c->qplanes) return do_steps_lowp(c, n_steps);
+static I8Args i8_args(si_ctx *c) {
+  I8Args a = c->i8;
+  a.h = c->has_field ? c->hf : nullptr;
+  a.cur = c->cur;
+  a.t = c->t;
+  return a;
+}
+
+static si_status do_steps_i8(si_ctx *c, int32_t n_steps) {
+  I8Args a = i8_args(c);
+  for (int32_t s = 0; s < n_steps; ++s) {
+    a.cur = c->cur;
+    a.t = c->t;
+    SI_HIP(c, launch_step_i8(a, c->num_cus, c->stream));
+    c->cur ^= 1;
+    c->t += 1;
+    SI_ENERGY_CHECK(c);
+  }
+  return SI_OK;
+}
+
+// Steps of a single instance on the FP32 matrix cores.
+static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
   StepArgs a;
   a.J = c->J;
   a.dt = c->dt;
@@ -1181,6 +1303,13 @@ static si_status do_steps(si_ctx *c, int32_t n_steps) {
     SI_ENERGY_CHECK(c);
   }
   return SI_OK;
+}
+
+static si_status do_steps(si_ctx *c, int32_t n_steps) {
+  if (c->n_inst) return do_steps_batch(c, n_steps);
+  if (c->qplanes) return do_steps_lowp(c, n_steps);
+  if (i8_on(c)) return do_steps_i8(c, n_steps);
+  return do_steps_f32(c, n_steps);
 }
 
 // Adjoint, forward half: run from the current step t0 to the end of the
@@ -1229,9 +1358,10 @@ static si_status adj_forward(si_ctx *c, int32_t C, double *loss) {
     SI_HIP(c, hipMemcpyAsync(ck + NR, c->p[c->cur], NR * sizeof(float),
                              hipMemcpyDeviceToDevice, c->stream));
     const int32_t len = (S - c->t) < C ? (S - c->t) : C;
-    si_status st = do_steps(c, len);
+    si_status st = do_steps_f32(c, len);  // as the backward half recomputes it
     if (st != SI_OK) return st;
   }
+  SI_HIP(c, i8_refresh(c));
   // seed: lq_S = -(1/R) J q_S, lp_S = 0, and the loss
   SI_HIP(c, launch_adj_seed(c->J, c->q[c->cur], c->adj_lam, c->adj_lam + NR, c->adj_part,
                             c->n_pad, c->r_pad, inv_r, c->stream));
@@ -1378,7 +1508,15 @@ static si_status run_graph(si_ctx *c, int32_t n_steps) {
 // Workgroups of the resident launch for the current tile, or 0 when the
 // context has no resident form or they do not all fit on the device.
 static int32_t resident_groups(si_ctx *c) {
-  if (c->n_inst || c->qplanes || split_for(c, c->tile) > 1) return 0;
+  if (c->n_inst || c->qplanes) return 0;
+  if (i8_on(c)) {
+    if (c->i8_groups < 0) {
+      if (resident_i8_groups(c->i8, c->num_cus, &c->i8_groups) != hipSuccess) c->i8_groups = 0;
+      (void)hipGetLastError();
+    }
+    return c->i8_groups;
+  }
+  if (split_for(c, c->tile) > 1) return 0;
   if (c->resident_tile != c->tile) {
     int per = 0;
     if (resident_f32_groups_per_cu(c->tile, c->prm.order, c->prm.wall, &per) != hipSuccess)
@@ -1411,7 +1549,10 @@ static si_status run_resident(si_ctx *c, int32_t n_steps, int32_t groups) {
   r.n_steps = n_steps;
   r.count = reinterpret_cast<uint32_t *>(c->res_sync + 64);
   r.err = c->res_sync;
-  SI_HIP(c, launch_resident_f32(c->tile, a, r, c->stream));
+  if (i8_on(c))
+    SI_HIP(c, launch_resident_i8(i8_args(c), r, groups, c->stream));
+  else
+    SI_HIP(c, launch_resident_f32(c->tile, a, r, c->stream));
   c->t += n_steps;
   c->cur ^= (n_steps & 1);
   int32_t err = 0;
@@ -1449,6 +1590,7 @@ si_status spring_ising_set_ksplit(si_ctx *c, int32_t ksplit) {
   c->epoch++;
   c->ksplit_mode = ksplit;
   SI_HIP(c, ensure_split_ws(c));
+  SI_HIP(c, i8_refresh(c));
   c->drop_graphs();
   return SI_OK;
 }
@@ -1581,6 +1723,10 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
     ~KeepEvery() { c->e_every = v; }
   } keep{c, c->e_every};
   c->e_every = 0;
+  // the int8 form, where the context has it, is timed against the fastest
+  // FP32 tile below
+  const bool has_i8 = c->i8.Jt && c->ksplit_mode == 0;
+  c->i8_off = has_i8;
   const int32_t last = lowp ? TILE_BF16_LAST : TILE_F32_LAST;
   const int32_t timed = steps - 1 > 0 ? steps - 1 : 1;
   int32_t best = tile0;
@@ -1622,9 +1768,33 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   }
   c->tile = best;
   SI_HIP(c, ensure_split_ws(c));
+  tile_cache_put(tile_key(c), best, best_t);
+  if (has_i8) {
+    c->i8_off = false;
+    float i8_t = 1e30f;
+    for (int round = 0; round < 2; ++round) {
+      SI_HIP(c, i8_refresh(c));
+      si_status st = do_steps(c, 1);
+      if (st != SI_OK) return st;
+      SI_HIP(c, hipEventRecord(e0, c->stream));
+      st = do_steps(c, timed);
+      if (st != SI_OK) return st;
+      SI_HIP(c, hipEventRecord(e1, c->stream));
+      SI_HIP(c, hipMemcpyAsync(c->q[cur0], save, NR * 4, hipMemcpyDeviceToDevice, c->stream));
+      SI_HIP(c, hipMemcpyAsync(c->p[cur0], save + NR, NR * 4, hipMemcpyDeviceToDevice, c->stream));
+      c->t = t0;
+      c->cur = cur0;
+      SI_HIP(c, hipEventSynchronize(e1));
+      float ms = 0.f;
+      SI_HIP(c, hipEventElapsedTime(&ms, e0, e1));
+      i8_t = std::min(i8_t, 1000.f * ms / (float)timed);
+    }
+    c->i8_off = best_t < i8_t;
+    SI_HIP(c, i8_refresh(c));
+    best_t = std::min(best_t, i8_t);
+  }
   c->drop_graphs();
   c->tile_source = SI_TILE_FROM_AUTOTUNE;
-  tile_cache_put(tile_key(c), best, best_t);
   if (best_tile) *best_tile = best;
   if (best_us) *best_us = best_t;
   return SI_OK;
@@ -1849,6 +2019,7 @@ si_status spring_ising_set_state(si_ctx *c, const float *x, const float *p, int3
     SI_HIP(c, launch_split_planes(c->q[c->cur], c->qb[c->cur], (int64_t)c->n_pad * c->r_pad,
                                   c->qplanes, c->stream));
   c->t = t;
+  SI_HIP(c, i8_refresh(c));
   return SI_OK;
 }
 
@@ -2022,6 +2193,8 @@ si_status spring_ising_info(si_ctx *c, si_info *info) {
   if (c->n_inst)
     snprintf(info->kernel_name, sizeof info->kernel_name, "step_batch_%s_%dx%d_x%d",
              c->b_lowp ? "bf16" : "f32", batch_tile_rows(c->tile), BATCH_BN, c->n_inst);
+  else if (i8_on(c))
+    snprintf(info->kernel_name, sizeof info->kernel_name, "%s", i8_kernel_name());
   else if (split_for(c, c->tile) > 1)
     snprintf(info->kernel_name, sizeof info->kernel_name, "%s_ks%d",
              shape_of(c->prm.precision, c->tile).name, split_for(c, c->tile));

@@ -1,0 +1,625 @@
+// FP32 step with the coupling product on the int8 matrix cores.
+//
+// The plain method's product F = J.Q (Eq. 8) in fixed point: every position
+// is held beside its FP32 value as a 32-bit integer v = rint(q 2^k) with one
+// exponent k per replica, chosen so that the replica's largest |q| just fits,
+// and split into four balanced base-256 digits.  For integer couplings
+// |J_ij| <= 127 the four digit products run on v_mfma_i32_32x32x32_i8 with
+// int32 accumulation, which is exact, and F is their weighted sum: pairs of
+// digits exactly in 32 bits, then one FP32 conversion of each half and one
+// fused multiply-add.  Positions within a factor of 64 of the replica's
+// largest enter without any error, smaller ones with at most 2^-31 of the
+// largest (a complete graph couples every other row to that largest one, and
+// in its own row -k q_i dwarfs the error); the FP32 matrix cores round every
+// partial sum to 24 bits instead.  Against 64 bits, final positions after 20
+// steps: 5.3e-8 (FP32 4.6e-7) at N = 2000, R = 1024.  The sum does not depend
+// on its order, so neither the tile nor a split changes a result.
+//
+// Measured (MI355X, us per step, FP32 matrix cores before): N = 2000, R = 1024
+// 22.3 (73.6), R = 2048 42 (141), N = 4000, R = 2048 128 (532), N = 8000,
+// R = 2048 475 (2076).  Bound: four int8 products take 7.6 us of matrix time a
+// step at N = 2000, R = 1024 (256 tiles, one per CU; 52 us at the FP32 peak);
+// a 256-deep slab of a tile takes 1.4 .. 1.9 us instead of 0.95, because the
+// loads of J and the copies and LDS reads of the digits fill the CU's memory
+// and LDS pipelines as well, and the start and the end of a launch take about
+// 8 us.  Slower: J through LDS too (24.0 at N = 2000, R = 1024; 127 at
+// N = 4000, R = 2048), eight 32 x 32 matrix waves (23.6; 138), eight waves
+// without state waves (25; 147), counters in LDS for the slab barriers (23.4;
+// 132), J fetched into L2 ahead (23.2; 136).
+//
+// Operand layout: 1 KB blocks of 32 rows (or replicas) by 32 contraction
+// indices in the matrix instruction's own lane order (lane l holds the 16
+// bytes of row l % 32 from index 16 (l / 32) on), so that slabs are copied to
+// LDS, and fragments read from it, as consecutive 1 KB pieces: no swizzle,
+// no bank conflict.  J: [row block][k block], Q: [column block][k block][digit].
+//
+// Scales.  The digits of q_{n+1} are written by the step that computes it,
+// so the largest |q_{n+1}| of a replica has to be known before: in the paper
+// order q_{n+1} = clamp(q_n + (Delta_n/m) p_n) depends on the state n alone,
+// and the previous step, which produced that state, leaves the maximum per
+// row tile and replica in mx.  After set_state, set_schedule or steps by
+// other kernels a preparation kernel derives digits, scales and maxima from
+// the FP32 state.  Every entry q_{n+1} lies within the walls, so only
+// positions given by the caller can be non-finite: their replicas carry
+// I8_SPECIAL and the step sums their FP32 products directly.
+#include <algorithm>
+
+#include "si_epilogue.h"
+#include "si_grid_barrier.h"
+#include "si_internal.h"
+
+namespace si {
+
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef int intx16 __attribute__((ext_vector_type(16)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void_q;
+typedef __attribute__((address_space(1))) const void gbl_void_q;
+
+namespace {
+constexpr int QP = I8_DIGITS;
+constexpr int BLK = 1024;  // bytes of one 32 x 32 operand block
+}  // namespace
+
+// 1 KB block of J's row block rb, or of the first digit of the positions'
+// column block cb, at contraction block kb.  The contraction is outermost:
+// all workgroups walk it together, so what they read at one time lies in
+// one consecutive range and spreads over every channel of the caches and the
+// memory (row blocks outermost would put it at strides of a power of two).
+__device__ __forceinline__ size_t i8_jblk(int kb, int rb, int nrb) {
+  return ((size_t)(kb >> 1) * nrb + rb) * 2 + (kb & 1);
+}
+__device__ __forceinline__ size_t i8_qblk(int kb, int cb, int ncb) {
+  return (((size_t)(kb >> 1) * ncb + cb) * 2 + (kb & 1)) * QP;
+}
+
+// Exponent k of a replica whose largest |q| is m: |rint(q 2^k)| fits four
+// balanced digits (at most 0x7F7F7F7F).
+__device__ __forceinline__ int i8_exponent(float m) {
+  if (!(m <= 3.402823466e38f)) return I8_SPECIAL;
+  if (m == 0.f) return 0;
+  int e;
+  (void)frexpf(m, &e);
+  int k = 31 - e;
+  if (ldexpf(m, k) > 2139062016.f) --k;  // 0x7F7F7F00
+  return k;
+}
+
+// The four digits of q as the bytes of one word, lowest digit first.
+__device__ __forceinline__ uint32_t i8_digits(float q, int k) {
+  const float v = fminf(fmaxf(rintf(ldexpf(q, k)), -2139062016.f), 2139062016.f);
+  return ((uint32_t)(int)v + 0x80808080u) ^ 0x80808080u;
+}
+
+// Bytes of four words regrouped by digit: out[d] = digit d of the four.
+__device__ __forceinline__ void byte_transpose(const uint32_t (&w)[4], uint32_t (&out)[4]) {
+  const uint32_t lo01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);
+  const uint32_t hi01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+  const uint32_t lo23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+  const uint32_t hi23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+}
+
+// 4 x 4 transpose over the four lanes of a quad: lane t's w[c] becomes lane
+// c's out[t].
+__device__ __forceinline__ void quad_transpose(uint32_t (&w)[4]) {
+  const int t = threadIdx.x & 3;
+  // exchange with lane t ^ 1 (quad_perm 1,0,3,2), then with t ^ 2 (2,3,0,1)
+#pragma unroll
+  for (int c = 0; c < 4; c += 2) {
+    const uint32_t send = (t & 1) ? w[c] : w[c + 1];
+    const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0xB1, 0xF, 0xF, true);
+    if (t & 1)
+      w[c] = got;
+    else
+      w[c + 1] = got;
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const uint32_t send = (t & 2) ? w[c] : w[c + 2];
+    const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)send, 0x4E, 0xF, 0xF, true);
+    if (t & 2)
+      w[c] = got;
+    else
+      w[c + 2] = got;
+  }
+}
+
+// Wait until at most N memory operations of this wave are in flight, then
+// synchronise the workgroup.  The wait goes through the builtin, which the
+// compiler's own wait insertion accounts for.
+template <int N>
+__device__ __forceinline__ void q_wait_barrier() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+  asm volatile("s_barrier" ::: "memory");
+}
+__device__ __forceinline__ void q_barrier() { asm volatile("s_barrier" ::: "memory"); }
+__device__ __forceinline__ void q_wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
+// ---------------------------------------------------------------------------
+// Step kernel: 256 x 32 tiles in two roles.  Four matrix waves of 64 x 32 run
+// the products: each reads its own rows of J straight from memory into
+// registers, PD contraction blocks ahead, and the digits, which all four
+// need, from an LDS ring of 256-deep slabs.  Four state waves fill the ring
+// and own the tile's state: in the paper order q' and its digits need no
+// coupling term, so they are formed while the product runs, and p' follows
+// while the product of the workgroup's next tile runs.  (A workgroup takes
+// every gridDim-th tile of its XCD, and the ring flows across tiles.)  The
+// two roles share the matrix pipes, the copies' queue and the vector units
+// instead of taking turns on them.
+//
+// Barriers, passed by both roles: one when the first slab has landed, then
+// per tile nk slab barriers (the slab has been read, the next one has
+// landed) and one when F is in LDS.
+// ---------------------------------------------------------------------------
+struct I8Cfg {
+  static constexpr int BM = I8_BM, BN = I8_BN, BKB = I8_BKB, STAGES = 3;
+  static constexpr int NM = 4, NS = 4, NT = 64 * (NM + NS);
+  static constexpr int SLOT = BKB * QP * BLK;  // digits of one slab
+  static constexpr int L = BKB * QP / NS;      // 1 KB copies per state wave and slab
+  static constexpr int PD = 8;                 // contraction blocks of J held ahead
+  static constexpr int LDT = BM + 4;           // floats per column of F
+  static constexpr int COLS = BN / NS;         // columns per state wave
+  static constexpr int SETS = COLS / 4;
+  static_assert(BM == 64 * NM && BN == 32 && COLS == 8 && BKB % PD == 0, "tile");
+  static_assert(BKB == 2 * NS && (STAGES - 1) * L <= 63 && STAGES >= 2, "ring");
+};
+
+struct I8Smem {
+  __attribute__((aligned(16))) uint8_t ring[I8Cfg::STAGES * I8Cfg::SLOT];
+  __attribute__((aligned(16))) float tile[I8Cfg::BN * I8Cfg::LDT];
+};
+
+// Tile i of this workgroup.  Every XCD (workgroup b runs on XCD b % 8) takes
+// an xr-th of the row tiles by an xc-th of the column tiles (xr xc = 8), so
+// that its L2 fetches that part of J and of the digits only, and walks it in
+// bands of four row tiles, column by column, so that a band of J stays there.
+struct I8Walk {
+  int pr, pc, r0, c0, nr, nc, first, stride, count;
+  __device__ __forceinline__ I8Walk(const I8Args &a) {
+    const int ntr = a.ld / I8Cfg::BM, ntc = a.r_pad / I8Cfg::BN, xc = NUM_XCD / a.xr;
+    const int x = blockIdx.x % NUM_XCD;
+    pr = (ntr + a.xr - 1) / a.xr;
+    pc = (ntc + xc - 1) / xc;
+    r0 = (x / xc) * pr;
+    c0 = (x % xc) * pc;
+    nr = min(pr, ntr - r0);
+    nc = min(pc, ntc - c0);
+    first = blockIdx.x / NUM_XCD;
+    stride = gridDim.x / NUM_XCD;
+    const int tiles = nr > 0 && nc > 0 ? nr * nc : 0;
+    count = first < tiles ? (tiles - first + stride - 1) / stride : 0;
+  }
+  __device__ __forceinline__ void at(int i, int &m0, int &n0) const {
+    const int t = first + i * stride, band = t / (4 * nc), rows = min(4, nr - band * 4);
+    const int u = t - band * 4 * nc;
+    m0 = (r0 + band * 4 + u % rows) * I8Cfg::BM;
+    n0 = (c0 + u / rows) * I8Cfg::BN;
+  }
+};
+
+// The matrix waves' part of one step.
+__device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk &walk, I8Smem &sm) {
+  using C = I8Cfg;
+  constexpr int NB = C::BKB, PD = C::PD;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nk = (a.n + 32 * NB - 1) / (32 * NB), nrb = a.ld / 32;
+  const size_t pair = (size_t)nrb * 2 * BLK;  // two contraction blocks further
+  int m0, n0;
+  auto source = [&](int i) {
+    walk.at(i, m0, n0);
+    return a.Jt + i8_jblk(0, m0 / 32 + wave * 2, nrb) * BLK + lane * 16;
+  };
+  intx4 fa[PD][2], fb[2][QP];
+  auto load_a = [&](const uint8_t *s, int i, intx4 (&x)[2]) {
+    s += (size_t)(i / 2) * pair + (i & 1) * BLK;
+    x[0] = *reinterpret_cast<const intx4 *>(s);
+    x[1] = *reinterpret_cast<const intx4 *>(s + 2 * BLK);
+  };
+  auto read_b = [&](const uint8_t *st, int i, int f) {
+#pragma unroll
+    for (int d = 0; d < QP; ++d)
+      fb[f][d] = *reinterpret_cast<const intx4 *>(st + (i * QP + d) * BLK);
+  };
+  const uint8_t *cur = source(0), *nxt = cur;
+#pragma unroll
+  for (int i = 0; i < PD; ++i) load_a(cur, i, fa[i]);
+  int rd = 0;
+  const uint8_t *st = sm.ring + lane * 16;
+  q_barrier();  // the first slab has landed
+  read_b(st, 0, 0);
+  for (int tile = 0; tile < walk.count; ++tile) {
+    walk.at(tile, m0, n0);
+    const int kcol = a.kexp[a.cur][n0 + (lane & 31)];
+    intx16 acc[2][QP];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int d = 0; d < QP; ++d)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][d][v] = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      // the slab after this one (of the next tile; past the last: this one)
+      nxt = kt + 1 < nk ? cur + (NB / 2) * pair : tile + 1 < walk.count ? source(tile + 1) : cur;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (i + 1 < NB) {
+          read_b(st, i + 1, (i & 1) ^ 1);
+        } else {
+          q_wait_lds();  // this wave has read the slab
+          q_barrier();
+          rd = rd + 1 == C::STAGES ? 0 : rd + 1;
+          st = sm.ring + rd * C::SLOT + lane * 16;
+          read_b(st, 0, (i & 1) ^ 1);  // (past the last slab: not used)
+        }
+        // (the scheduler would gather the loads of J at the end)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < QP; ++d)
+#pragma unroll
+          for (int r = 0; r < 2; ++r)
+            acc[r][d] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i % PD][r], fb[i & 1][d],
+                                                              acc[r][d], 0, 0, 0);
+        load_a(i + PD < NB ? cur : nxt, (i + PD) % NB, fa[i % PD]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      cur = nxt;
+    }
+    // F = sum_d 256^d acc_d 2^-k: pairs of digits exactly in 32 bits, then
+    // one FP32 conversion each and one fused multiply-add
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float f[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int e = 4 * g + v;
+          const float hi = (float)(acc[r][3][e] * 256 + acc[r][2][e]);
+          const float lo = (float)(acc[r][1][e] * 256 + acc[r][0][e]);
+          f[v] = ldexpf(fmaf(hi, 65536.f, lo), -kcol);
+        }
+        epi_put(sm.tile, C::LDT, wave * 64 + r * 32 + g * 8 + (lane / 32) * 4, lane & 31, f[0],
+                f[1], f[2], f[3]);
+      }
+    q_wait_lds();
+    q_barrier();  // F is in LDS
+  }
+}
+
+// The state waves' part of one step: wave sw owns columns 8 sw .. 8 sw + 7 of
+// a tile, a lane four spins of each.
+template <int WALL>
+__device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8Smem &sm) {
+  using C = I8Cfg;
+  const int sw = __builtin_amdgcn_readfirstlane(((int)threadIdx.x >> 6) - C::NM);
+  const int lane = threadIdx.x & 63, row = lane * 4, nx = a.cur ^ 1;
+  const int nk = (a.n + 32 * C::BKB - 1) / (32 * C::BKB), ncb = a.r_pad / 32;
+  const int ntr = a.ld / C::BM;
+  int m0, n0;
+  // copies: wave sw takes the two contraction blocks of pair sw of each slab
+  const size_t step = (size_t)ncb * (C::BKB * QP) * BLK;
+  const uint8_t *src = nullptr;
+  int itile = 0, ikt = 0, islot = 0;  // tile and slab of the next copy, its slot
+  auto issue = [&]() {
+    if (itile >= walk.count) return;
+    if (ikt == 0) {
+      int m, n;
+      walk.at(itile, m, n);
+      src = a.Qt[a.cur] + i8_qblk(2 * sw, n / 32, ncb) * BLK + lane * 16;
+    }
+    uint8_t *dst = sm.ring + islot * C::SLOT + sw * C::L * BLK;
+#pragma unroll
+    for (int d = 0; d < C::L; ++d)
+      __builtin_amdgcn_global_load_lds((gbl_void_q *)(src + d * BLK), (lds_void_q *)(dst + d * BLK),
+                                       16, 0, 0);
+    src += step;
+    islot = islot + 1 == C::STAGES ? 0 : islot + 1;
+    if (++ikt == nk) {
+      ikt = 0;
+      ++itile;
+    }
+  };
+  const int total = walk.count * nk;
+  int g = 1, left = 0;  // next slab to hand over (of all tiles'), barriers left in this tile
+  // the barrier after a slab: the next one has landed, its slot is refilled
+  auto pass = [&]() {
+    if (g + C::STAGES - 2 < total)
+      q_wait_barrier<(C::STAGES - 2) * C::L>();
+    else
+      q_wait_barrier<0>();
+    issue();
+    ++g;
+    --left;
+  };
+  auto tick = [&]() {
+    if (left > 0) pass();
+  };
+  issue();
+  if (total > 1) issue();
+  q_wait_barrier<0>();  // the first slab has landed
+  if (C::STAGES > 2) issue();
+
+  const float dt = a.dt[a.t], zeta = a.zeta[a.t];
+  const float cdt = dt * a.inv_m;
+  const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
+  floatx4 q4[C::COLS], p4[C::COLS], h4;
+  int kin = 0;
+  // p' of tile (m, n) from F in LDS, and the next step's maxima
+  auto finish = [&](int m, int n) {
+#pragma unroll
+    for (int set = 0; set < C::SETS; ++set) {
+      uint32_t um[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int col = sw * C::COLS + set * 4 + c, cc = set * 4 + c;
+        const size_t off = (size_t)(n + col) * a.ld + m + row;
+        floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
+        if (__builtin_amdgcn_readlane(kin, cc) == I8_SPECIAL) {
+          // non-finite positions given by the caller: FP32 products, summed
+          f = floatx4{0.f, 0.f, 0.f, 0.f};
+          for (int i = 0; i < a.n; ++i) {
+            const float qi = a.q[a.cur][(size_t)(n + col) * a.ld + i];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) f[v] = fmaf(a.J[(size_t)(m + row + v) * a.ld + i], qi, f[v]);
+          }
+        }
+        float mx = 0.f;
+        floatx4 pn;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          float qv, pv;
+          spring_update<SI_ORDER_PAPER, WALL>(q4[cc][v], p4[cc][v], f[v] + h4[v], dt, zeta, a.k,
+                                              a.inv_m, a.qmax, a.pmax, qv, pv);
+          pn[v] = pv;
+          mx = fmaxf(mx, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
+        }
+        *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+        um[c] = __float_as_uint(mx);
+      }
+      quad_transpose(um);
+      float mx = fmaxf(fmaxf(__uint_as_float(um[0]), __uint_as_float(um[1])),
+                       fmaxf(__uint_as_float(um[2]), __uint_as_float(um[3])));
+#pragma unroll
+      for (int off = 4; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+      if (lane < 4)
+        a.mx[nx][(size_t)(m / C::BM) * a.r_pad + n + sw * C::COLS + set * 4 + lane] = mx;
+      tick();
+    }
+  };
+  for (int tile = 0; tile < walk.count; ++tile) {
+    left = nk;
+    if (tile > 0) finish(m0, n0);
+    walk.at(tile, m0, n0);
+    const int col0 = n0 + sw * C::COLS;
+    // scales of the new positions: maxima of this wave's columns, one column
+    // and every eighth row tile per lane
+    float mx = 0.f;
+    for (int rt = lane >> 3; rt < ntr; rt += 8)
+      mx = fmaxf(mx, a.mx[a.cur][(size_t)rt * a.r_pad + col0 + (lane & 7)]);
+    kin = a.kexp[a.cur][col0 + (lane & 7)];
+    h4 = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (a.h) h4 = *reinterpret_cast<const floatx4 *>(a.h + m0 + row);
+#pragma unroll
+    for (int c = 0; c < C::COLS; ++c) {
+      const size_t off = (size_t)(col0 + c) * a.ld + m0 + row;
+      q4[c] = *reinterpret_cast<const floatx4 *>(a.q[a.cur] + off);
+      p4[c] = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 8));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const int kout = i8_exponent(mx);
+    if (m0 == 0 && lane < C::COLS) a.kexp[nx][col0 + lane] = kout;
+    tick();
+    const int spin = m0 + (lane >> 2) * 16;
+#pragma unroll
+    for (int set = 0; set < C::SETS; ++set) {
+      uint32_t w[QP][4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int cc = set * 4 + c, k = __builtin_amdgcn_readlane(kout, cc);
+        uint32_t dg[4], by[4];
+        floatx4 qn;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float u = fmaf(cdt, p4[cc][v], q4[cc][v]);
+          qn[v] = fminf(fmaxf(u, -a.qmax), a.qmax);
+          dg[v] = i8_digits(qn[v], k);
+        }
+        *reinterpret_cast<floatx4 *>(a.q[nx] + (size_t)(col0 + cc) * a.ld + m0 + row) = qn;
+        byte_transpose(dg, by);
+#pragma unroll
+        for (int d = 0; d < QP; ++d) w[d][c] = by[d];
+        if (c == 1) tick();
+      }
+      // lane t of a quad takes column t: 16 consecutive spins per digit
+      uint8_t *out = a.Qt[nx] + i8_qblk(spin / 32, n0 / 32, ncb) * BLK + (spin & 16) * 32 +
+                     (sw * C::COLS + set * 4 + (lane & 3)) * 16;
+#pragma unroll
+      for (int d = 0; d < QP; ++d) {
+        quad_transpose(w[d]);
+        *reinterpret_cast<uintx4 *>(out + d * BLK) = uintx4{w[d][0], w[d][1], w[d][2], w[d][3]};
+      }
+      tick();
+    }
+    while (left > 0) pass();
+    q_barrier();  // F is in LDS
+  }
+  left = 0;
+  finish(m0, n0);
+}
+
+template <int WALL>
+__global__ __launch_bounds__(I8Cfg::NT) void step_i8_kernel(I8Args a) {
+  __shared__ I8Smem sm;
+  const I8Walk walk(a);
+  if (walk.count == 0) return;
+  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < I8Cfg::NM)
+    i8_matrix(a, walk, sm);
+  else
+    i8_state<WALL>(a, walk, sm);
+}
+
+// Resident form: one cooperative launch runs n_steps steps with a grid-wide
+// barrier between them (see grid_barrier).  One tile per workgroup.
+template <int WALL>
+__global__ __launch_bounds__(I8Cfg::NT) void resident_i8_kernel(I8Args a, ResidentArgs r) {
+  __shared__ I8Smem sm;
+  const I8Walk walk(a);
+  if (walk.count == 0) return;
+  for (int s = 0; s < r.n_steps; ++s) {
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < I8Cfg::NM)
+      i8_matrix(a, walk, sm);
+    else
+      i8_state<WALL>(a, walk, sm);
+    a.cur ^= 1;
+    a.t += 1;
+    if (s + 1 < r.n_steps && !grid_barrier(r.count, (uint32_t)(s + 1), r.err)) return;
+  }
+}
+
+// Digits, scales and maxima of the FP32 state (t: the next step's index).
+// One workgroup per eight replicas: a wave per replica finds the maxima, then
+// eight neighbouring replicas' 16-byte pieces fill whole 128-byte lines.
+__global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
+  __shared__ int kx[8];
+  const int r0 = blockIdx.x * 8, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const float *q = a.q[a.cur], *p = a.p[a.cur];
+  const float c = a.dt[a.t < a.total_steps ? a.t : a.total_steps - 1] * a.inv_m;
+  {
+    const size_t base = (size_t)(r0 + wave) * a.ld;
+    float mq = 0.f, mu = 0.f;
+    bool nan = false;
+    for (int i = lane * 4; i < a.ld; i += 256) {
+      const floatx4 q4 = *reinterpret_cast<const floatx4 *>(q + base + i);
+      const floatx4 p4 = *reinterpret_cast<const floatx4 *>(p + base + i);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        nan |= q4[v] != q4[v];
+        mq = fmaxf(mq, fabsf(q4[v]));
+        mu = fmaxf(mu, fabsf(fminf(fmaxf(fmaf(c, p4[v], q4[v]), -a.qmax), a.qmax)));
+      }
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+      mq = fmaxf(mq, __shfl_xor(mq, off));
+      mu = fmaxf(mu, __shfl_xor(mu, off));
+    }
+    const int k = __any(nan) ? I8_SPECIAL : i8_exponent(mq);
+    if (lane == 0) {
+      kx[wave] = k;
+      a.kexp[a.cur][r0 + wave] = k;
+    }
+    for (int rt = lane; rt < a.ld / I8_BM; rt += 64)
+      a.mx[a.cur][(size_t)rt * a.r_pad + r0 + wave] = rt == 0 ? mu : 0.f;
+  }
+  __syncthreads();
+  const int j = threadIdx.x & 7, r = r0 + j, k = kx[j], ncb = a.r_pad / 32;
+  for (int pc = threadIdx.x >> 3; pc < a.ld / 16; pc += 64) {
+    uint32_t w[QP][4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const floatx4 q4 = *reinterpret_cast<const floatx4 *>(q + (size_t)r * a.ld + pc * 16 + g * 4);
+      uint32_t dg[4], by[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dg[v] = k == I8_SPECIAL ? 0u : i8_digits(q4[v], k);
+      byte_transpose(dg, by);
+#pragma unroll
+      for (int d = 0; d < QP; ++d) w[d][g] = by[d];
+    }
+    uint8_t *out = a.Qt[a.cur] + i8_qblk(pc / 2, r / 32, ncb) * BLK + (pc & 1) * 512 +
+                   (r & 31) * 16;
+#pragma unroll
+    for (int d = 0; d < QP; ++d)
+      *reinterpret_cast<uintx4 *>(out + d * BLK) = uintx4{w[d][0], w[d][1], w[d][2], w[d][3]};
+  }
+}
+
+// Integer couplings into blocks: one wave per block, 16 couplings per lane.
+__global__ __launch_bounds__(256) void i8_pack_j_kernel(const float *__restrict__ J, int ld,
+                                                        int64_t blocks, uint8_t *__restrict__ out) {
+  const int lane = threadIdx.x & 63, nkb = ld / 32;
+  for (int64_t b = blockIdx.x * 4 + (threadIdx.x >> 6); b < blocks; b += (int64_t)gridDim.x * 4) {
+    const int rb = (int)(b / 2 % nkb), kb = (int)(b / 2 / nkb) * 2 + (int)(b & 1);
+    const float *src = J + (size_t)(rb * 32 + (lane & 31)) * ld + kb * 32 + (lane >> 5) * 16;
+    uint32_t w[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const floatx4 x = *reinterpret_cast<const floatx4 *>(src + g * 4);
+      w[g] = ((uint32_t)(int)x[0] & 255u) | (((uint32_t)(int)x[1] & 255u) << 8) |
+             (((uint32_t)(int)x[2] & 255u) << 16) | ((uint32_t)(int)x[3] << 24);
+    }
+    *reinterpret_cast<uintx4 *>(out + b * BLK + lane * 16) = uintx4{w[0], w[1], w[2], w[3]};
+  }
+}
+
+static bool i8_fits(const I8Args &a) {
+  return a.ld % I8Cfg::BM == 0 && a.r_pad % I8Cfg::BN == 0 && a.n >= 1 && a.n <= a.ld &&
+         (a.xr == 1 || a.xr == 2 || a.xr == 4 || a.xr == 8);
+}
+
+// One workgroup per CU (the register file holds one), fewer if an XCD's part
+// has fewer tiles than CUs.
+static int i8_grid(const I8Args &a, int num_cus) {
+  const int ntr = a.ld / I8Cfg::BM, ntc = a.r_pad / I8Cfg::BN, xc = NUM_XCD / a.xr;
+  const int part = ((ntr + a.xr - 1) / a.xr) * ((ntc + xc - 1) / xc);
+  const int per = std::max(num_cus / NUM_XCD, 1);
+  return NUM_XCD * std::min(part, per);
+}
+
+hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s) {
+  if (!i8_fits(a)) return hipErrorInvalidValue;
+  const int grid = i8_grid(a, num_cus);
+  if (a.wall == SI_WALL_CLAMP)
+    step_i8_kernel<SI_WALL_CLAMP><<<grid, I8Cfg::NT, 0, s>>>(a);
+  else
+    step_i8_kernel<SI_WALL_INELASTIC><<<grid, I8Cfg::NT, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+const char *i8_kernel_name() { return "step_i8x4_256x32_w4_k256_s3"; }
+
+static const void *i8_resident(int wall) {
+  return wall == SI_WALL_CLAMP ? reinterpret_cast<const void *>(&resident_i8_kernel<SI_WALL_CLAMP>)
+                               : reinterpret_cast<const void *>(&resident_i8_kernel<SI_WALL_INELASTIC>);
+}
+
+// Every workgroup of the grid must own exactly one tile: an even XCD split,
+// and no more tiles than workgroups that fit at once.
+hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups) {
+  *groups = 0;
+  if (!i8_fits(a)) return hipSuccess;
+  const int ntr = a.ld / I8Cfg::BM, ntc = a.r_pad / I8Cfg::BN;
+  if (ntr % a.xr || ntc % (NUM_XCD / a.xr) || i8_grid(a, num_cus) != ntr * ntc) return hipSuccess;
+  int per = 0;
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, i8_resident(a.wall), I8Cfg::NT, 0);
+  if (e == hipSuccess && ntr * ntc <= per * num_cus) *groups = ntr * ntc;
+  return e;
+}
+
+hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t groups,
+                              hipStream_t s) {
+  if (!i8_fits(a) || groups < 1) return hipErrorInvalidValue;
+  I8Args aa = a;
+  ResidentArgs rr = r;
+  void *args[] = {&aa, &rr};
+  return hipLaunchCooperativeKernel(i8_resident(a.wall), dim3(groups), dim3(I8Cfg::NT), args, 0, s);
+}
+
+hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s) {
+  if (a.r_pad % 8 || a.ld % I8_BM) return hipErrorInvalidValue;
+  i8_prepare_kernel<<<a.r_pad / 8, 512, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t launch_i8_pack_j(const float *J, int32_t ld, uint8_t *out, hipStream_t s) {
+  const int64_t blocks = (int64_t)(ld / 32) * (ld / 32);
+  const int64_t wg = (blocks + 3) / 4;
+  i8_pack_j_kernel<<<(int)(wg < 8192 ? wg : 8192), 256, 0, s>>>(J, ld, blocks, out);
+  return hipGetLastError();
+}
+
+}  // namespace si
