@@ -82,7 +82,8 @@ typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
  *   BF16X3_EXACTJ: J exact in BF16 (e.g. +-1); the FP32 positions split into
  *                 three BF16 pieces whose sum is the FP32 value exactly, so
  *                 every product is exact and only the FP32 accumulation
- *                 rounds (FP32-equivalent, on the BF16 matrix cores).
+ *                 rounds (FP32-equivalent, on the BF16 matrix cores); in the
+ *                 fixed point above where FP32 could be and N >= 1000.
  *   BF16X_MIXEDJ: per instance, BF16X_FP8J when J is exact in FP8 e4m3 and
  *                 BF16X_HILOJ otherwise; spring_ising_info reports the form
  *                 chosen for a single instance.

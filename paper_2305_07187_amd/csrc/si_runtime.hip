@@ -445,12 +445,20 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // replicas the split FP32 form keeps up to N = 2000 (R = 128: 17.6 against
 // 18.3; N = 2500: 28.6 against 21.1), with up to 64 to N = 4000 (26.3 against
 // 27.6; N = 6000: 57.4 against 37.4).
+// The split form of the BF16 matrix cores (BF16X3_EXACTJ: FP32 positions in
+// three planes, FP32 sums) takes the same products, and they are faster here
+// from N = 1000 on at any R (us per step, int8 against BF16: N = 600, R = 256
+// 10.9 against 10.2; N = 800, R = 512 13.1 against 12.4; N = 1000, R = 256
+// 12.6 against 13.4; N = 2000, R = 1024 21.8 against 30.8; N = 4000, R = 100
+// 28.1 against 35.7; N = 5000, R = 256 34.0 against 85.7).
 static bool i8_applies(const si_ctx *c) {
   const bool complete_integer = c->hflags[3] == 0 && c->hflags[7] == 0;
   const bool fits = (int64_t)c->n * c->hflags[6] <= 65281;
-  const bool pays = c->n > 4096 || (c->n > 2048 && c->r > 64) || (c->n > 512 && c->r >= 256);
-  return c->prm.precision == SI_PREC_FP32 && c->prm.order == SI_ORDER_PAPER && c->user_tile == 0 &&
-         !c->n_inst && complete_integer && fits && pays;
+  const bool split = c->prm.precision == SI_PREC_BF16X3_EXACTJ;
+  const bool pays = split ? c->n >= 1000
+                          : c->n > 4096 || (c->n > 2048 && c->r > 64) || (c->n > 512 && c->r >= 256);
+  return (split || c->prm.precision == SI_PREC_FP32) && c->prm.order == SI_ORDER_PAPER &&
+         c->user_tile == 0 && !c->n_inst && complete_integer && fits && pays;
 }
 
 static bool i8_on(const si_ctx *c) { return c->i8.Jt && c->ksplit_mode == 0 && !c->i8_off; }
@@ -511,9 +519,15 @@ static hipError_t i8_init(si_ctx *c) {
 }
 
 // Digits, scales and maxima of the current FP32 state: after every call that
-// wrote the state or the schedule by other means than the int8 step.
+// wrote the state or the schedule by other means than the int8 step.  A
+// context that has the int8 form but is off it gets its BF16 planes, which
+// the int8 step does not write.
 static hipError_t i8_refresh(si_ctx *c) {
-  if (!i8_on(c)) return hipSuccess;
+  if (!i8_on(c)) {
+    if (!c->i8.Jt || !c->qplanes) return hipSuccess;
+    return launch_split_planes(c->q[c->cur], c->qb[c->cur], (int64_t)c->n_pad * c->r_pad,
+                               c->qplanes, c->stream);
+  }
   c->i8.cur = c->cur;
   c->i8.t = c->t;
   return launch_i8_prepare(c->i8, c->stream);
@@ -1307,8 +1321,8 @@ static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
 
 static si_status do_steps(si_ctx *c, int32_t n_steps) {
   if (c->n_inst) return do_steps_batch(c, n_steps);
-  if (c->qplanes) return do_steps_lowp(c, n_steps);
   if (i8_on(c)) return do_steps_i8(c, n_steps);
+  if (c->qplanes) return do_steps_lowp(c, n_steps);
   return do_steps_f32(c, n_steps);
 }
 
@@ -1694,6 +1708,13 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   c->epoch++;
   if (c->n_inst) return autotune_batch(c, steps, best_tile, best_us);
   const int64_t NR = (int64_t)c->n_pad * c->r_pad;
+  // the int8 form, where the context has it, is timed against the fastest
+  // tile of the others below
+  const bool has_i8 = c->i8.Jt && c->ksplit_mode == 0;
+  if (has_i8) {
+    c->i8_off = true;
+    SI_HIP(c, i8_refresh(c));
+  }
   // saved state: q and p in the adjoint's segment buffer, the BF16 planes of
   // q in a buffer of their own; both kept for later calls
   if (!c->adj_seg || c->adj_seg_cap < 2 * NR) {
@@ -1723,10 +1744,6 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
     ~KeepEvery() { c->e_every = v; }
   } keep{c, c->e_every};
   c->e_every = 0;
-  // the int8 form, where the context has it, is timed against the fastest
-  // FP32 tile below
-  const bool has_i8 = c->i8.Jt && c->ksplit_mode == 0;
-  c->i8_off = has_i8;
   const int32_t last = lowp ? TILE_BF16_LAST : TILE_F32_LAST;
   const int32_t timed = steps - 1 > 0 ? steps - 1 : 1;
   int32_t best = tile0;
@@ -2015,7 +2032,7 @@ si_status spring_ising_set_state(si_ctx *c, const float *x, const float *p, int3
   }
   SI_HIP(c, launch_pack_state(x, c->n, c->r, c->q[c->cur], c->n_pad, c->r_pad, c->stream));
   SI_HIP(c, launch_pack_state(p, c->n, c->r, c->p[c->cur], c->n_pad, c->r_pad, c->stream));
-  if (c->qplanes)
+  if (c->qplanes && !c->i8.Jt)  // (i8_refresh otherwise)
     SI_HIP(c, launch_split_planes(c->q[c->cur], c->qb[c->cur], (int64_t)c->n_pad * c->r_pad,
                                   c->qplanes, c->stream));
   c->t = t;

@@ -205,3 +205,51 @@ def test_route():
         assert m.info()["kernel_name"].startswith(NAME) == want, (kw, Jc.shape)
         m.run(2)
         m.close()
+
+
+@pytest.mark.parametrize("n,r,jmax", [(1000, 1, 1), (1000, 33, 65), (1025, 256, 1), (2000, 64, 32)])
+def test_exact_split_form(n, r, jmax):
+    # the BF16 matrix cores' exact form takes the same products: one step to
+    # the same bound, and the BF16 planes follow when a call takes it off them
+    import torch
+    si = ensure_built()
+    announce(f"fixed-point step of bf16x3_exactj N={n} R={r} |J|={jmax}")
+    J = instances.make_pm1(n, n) * np.float32(jmax)
+    x, p = _signed(n, r, 1, 1.0), _signed(n, r, 2, 1.0)
+    S = 20
+    m = si.SpringIsing(to_dev(J), to_dev(x), to_dev(p), total_steps=S, precision="bf16x3_exactj")
+    assert m.info()["kernel_name"].startswith(NAME)
+    m.set_state(to_dev(x), to_dev(p), 3)
+    dts, zetas = oracle_schedules(S)
+    J64 = J.astype(np.float64)
+
+    def check_step(fp32_sum):
+        x0, p0, t = m.state()
+        torch.cuda.synchronize()
+        m.step()
+        xg, pg, _ = m.state()
+        torch.cuda.synchronize()
+        Q0, P0 = x0.cpu().numpy().T.astype(np.float64), p0.cpu().numpy().T.astype(np.float64)
+        dt, zeta = float(dts[t]), float(zetas[t])
+        Q1, P1 = oracle.step(J64, Q0, P0, dt, zeta, qmax=QMAX)
+        qb, pb = _bounds(J64, Q0, P0, J64 @ Q0, dt, zeta)
+        if fp32_sum:  # 3 n products added in FP32, in any order
+            pb = pb + dt * zeta * 3 * n * 2.0 ** -24 * (np.abs(J64) @ np.abs(Q0))
+        assert np.all(np.abs(xg.cpu().numpy().T - Q1) <= qb)
+        assert np.all(np.abs(pg.cpu().numpy().T - P1) <= pb)
+
+    check_step(False)
+    m.set_ksplit(1)  # off the fixed point, and back, also through autotune
+    assert not m.info()["kernel_name"].startswith(NAME)
+    check_step(True)
+    m.set_ksplit(0)
+    assert m.info()["kernel_name"].startswith(NAME)
+    check_step(False)
+    m.autotune(2)
+    check_step(not m.info()["kernel_name"].startswith(NAME))
+    m.close()
+    si.spring_ising_tile_cache_clear()
+    f = si.SpringIsing(to_dev(instances.make_pm1(999, 1)), to_dev(instances.make_x0(999, r, 1)),
+                       total_steps=2, precision="bf16x3_exactj")
+    assert not f.info()["kernel_name"].startswith(NAME)
+    f.close()
