@@ -36,6 +36,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -636,12 +637,13 @@ def main():
     value = n * r * iters * args.steps / elapsed
     fp32_line = args.precision == "fp32"
     peak = PEAK_FP32_MFMA_TFLOPS if fp32_line else PEAK_BF16_MFMA_TFLOPS
-    # the fixed-point form of the FP32 step runs four int8 products per
-    # coupling product (each position in four base-256 digits), so a quarter
-    # of the int8 rate is what it can reach in terms of the product's flop
-    fixed_point = info["kernel_name"].startswith("step_i8x4")
+    # the fixed-point form of the FP32 step runs several int8 products per
+    # coupling product (four, with each position in four base-256 digits; ten,
+    # with the couplings in digits as well), so that fraction of the int8 rate
+    # is what it can reach in terms of the product's flop
+    fixed_point = re.match(r"step_i8x(\d+)_", info["kernel_name"])
     if fixed_point:
-        peak = PEAK_INT8_MFMA_TOPS / 4
+        peak = PEAK_INT8_MFMA_TOPS / int(fixed_point.group(1))
     out = {
         "metric": f"spin-updates/s (N*R*steps/s) at N={n}",
         "value": value,

@@ -73,7 +73,9 @@ typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
  *                 and set_ksplit 0 and where it is faster, the product is
  *                 formed in fixed point on the int8 matrix cores: every
  *                 position to 2^-31 of its replica's largest, sums exact,
- *                 the result rounded to FP32.
+ *                 the result rounded to FP32.  Other couplings up to N =
+ *                 32000 likewise, each to 2^-31 of its row's largest, where
+ *                 every row is dense and without outliers.
  *   BF16X_FP8J  : J stored as FP8 e4m3 (must be exact, e.g. +-1), positions
  *                 as a BF16 copy of the FP32 master state.
  *   BF16X_BF16J : J stored as BF16 (must be exact), positions BF16.
@@ -82,8 +84,8 @@ typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
  *   BF16X3_EXACTJ: J exact in BF16 (e.g. +-1); the FP32 positions split into
  *                 three BF16 pieces whose sum is the FP32 value exactly, so
  *                 every product is exact and only the FP32 accumulation
- *                 rounds (FP32-equivalent, on the BF16 matrix cores); in the
- *                 fixed point above where FP32 could be and N >= 1000.
+ *                 rounds (FP32-equivalent, on the BF16 matrix cores); integer J
+ *                 in the fixed point above where N >= 1000.
  *   BF16X_MIXEDJ: per instance, BF16X_FP8J when J is exact in FP8 e4m3 and
  *                 BF16X_HILOJ otherwise; spring_ising_info reports the form
  *                 chosen for a single instance.

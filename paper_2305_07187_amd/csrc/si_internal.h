@@ -98,20 +98,25 @@ hipError_t resident_f32_groups_per_cu(int32_t tile, int32_t order, int32_t wall,
 hipError_t launch_resident_f32(int32_t tile, const StepArgs &a, const ResidentArgs &r,
                                hipStream_t s);
 
-// FP32 step with the product on the int8 matrix cores (integer couplings of
-// complete graphs; see si_step_i8.hip).
+// FP32 step with the product on the int8 matrix cores (complete graphs; see
+// si_step_i8.hip).
 constexpr int I8_DIGITS = 4;       // base-256 digits per position
-constexpr int I8_BM = 256, I8_BN = 32, I8_BKB = 8;  // tile, contraction blocks of 32 per slab
+constexpr int I8_JDIGITS = 4;      // per real coupling (integer couplings: one)
+constexpr int I8_BM = 256, I8_BM_REAL = 128;  // rows of a tile
+constexpr int I8_N_REAL = 32000;   // 4 N 128^2 < 2^31
+constexpr float I8_CREST = 32.f;   // largest over rms of a row of real couplings, at most
 constexpr int I8_SPECIAL = 1 << 20;  // scale exponent of a replica with non-finite positions
 struct I8Args {
-  const uint8_t *Jt;   // int8 J in 1 KB blocks [ld/32][ld/32]
+  const uint8_t *Jt;   // digits of J in 1 KB blocks
+  const int *jexp;     // scale exponent per row of real couplings; null: integers
   const float *J;      // FP32 J [ld][ld]
-  uint8_t *Qt[2];      // digits of the positions [r_pad/32][ld/32][I8_DIGITS] blocks
+  uint8_t *Qt[2];      // digits of the positions in 1 KB blocks
   int *kexp[2];        // scale exponent per replica: digits are of rint(q 2^kexp)
-  float *mx[2];        // [ld/I8_BM][r_pad]: largest |q| after the next step, per row tile
+  float *mx[2];        // [ld/bm][r_pad]: largest |q| after the next step, per row tile
   float *q[2], *p[2];  // [r_pad][ld]
   const float *dt, *zeta, *h;
   int32_t cur, t, total_steps, ld, n, r_pad;
+  int32_t bm;          // rows of a tile: I8_BM, real couplings I8_BM_REAL
   int32_t xr;          // XCDs the row tiles are split over (1, 2, 4 or 8)
   float k, inv_m, qmax, pmax;
   int32_t wall;
@@ -121,9 +126,14 @@ hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s);
 hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups);
 hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t groups,
                               hipStream_t s);
-const char *i8_kernel_name();
+int32_t i8_xcd_rows(const I8Args &a);
+const char *i8_kernel_name(const I8Args &a);
 hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s);
-hipError_t launch_i8_pack_j(const float *J, int32_t ld, uint8_t *out, hipStream_t s);
+// *heavy (device): set if a row's largest coupling is too far above the rest.
+hipError_t launch_i8_rows(const float *J, int32_t ld, int32_t n, int32_t *jexp, int32_t *heavy,
+                          hipStream_t s);
+hipError_t launch_i8_pack_j(const float *J, int32_t ld, const int32_t *jexp, uint8_t *out,
+                            hipStream_t s);
 
 // Batched form: per-instance buffers and the work list of one grouped launch.
 // Batch tiles (both precisions): 1 = 128 x 64 work items, 2 = 64 x 64.

@@ -451,33 +451,71 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // 10.9 against 10.2; N = 800, R = 512 13.1 against 12.4; N = 1000, R = 256
 // 12.6 against 13.4; N = 2000, R = 1024 21.8 against 30.8; N = 4000, R = 100
 // 28.1 against 35.7; N = 5000, R = 256 34.0 against 85.7).
+//
+// Real couplings take four digits as well (each to 2^-31 of its row's
+// largest) and ten of the sixteen digit products; those left out lie below
+// 2^-31 of the largest product.  Rows must be dense and without outliers (see
+// i8_rows_kernel).  A tile of ten products is long (8 us and 12 us per 1000
+// spins, even for one), so they pay where N R fills the chip, from N R =
+// 640000 on (us per step, int8 against FP32: N = 600, R = 1024 16.9 against
+// 16.9; N = 1000, R = 512 21.2 against 16.9, R = 1024 21.7 against 26.7;
+// N = 2000, R = 256 32.2 against 26.9, R = 512 32.6 against 42.9, R = 1024
+// 41.3 against 74.1; N = 2500, R = 256 38.0 against 51.1; N = 4000, R = 128
+// 54.8 against 42.5; N = 8000, R = 50 102 against 77, R = 100 108 against 143,
+// R = 2048 1050 against 2080).
+static bool i8_integer(const si_ctx *c) {
+  return c->hflags[3] == 0 && (int64_t)c->n * c->hflags[6] <= 65281;
+}
+
 static bool i8_applies(const si_ctx *c) {
-  const bool complete_integer = c->hflags[3] == 0 && c->hflags[7] == 0;
-  const bool fits = (int64_t)c->n * c->hflags[6] <= 65281;
+  const bool integer = i8_integer(c);
+  if (integer ? c->hflags[7] != 0 : c->n > I8_N_REAL || c->prm.precision != SI_PREC_FP32)
+    return false;
   const bool split = c->prm.precision == SI_PREC_BF16X3_EXACTJ;
-  const bool pays = split ? c->n >= 1000
-                          : c->n > 4096 || (c->n > 2048 && c->r > 64) || (c->n > 512 && c->r >= 256);
+  const bool pays =
+      !integer ? c->n > 512 && (int64_t)c->n * round_up(c->r, 64) >= 640000
+      : split  ? c->n >= 1000
+               : c->n > 4096 || (c->n > 2048 && c->r > 64) || (c->n > 512 && c->r >= 256);
   return (split || c->prm.precision == SI_PREC_FP32) && c->prm.order == SI_ORDER_PAPER &&
-         c->user_tile == 0 && !c->n_inst && complete_integer && fits && pays;
+         c->user_tile == 0 && !c->n_inst && pays;
 }
 
 static bool i8_on(const si_ctx *c) { return c->i8.Jt && c->ksplit_mode == 0 && !c->i8_off; }
 
-// Buffers of the int8 form in one allocation.  Without the memory for it the
+// Buffers of the int8 form, the large ones in one allocation.  Without the memory for it the
 // context simply runs on the FP32 matrix cores.
 static hipError_t i8_init(si_ctx *c) {
   if (!i8_applies(c)) return hipSuccess;
-  const int64_t nn = (int64_t)c->n_pad * c->n_pad, nr = (int64_t)c->n_pad * c->r_pad;
-  const int64_t mxb = round_up((int64_t)(c->n_pad / I8_BM) * c->r_pad * 4, 256);
+  const bool real = !i8_integer(c);
+  const int32_t bm = real ? I8_BM_REAL : I8_BM;
+  const int64_t jb = (int64_t)c->n_pad * c->n_pad * (real ? I8_JDIGITS : 1);
+  const int64_t nr = (int64_t)c->n_pad * c->r_pad;
+  const int64_t mxb = round_up((int64_t)(c->n_pad / bm) * c->r_pad * 4, 256);
   const int64_t kb = round_up((int64_t)c->r_pad * 4, 256);
+  int32_t *jexp = nullptr;
   uint8_t *buf = nullptr;
-  if (c->alloc(&buf, nn + 2 * (nr * I8_DIGITS + mxb + kb)) != hipSuccess) {
+  if (real) {
+    // (see i8_rows_kernel: not for rows with couplings far above the rest)
+    if (c->alloc(&jexp, c->n_pad + 1) != hipSuccess) {
+      (void)hipGetLastError();
+      return hipSuccess;
+    }
+    int32_t heavy = 0, *flag = jexp + c->n_pad;
+    hipError_t e = launch_zero_i32(flag, 1, c->stream);
+    if (e == hipSuccess) e = launch_i8_rows(c->J, c->n_pad, c->n, jexp, flag, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&heavy, flag, 4, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess || heavy) return e;
+  }
+  if (c->alloc(&buf, jb + 2 * (nr * I8_DIGITS + mxb + kb)) != hipSuccess) {
     (void)hipGetLastError();
     return hipSuccess;
   }
   I8Args &a = c->i8;
   a.J = c->J;
-  uint8_t *at = buf + nn;
+  a.jexp = jexp;
+  a.bm = bm;
+  uint8_t *at = buf + jb;
   for (int b = 0; b < 2; ++b) {
     a.Qt[b] = at;
     at += nr * I8_DIGITS;
@@ -499,21 +537,8 @@ static hipError_t i8_init(si_ctx *c) {
   a.qmax = c->prm.qmax;
   a.pmax = c->prm.pmax;
   a.wall = c->prm.wall;
-  // the split of the tiles over the XCDs' L2s that fetches least: every row
-  // group reads all of its column group's digits and the other way round
-  const int64_t ntr = c->n_pad / I8_BM, ntc = c->r_pad / I8_BN;
-  double least = 0.0;
-  for (int32_t xr = 1; xr <= NUM_XCD; xr *= 2) {
-    const int64_t xc = NUM_XCD / xr;
-    const double pad = (double)(round_up(ntr, xr) * round_up(ntc, xc)) / (double)(ntr * ntc);
-    const int64_t bands = ((ntr + xr - 1) / xr + 3) / 4;  // sweeps over its columns
-    const double cost = pad * ((double)nn * xc + (double)nr * I8_DIGITS * xr * bands);
-    if (xr == 1 || cost < least) {
-      least = cost;
-      a.xr = xr;
-    }
-  }
-  hipError_t e = launch_i8_pack_j(c->J, c->n_pad, buf, c->stream);
+  a.xr = i8_xcd_rows(a);
+  hipError_t e = launch_i8_pack_j(c->J, c->n_pad, jexp, buf, c->stream);
   if (e == hipSuccess) a.Jt = buf;
   return e;
 }
@@ -817,7 +842,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
     return fail(SI_ERR_INVALID, "init: tile %d cannot run precision %d", bad, prm->precision);
   }
   const TileShape ts = shape_of(prm->precision, c->tile);
-  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, i8_applies(c) ? I8_BM : 128));
+  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, i8_applies(c) && i8_integer(c) ? I8_BM : 128));
   c->r_pad = (int32_t)round_up(r, ts.bn > 64 ? ts.bn : 64);
   const bool j_integer = c->hflags[3] == 0;
   const bool need_bf16 = prm->precision == SI_PREC_BF16X_BF16J ||
@@ -2211,7 +2236,7 @@ si_status spring_ising_info(si_ctx *c, si_info *info) {
     snprintf(info->kernel_name, sizeof info->kernel_name, "step_batch_%s_%dx%d_x%d",
              c->b_lowp ? "bf16" : "f32", batch_tile_rows(c->tile), BATCH_BN, c->n_inst);
   else if (i8_on(c))
-    snprintf(info->kernel_name, sizeof info->kernel_name, "%s", i8_kernel_name());
+    snprintf(info->kernel_name, sizeof info->kernel_name, "%s", i8_kernel_name(c->i8));
   else if (split_for(c, c->tile) > 1)
     snprintf(info->kernel_name, sizeof info->kernel_name, "%s_ks%d",
              shape_of(c->prm.precision, c->tile).name, split_for(c, c->tile));

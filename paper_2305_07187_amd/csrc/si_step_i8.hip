@@ -61,13 +61,14 @@ constexpr int QP = I8_DIGITS;
 constexpr int BLK = 1024;  // bytes of one 32 x 32 operand block
 }  // namespace
 
-// 1 KB block of J's row block rb, or of the first digit of the positions'
-// column block cb, at contraction block kb.  The contraction is outermost:
+// First digit's 1 KB block (of jd, or QP) of J's row block rb, or of the
+// positions' column block cb, at contraction block kb.  The contraction is outermost:
 // all workgroups walk it together, so what they read at one time lies in
 // one consecutive range and spreads over every channel of the caches and the
 // memory (row blocks outermost would put it at strides of a power of two).
+template <int JD>
 __device__ __forceinline__ size_t i8_jblk(int kb, int rb, int nrb) {
-  return ((size_t)(kb >> 1) * nrb + rb) * 2 + (kb & 1);
+  return (((size_t)(kb >> 1) * nrb + rb) * 2 + (kb & 1)) * JD;
 }
 __device__ __forceinline__ size_t i8_qblk(int kb, int cb, int ncb) {
   return (((size_t)(kb >> 1) * ncb + cb) * 2 + (kb & 1)) * QP;
@@ -155,32 +156,43 @@ __device__ __forceinline__ void q_wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F
 // per tile nk slab barriers (the slab has been read, the next one has
 // landed) and one when F is in LDS.
 // ---------------------------------------------------------------------------
+template <int JD_>
 struct I8Cfg {
-  static constexpr int BM = I8_BM, BN = I8_BN, BKB = I8_BKB, STAGES = 3;
+  static constexpr int JD = JD_;               // digits of J
+  static constexpr bool REAL = JD > 1;
+  static constexpr int BM = REAL ? I8_BM_REAL : I8_BM, BN = REAL ? 64 : 32;
+  static constexpr int BKB = REAL ? 4 : 8, STAGES = 3;  // contraction blocks per slab, slabs
   static constexpr int NM = 4, NS = 4, NT = 64 * (NM + NS);
-  static constexpr int SLOT = BKB * QP * BLK;  // digits of one slab
-  static constexpr int L = BKB * QP / NS;      // 1 KB copies per state wave and slab
-  static constexpr int PD = 8;                 // contraction blocks of J held ahead
+  static constexpr int RB = BM / 32 / NM, NCB = BN / 32;  // blocks of a matrix wave
+  static constexpr int SLOT = BKB * NCB * QP * BLK;       // digits of one slab
+  static constexpr int L = BKB * NCB * QP / NS;  // 1 KB copies per state wave and slab
+  static constexpr int PD = REAL ? 4 : 8;      // contraction blocks of J held ahead (a slab)
   static constexpr int LDT = BM + 4;           // floats per column of F
   static constexpr int COLS = BN / NS;         // columns per state wave
-  static constexpr int SETS = COLS / 4;
-  static_assert(BM == 64 * NM && BN == 32 && COLS == 8 && BKB % PD == 0, "tile");
-  static_assert(BKB == 2 * NS && (STAGES - 1) * L <= 63 && STAGES >= 2, "ring");
+  static constexpr int LPC = BM / 4;           // lanes per column, four spins each
+  static constexpr int PERL = COLS * LPC / 64;  // columns per lane
+  static constexpr int SETS = PERL / 4;
+  static_assert(BM == 32 * RB * NM && PERL == 8 && BKB % PD == 0, "tile");
+  static_assert(BKB * NCB == 2 * NS && (STAGES - 1) * L <= 63 && STAGES >= 2, "ring");
 };
+using I8Int = I8Cfg<1>;
+using I8Real = I8Cfg<I8_JDIGITS>;
 
+template <class C>
 struct I8Smem {
-  __attribute__((aligned(16))) uint8_t ring[I8Cfg::STAGES * I8Cfg::SLOT];
-  __attribute__((aligned(16))) float tile[I8Cfg::BN * I8Cfg::LDT];
+  __attribute__((aligned(16))) uint8_t ring[C::STAGES * C::SLOT];
+  __attribute__((aligned(16))) float tile[C::BN * C::LDT];
 };
 
 // Tile i of this workgroup.  Every XCD (workgroup b runs on XCD b % 8) takes
 // an xr-th of the row tiles by an xc-th of the column tiles (xr xc = 8), so
 // that its L2 fetches that part of J and of the digits only, and walks it in
 // bands of four row tiles, column by column, so that a band of J stays there.
+template <class C>
 struct I8Walk {
   int pr, pc, r0, c0, nr, nc, first, stride, count;
   __device__ __forceinline__ I8Walk(const I8Args &a) {
-    const int ntr = a.ld / I8Cfg::BM, ntc = a.r_pad / I8Cfg::BN, xc = NUM_XCD / a.xr;
+    const int ntr = a.ld / C::BM, ntc = a.r_pad / C::BN, xc = NUM_XCD / a.xr;
     const int x = blockIdx.x % NUM_XCD;
     pr = (ntr + a.xr - 1) / a.xr;
     pc = (ntc + xc - 1) / xc;
@@ -196,14 +208,15 @@ struct I8Walk {
   __device__ __forceinline__ void at(int i, int &m0, int &n0) const {
     const int t = first + i * stride, band = t / (4 * nc), rows = min(4, nr - band * 4);
     const int u = t - band * 4 * nc;
-    m0 = (r0 + band * 4 + u % rows) * I8Cfg::BM;
-    n0 = (c0 + u / rows) * I8Cfg::BN;
+    m0 = (r0 + band * 4 + u % rows) * C::BM;
+    n0 = (c0 + u / rows) * C::BN;
   }
 };
 
 // The matrix waves' part of one step.
-__device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk &walk, I8Smem &sm) {
-  using C = I8Cfg;
+__device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk<I8Int> &walk,
+                                          I8Smem<I8Int> &sm) {
+  using C = I8Int;
   constexpr int NB = C::BKB, PD = C::PD;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nk = (a.n + 32 * NB - 1) / (32 * NB), nrb = a.ld / 32;
@@ -211,7 +224,7 @@ __device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk &walk, I
   int m0, n0;
   auto source = [&](int i) {
     walk.at(i, m0, n0);
-    return a.Jt + i8_jblk(0, m0 / 32 + wave * 2, nrb) * BLK + lane * 16;
+    return a.Jt + i8_jblk<1>(0, m0 / 32 + wave * 2, nrb) * BLK + lane * 16;
   };
   intx4 fa[PD][2], fb[2][QP];
   auto load_a = [&](const uint8_t *s, int i, intx4 (&x)[2]) {
@@ -290,17 +303,139 @@ __device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk &walk, I
   }
 }
 
-// The state waves' part of one step: wave sw owns columns 8 sw .. 8 sw + 7 of
-// a tile, a lane four spins of each.
-template <int WALL>
-__device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8Smem &sm) {
-  using C = I8Cfg;
+// The same for couplings in four digits: 32 x 64 per wave, ten products per
+// pair of blocks, summed by their weight 256^o (o = digit of J + digit of
+// q - 3).  A column block's digits are read for the next contraction block as
+// soon as its ten products are issued, while the other's run.
+//
+// Measured (us per step, FP32 matrix cores before): N = 2000, R = 1024 41.3
+// (74.1), N = 4000, R = 2048 275 (532), N = 8000, R = 2048 1050 (2080); final
+// positions against 64 bits after 5 steps at the last: 4.8e-8 (1.0e-6).
+// Bound: the products; a loop of them alone takes 906 us at the last size
+// (42 .. 48 cycles each instead of 32; 800 us with couplings of one digit),
+// with the loads of J 950, with those and the digits' reads 1050.  Reordered
+// for longer distances between dependent sums 1050, a shorter look-ahead of
+// J (2 blocks) 1155.
+__device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk<I8Real> &walk,
+                                          I8Smem<I8Real> &sm) {
+  using C = I8Real;
+  constexpr int NB = C::BKB, PD = C::PD, JD = C::JD;
+  static_assert(JD == 4 && QP == 4 && C::RB == 1 && C::NCB == 2, "products");
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nk = (a.n + 32 * NB - 1) / (32 * NB), nrb = a.ld / 32;
+  const size_t pair = (size_t)nrb * 2 * JD * BLK;  // two contraction blocks further
+  int m0, n0;
+  auto source = [&](int i) {
+    walk.at(i, m0, n0);
+    return a.Jt + i8_jblk<JD>(0, m0 / 32 + wave, nrb) * BLK + lane * 16;
+  };
+  intx4 fa[PD][JD], fb[2][QP];
+  auto load_a = [&](const uint8_t *s, int i, intx4 (&x)[JD]) {
+    s += (size_t)(i / 2) * pair + (i & 1) * JD * BLK;
+#pragma unroll
+    for (int d = 0; d < JD; ++d) x[d] = *reinterpret_cast<const intx4 *>(s + d * BLK);
+  };
+  // (slab: [pair of blocks][column block][block of the pair][digit])
+  auto read_b = [&](const uint8_t *st, int i, int c) {
+#pragma unroll
+    for (int d = 0; d < QP; ++d)
+      fb[c][d] = *reinterpret_cast<const intx4 *>(
+          st + ((((i >> 1) * 2 + c) * 2 + (i & 1)) * QP + d) * BLK);
+  };
+  const uint8_t *cur = source(0), *nxt = cur;
+#pragma unroll
+  for (int i = 0; i < PD; ++i) load_a(cur, i, fa[i]);
+  int rd = 0;
+  const uint8_t *st = sm.ring + lane * 16;
+  q_barrier();  // the first slab has landed
+  read_b(st, 0, 0);
+  read_b(st, 0, 1);
+  for (int tile = 0; tile < walk.count; ++tile) {
+    intx16 acc[2][4];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[c][o][v] = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      // the slab after this one (of the next tile; past the last: this one)
+      nxt = kt + 1 < nk ? cur + (NB / 2) * pair : tile + 1 < walk.count ? source(tile + 1) : cur;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          __builtin_amdgcn_sched_barrier(0);
+          // digits of J and of q
+          constexpr int PJ[10] = {0, 1, 2, 1, 2, 3, 2, 3, 3, 3}, PQ[10] = {3, 3, 3, 2, 2, 3, 1, 1, 2, 0};
+#pragma unroll
+          for (int e = 0; e < 10; ++e) {
+            const int o = PJ[e] + PQ[e] - 3;
+            acc[c][o] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i % PD][PJ[e]], fb[c][PQ[e]],
+                                                              acc[c][o], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (i + 1 < NB) {
+            read_b(st, i + 1, c);
+          } else {
+            if (c == 0) {
+              q_wait_lds();  // this wave has read the slab
+              q_barrier();
+              rd = rd + 1 == C::STAGES ? 0 : rd + 1;
+              st = sm.ring + rd * C::SLOT + lane * 16;
+            }
+            read_b(st, 0, c);  // (past the last slab: not used)
+          }
+        }
+        load_a(i + PD < NB ? cur : nxt, (i + PD) % NB, fa[i % PD]);
+      }
+      cur = nxt;
+    }
+    // F = sum_o 256^(o + 3) acc_o 2^-(k + row's exponent): the leading sums
+    // are exact in FP32 up to 2^24, each further one weighs 256 times less
+    walk.at(tile, m0, n0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int kcol = a.kexp[a.cur][n0 + c * 32 + (lane & 31)];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int row = wave * 32 + g * 8 + (lane / 32) * 4;
+        const intx4 kj = *reinterpret_cast<const intx4 *>(a.jexp + m0 + row);
+        float f[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int e = 4 * g + v;
+          float x = fmaf((float)acc[c][1][e], 256.f, (float)acc[c][0][e]);
+          x = fmaf((float)acc[c][2][e], 65536.f, x);
+          x = fmaf((float)acc[c][3][e], 16777216.f, x);
+          f[v] = ldexpf(x, 24 - kcol - kj[v]);
+        }
+        epi_put(sm.tile, C::LDT, row, c * 32 + (lane & 31), f[0], f[1], f[2], f[3]);
+      }
+    }
+    q_wait_lds();
+    q_barrier();  // F is in LDS
+  }
+}
+
+// The state waves' part of one step: wave sw owns COLS columns of a tile, a
+// lane four spins of eight of them.
+template <class C, int WALL>
+__device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk, I8Smem<C> &sm) {
   const int sw = __builtin_amdgcn_readfirstlane(((int)threadIdx.x >> 6) - C::NM);
-  const int lane = threadIdx.x & 63, row = lane * 4, nx = a.cur ^ 1;
+  const int lane = threadIdx.x & 63, row = lane % C::LPC * 4, nx = a.cur ^ 1;
+  const int lc = lane / C::LPC * C::PERL;  // first of the lane's columns among the wave's
+  // entry of the lane's column cc in a vector that holds one column per lane
+  auto of = [&](int v, int cc) {
+    const int x = __builtin_amdgcn_readlane(v, cc);
+    if constexpr (C::LPC == 64) return x;
+    const int y = __builtin_amdgcn_readlane(v, C::PERL + cc);
+    return lc ? y : x;
+  };
   const int nk = (a.n + 32 * C::BKB - 1) / (32 * C::BKB), ncb = a.r_pad / 32;
   const int ntr = a.ld / C::BM;
   int m0, n0;
-  // copies: wave sw takes the two contraction blocks of pair sw of each slab
+  // copies: wave sw takes two contraction blocks of one column block of each slab
   const size_t step = (size_t)ncb * (C::BKB * QP) * BLK;
   const uint8_t *src = nullptr;
   int itile = 0, ikt = 0, islot = 0;  // tile and slab of the next copy, its slot
@@ -309,7 +444,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
     if (ikt == 0) {
       int m, n;
       walk.at(itile, m, n);
-      src = a.Qt[a.cur] + i8_qblk(2 * sw, n / 32, ncb) * BLK + lane * 16;
+      src = a.Qt[a.cur] + i8_qblk(sw / C::NCB * 2, n / 32 + sw % C::NCB, ncb) * BLK + lane * 16;
     }
     uint8_t *dst = sm.ring + islot * C::SLOT + sw * C::L * BLK;
 #pragma unroll
@@ -346,7 +481,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
   const float dt = a.dt[a.t], zeta = a.zeta[a.t];
   const float cdt = dt * a.inv_m;
   const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
-  floatx4 q4[C::COLS], p4[C::COLS], h4;
+  floatx4 q4[C::PERL], p4[C::PERL], h4;
   int kin = 0;
   // p' of tile (m, n) from F in LDS, and the next step's maxima
   auto finish = [&](int m, int n) {
@@ -355,10 +490,10 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
       uint32_t um[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const int col = sw * C::COLS + set * 4 + c, cc = set * 4 + c;
+        const int cc = set * 4 + c, col = sw * C::COLS + lc + cc;
         const size_t off = (size_t)(n + col) * a.ld + m + row;
         floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
-        if (__builtin_amdgcn_readlane(kin, cc) == I8_SPECIAL) {
+        if (of(kin, cc) == I8_SPECIAL) {
           // non-finite positions given by the caller: FP32 products, summed
           f = floatx4{0.f, 0.f, 0.f, 0.f};
           for (int i = 0; i < a.n; ++i) {
@@ -384,9 +519,9 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
       float mx = fmaxf(fmaxf(__uint_as_float(um[0]), __uint_as_float(um[1])),
                        fmaxf(__uint_as_float(um[2]), __uint_as_float(um[3])));
 #pragma unroll
-      for (int off = 4; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      if (lane < 4)
-        a.mx[nx][(size_t)(m / C::BM) * a.r_pad + n + sw * C::COLS + set * 4 + lane] = mx;
+      for (int off = 4; off < C::LPC; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+      if (lane % C::LPC < 4)
+        a.mx[nx][(size_t)(m / C::BM) * a.r_pad + n + sw * C::COLS + lc + set * 4 + (lane & 3)] = mx;
       tick();
     }
   };
@@ -396,32 +531,32 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
     walk.at(tile, m0, n0);
     const int col0 = n0 + sw * C::COLS;
     // scales of the new positions: maxima of this wave's columns, one column
-    // and every eighth row tile per lane
+    // and every (64 / COLS)th row tile per lane
     float mx = 0.f;
-    for (int rt = lane >> 3; rt < ntr; rt += 8)
-      mx = fmaxf(mx, a.mx[a.cur][(size_t)rt * a.r_pad + col0 + (lane & 7)]);
-    kin = a.kexp[a.cur][col0 + (lane & 7)];
+    const int mine = col0 + lane % C::COLS;
+    for (int rt = lane / C::COLS; rt < ntr; rt += 64 / C::COLS)
+      mx = fmaxf(mx, a.mx[a.cur][(size_t)rt * a.r_pad + mine]);
+    kin = a.kexp[a.cur][mine];
     h4 = floatx4{0.f, 0.f, 0.f, 0.f};
     if (a.h) h4 = *reinterpret_cast<const floatx4 *>(a.h + m0 + row);
 #pragma unroll
-    for (int c = 0; c < C::COLS; ++c) {
-      const size_t off = (size_t)(col0 + c) * a.ld + m0 + row;
+    for (int c = 0; c < C::PERL; ++c) {
+      const size_t off = (size_t)(col0 + lc + c) * a.ld + m0 + row;
       q4[c] = *reinterpret_cast<const floatx4 *>(a.q[a.cur] + off);
       p4[c] = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 8));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+#pragma unroll
+    for (int off = C::COLS; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     const int kout = i8_exponent(mx);
     if (m0 == 0 && lane < C::COLS) a.kexp[nx][col0 + lane] = kout;
     tick();
-    const int spin = m0 + (lane >> 2) * 16;
+    const int spin = m0 + (lane % C::LPC >> 2) * 16;
 #pragma unroll
     for (int set = 0; set < C::SETS; ++set) {
       uint32_t w[QP][4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const int cc = set * 4 + c, k = __builtin_amdgcn_readlane(kout, cc);
+        const int cc = set * 4 + c, k = of(kout, cc);
         uint32_t dg[4], by[4];
         floatx4 qn;
 #pragma unroll
@@ -430,15 +565,16 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
           qn[v] = fminf(fmaxf(u, -a.qmax), a.qmax);
           dg[v] = i8_digits(qn[v], k);
         }
-        *reinterpret_cast<floatx4 *>(a.q[nx] + (size_t)(col0 + cc) * a.ld + m0 + row) = qn;
+        *reinterpret_cast<floatx4 *>(a.q[nx] + (size_t)(col0 + lc + cc) * a.ld + m0 + row) = qn;
         byte_transpose(dg, by);
 #pragma unroll
         for (int d = 0; d < QP; ++d) w[d][c] = by[d];
         if (c == 1) tick();
       }
       // lane t of a quad takes column t: 16 consecutive spins per digit
-      uint8_t *out = a.Qt[nx] + i8_qblk(spin / 32, n0 / 32, ncb) * BLK + (spin & 16) * 32 +
-                     (sw * C::COLS + set * 4 + (lane & 3)) * 16;
+      const int rep = col0 + lc + set * 4 + (lane & 3);
+      uint8_t *out = a.Qt[nx] + i8_qblk(spin / 32, rep / 32, ncb) * BLK + (spin & 16) * 32 +
+                     (rep & 31) * 16;
 #pragma unroll
       for (int d = 0; d < QP; ++d) {
         quad_transpose(w[d]);
@@ -453,29 +589,29 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk &walk, I8
   finish(m0, n0);
 }
 
-template <int WALL>
-__global__ __launch_bounds__(I8Cfg::NT) void step_i8_kernel(I8Args a) {
-  __shared__ I8Smem sm;
-  const I8Walk walk(a);
+template <class C, int WALL>
+__global__ __launch_bounds__(C::NT) void step_i8_kernel(I8Args a) {
+  __shared__ I8Smem<C> sm;
+  const I8Walk<C> walk(a);
   if (walk.count == 0) return;
-  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < I8Cfg::NM)
+  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < C::NM)
     i8_matrix(a, walk, sm);
   else
-    i8_state<WALL>(a, walk, sm);
+    i8_state<C, WALL>(a, walk, sm);
 }
 
 // Resident form: one cooperative launch runs n_steps steps with a grid-wide
 // barrier between them (see grid_barrier).  One tile per workgroup.
-template <int WALL>
-__global__ __launch_bounds__(I8Cfg::NT) void resident_i8_kernel(I8Args a, ResidentArgs r) {
-  __shared__ I8Smem sm;
-  const I8Walk walk(a);
+template <class C, int WALL>
+__global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentArgs r) {
+  __shared__ I8Smem<C> sm;
+  const I8Walk<C> walk(a);
   if (walk.count == 0) return;
   for (int s = 0; s < r.n_steps; ++s) {
-    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < I8Cfg::NM)
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < C::NM)
       i8_matrix(a, walk, sm);
     else
-      i8_state<WALL>(a, walk, sm);
+      i8_state<C, WALL>(a, walk, sm);
     a.cur ^= 1;
     a.t += 1;
     if (s + 1 < r.n_steps && !grid_barrier(r.count, (uint32_t)(s + 1), r.err)) return;
@@ -513,7 +649,7 @@ __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
       kx[wave] = k;
       a.kexp[a.cur][r0 + wave] = k;
     }
-    for (int rt = lane; rt < a.ld / I8_BM; rt += 64)
+    for (int rt = lane; rt < a.ld / a.bm; rt += 64)
       a.mx[a.cur][(size_t)rt * a.r_pad + r0 + wave] = rt == 0 ? mu : 0.f;
   }
   __syncthreads();
@@ -538,53 +674,142 @@ __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
   }
 }
 
-// Integer couplings into blocks: one wave per block, 16 couplings per lane.
+// Couplings into blocks of digits: one wave per block, 16 couplings per lane.
+template <int JD>
 __global__ __launch_bounds__(256) void i8_pack_j_kernel(const float *__restrict__ J, int ld,
-                                                        int64_t blocks, uint8_t *__restrict__ out) {
+                                                        int64_t blocks, const int *__restrict__ jexp,
+                                                        uint8_t *__restrict__ out) {
   const int lane = threadIdx.x & 63, nkb = ld / 32;
   for (int64_t b = blockIdx.x * 4 + (threadIdx.x >> 6); b < blocks; b += (int64_t)gridDim.x * 4) {
     const int rb = (int)(b / 2 % nkb), kb = (int)(b / 2 / nkb) * 2 + (int)(b & 1);
-    const float *src = J + (size_t)(rb * 32 + (lane & 31)) * ld + kb * 32 + (lane >> 5) * 16;
-    uint32_t w[4];
+    const int row = rb * 32 + (lane & 31);
+    const float *src = J + (size_t)row * ld + kb * 32 + (lane >> 5) * 16;
+    const int k = JD > 1 ? jexp[row] : 0;
+    uint32_t w[JD][4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const floatx4 x = *reinterpret_cast<const floatx4 *>(src + g * 4);
-      w[g] = ((uint32_t)(int)x[0] & 255u) | (((uint32_t)(int)x[1] & 255u) << 8) |
-             (((uint32_t)(int)x[2] & 255u) << 16) | ((uint32_t)(int)x[3] << 24);
+      if constexpr (JD == 1) {
+        w[0][g] = ((uint32_t)(int)x[0] & 255u) | (((uint32_t)(int)x[1] & 255u) << 8) |
+                  (((uint32_t)(int)x[2] & 255u) << 16) | ((uint32_t)(int)x[3] << 24);
+      } else {
+        uint32_t dg[4], by[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dg[v] = i8_digits(x[v], k);
+        byte_transpose(dg, by);
+#pragma unroll
+        for (int d = 0; d < JD; ++d) w[d][g] = by[d];
+      }
     }
-    *reinterpret_cast<uintx4 *>(out + b * BLK + lane * 16) = uintx4{w[0], w[1], w[2], w[3]};
+#pragma unroll
+    for (int d = 0; d < JD; ++d)
+      *reinterpret_cast<uintx4 *>(out + (b * JD + d) * BLK + lane * 16) =
+          uintx4{w[d][0], w[d][1], w[d][2], w[d][3]};
   }
 }
 
-static bool i8_fits(const I8Args &a) {
-  return a.ld % I8Cfg::BM == 0 && a.r_pad % I8Cfg::BN == 0 && a.n >= 1 && a.n <= a.ld &&
-         (a.xr == 1 || a.xr == 2 || a.xr == 4 || a.xr == 8);
+// Exponent of every row of real couplings, as for a replica's positions.
+// *heavy is set if a row is not a dense one of like couplings: its largest
+// exceeds I8_CREST times the root mean square of its n entries, or more than
+// a sixteenth of them lie below 1/1024 of the largest (a Gaussian row: 0.4 %;
+// the diagonal is one).  Such rows' sums may be finer in FP32 than 2^-31 of
+// their largest product.  One wave per row.
+__global__ __launch_bounds__(256) void i8_rows_kernel(const float *__restrict__ J, int ld, int n,
+                                                      int *__restrict__ jexp, int *heavy) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  float m = 0.f;
+  for (int i = lane * 4; i < ld; i += 256) {
+    const floatx4 x = *reinterpret_cast<const floatx4 *>(J + (size_t)row * ld + i);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(x[v]));
+  }
+  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  float s = 0.f;  // sum of squares in units of the largest
+  int small = 0;
+  for (int i = lane * 4; i < ld && m > 0.f; i += 256) {
+    const floatx4 x = *reinterpret_cast<const floatx4 *>(J + (size_t)row * ld + i);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      s = fmaf(x[v] / m, x[v] / m, s);
+      small += i + v < n && fabsf(x[v]) < m * (1.f / 1024.f);
+    }
+  }
+  for (int off = 32; off >= 1; off >>= 1) {
+    s += __shfl_xor(s, off);
+    small += __shfl_xor(small, off);
+  }
+  if (lane == 0) {
+    jexp[row] = i8_exponent(m);
+    if (row < n && (s * (I8_CREST * I8_CREST) < (float)n || small > n / 16 || m == 0.f)) *heavy = 1;
+  }
 }
+
+static bool i8_real(const I8Args &a) { return a.bm == I8_BM_REAL; }
+
+static bool i8_fits(const I8Args &a) {
+  return (a.bm == I8_BM || (i8_real(a) && a.jexp)) && a.ld % a.bm == 0 && a.r_pad % 64 == 0 &&
+         a.n >= 1 && a.n <= a.ld && (a.xr == 1 || a.xr == 2 || a.xr == 4 || a.xr == 8);
+}
+
+static int i8_bn(const I8Args &a) { return i8_real(a) ? I8Real::BN : I8Int::BN; }
 
 // One workgroup per CU (the register file holds one), fewer if an XCD's part
 // has fewer tiles than CUs.
 static int i8_grid(const I8Args &a, int num_cus) {
-  const int ntr = a.ld / I8Cfg::BM, ntc = a.r_pad / I8Cfg::BN, xc = NUM_XCD / a.xr;
+  const int ntr = a.ld / a.bm, ntc = a.r_pad / i8_bn(a), xc = NUM_XCD / a.xr;
   const int part = ((ntr + a.xr - 1) / a.xr) * ((ntc + xc - 1) / xc);
   const int per = std::max(num_cus / NUM_XCD, 1);
   return NUM_XCD * std::min(part, per);
 }
 
-hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s) {
-  if (!i8_fits(a)) return hipErrorInvalidValue;
-  const int grid = i8_grid(a, num_cus);
-  if (a.wall == SI_WALL_CLAMP)
-    step_i8_kernel<SI_WALL_CLAMP><<<grid, I8Cfg::NT, 0, s>>>(a);
-  else
-    step_i8_kernel<SI_WALL_INELASTIC><<<grid, I8Cfg::NT, 0, s>>>(a);
-  return hipGetLastError();
+// The split of the tiles over the XCDs' L2s that fetches least: every row
+// group reads all of its column group's digits and the other way round.
+int32_t i8_xcd_rows(const I8Args &a) {
+  const int64_t ntr = a.ld / a.bm, ntc = a.r_pad / i8_bn(a);
+  const int64_t nn = (int64_t)a.ld * a.ld * (i8_real(a) ? I8_JDIGITS : 1);
+  const int64_t nr = (int64_t)a.ld * a.r_pad * I8_DIGITS;
+  int32_t best = 1;
+  double least = 0.0;
+  for (int32_t xr = 1; xr <= NUM_XCD; xr *= 2) {
+    const int64_t xc = NUM_XCD / xr, pr = (ntr + xr - 1) / xr, pc = (ntc + xc - 1) / xc;
+    const double pad = (double)(pr * xr * pc * xc) / (double)(ntr * ntc);
+    const int64_t bands = (pr + 3) / 4;  // sweeps over its columns
+    const double cost = pad * ((double)nn * xc + (double)nr * xr * bands);
+    if (xr == 1 || cost < least) {
+      least = cost;
+      best = xr;
+    }
+  }
+  return best;
 }
 
-const char *i8_kernel_name() { return "step_i8x4_256x32_w4_k256_s3"; }
+static const void *i8_step(const I8Args &a) {
+  const bool clamp = a.wall == SI_WALL_CLAMP;
+  if (i8_real(a))
+    return clamp ? reinterpret_cast<const void *>(&step_i8_kernel<I8Real, SI_WALL_CLAMP>)
+                 : reinterpret_cast<const void *>(&step_i8_kernel<I8Real, SI_WALL_INELASTIC>);
+  return clamp ? reinterpret_cast<const void *>(&step_i8_kernel<I8Int, SI_WALL_CLAMP>)
+               : reinterpret_cast<const void *>(&step_i8_kernel<I8Int, SI_WALL_INELASTIC>);
+}
 
-static const void *i8_resident(int wall) {
-  return wall == SI_WALL_CLAMP ? reinterpret_cast<const void *>(&resident_i8_kernel<SI_WALL_CLAMP>)
-                               : reinterpret_cast<const void *>(&resident_i8_kernel<SI_WALL_INELASTIC>);
+static const void *i8_resident(const I8Args &a) {
+  const bool clamp = a.wall == SI_WALL_CLAMP;
+  if (i8_real(a))
+    return clamp ? reinterpret_cast<const void *>(&resident_i8_kernel<I8Real, SI_WALL_CLAMP>)
+                 : reinterpret_cast<const void *>(&resident_i8_kernel<I8Real, SI_WALL_INELASTIC>);
+  return clamp ? reinterpret_cast<const void *>(&resident_i8_kernel<I8Int, SI_WALL_CLAMP>)
+               : reinterpret_cast<const void *>(&resident_i8_kernel<I8Int, SI_WALL_INELASTIC>);
+}
+
+hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s) {
+  if (!i8_fits(a)) return hipErrorInvalidValue;
+  I8Args aa = a;
+  void *args[] = {&aa};
+  return hipLaunchKernel(i8_step(a), dim3(i8_grid(a, num_cus)), dim3(I8Int::NT), args, 0, s);
+}
+
+const char *i8_kernel_name(const I8Args &a) {
+  return i8_real(a) ? "step_i8x10_128x64_w4_k128_s3" : "step_i8x4_256x32_w4_k256_s3";
 }
 
 // Every workgroup of the grid must own exactly one tile: an even XCD split,
@@ -592,10 +817,10 @@ static const void *i8_resident(int wall) {
 hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups) {
   *groups = 0;
   if (!i8_fits(a)) return hipSuccess;
-  const int ntr = a.ld / I8Cfg::BM, ntc = a.r_pad / I8Cfg::BN;
+  const int ntr = a.ld / a.bm, ntc = a.r_pad / i8_bn(a);
   if (ntr % a.xr || ntc % (NUM_XCD / a.xr) || i8_grid(a, num_cus) != ntr * ntc) return hipSuccess;
   int per = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, i8_resident(a.wall), I8Cfg::NT, 0);
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, i8_resident(a), I8Int::NT, 0);
   if (e == hipSuccess && ntr * ntc <= per * num_cus) *groups = ntr * ntc;
   return e;
 }
@@ -606,19 +831,30 @@ hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t gr
   I8Args aa = a;
   ResidentArgs rr = r;
   void *args[] = {&aa, &rr};
-  return hipLaunchCooperativeKernel(i8_resident(a.wall), dim3(groups), dim3(I8Cfg::NT), args, 0, s);
+  return hipLaunchCooperativeKernel(i8_resident(a), dim3(groups), dim3(I8Int::NT), args, 0, s);
 }
 
 hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s) {
-  if (a.r_pad % 8 || a.ld % I8_BM) return hipErrorInvalidValue;
+  if (a.r_pad % 8 || a.ld % 128 || a.ld % a.bm) return hipErrorInvalidValue;
   i8_prepare_kernel<<<a.r_pad / 8, 512, 0, s>>>(a);
   return hipGetLastError();
 }
 
-hipError_t launch_i8_pack_j(const float *J, int32_t ld, uint8_t *out, hipStream_t s) {
+hipError_t launch_i8_rows(const float *J, int32_t ld, int32_t n, int32_t *jexp, int32_t *heavy,
+                          hipStream_t s) {
+  if (ld % 4) return hipErrorInvalidValue;
+  i8_rows_kernel<<<ld / 4, 256, 0, s>>>(J, ld, n, jexp, heavy);
+  return hipGetLastError();
+}
+
+hipError_t launch_i8_pack_j(const float *J, int32_t ld, const int32_t *jexp, uint8_t *out,
+                            hipStream_t s) {
   const int64_t blocks = (int64_t)(ld / 32) * (ld / 32);
-  const int64_t wg = (blocks + 3) / 4;
-  i8_pack_j_kernel<<<(int)(wg < 8192 ? wg : 8192), 256, 0, s>>>(J, ld, blocks, out);
+  const int wg = (int)std::min<int64_t>((blocks + 3) / 4, 8192);
+  if (jexp)
+    i8_pack_j_kernel<I8_JDIGITS><<<wg, 256, 0, s>>>(J, ld, blocks, jexp, out);
+  else
+    i8_pack_j_kernel<1><<<wg, 256, 0, s>>>(J, ld, blocks, jexp, out);
   return hipGetLastError();
 }
 

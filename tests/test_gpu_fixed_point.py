@@ -253,3 +253,125 @@ def test_exact_split_form(n, r, jmax):
                        total_steps=2, precision="bf16x3_exactj")
     assert not f.info()["kernel_name"].startswith(NAME)
     f.close()
+
+
+# Real couplings: four digits each, scaled per row (half a unit: 2^-31 of the
+# row's largest); of the sixteen digit products the six lowest are left out,
+# together below 3.2 x 2^16 x 2^14 units, a unit being at most 2^-60 of the
+# product of the row's and the replica's largest.
+REAL = "step_i8x10"
+
+
+def _real_bounds(J64, Q, P, F, dt, zeta):
+    u = 2.0 ** -24
+    jm, qm = np.abs(J64).max(axis=1)[:, None], np.abs(Q).max(axis=0)
+    f_err = (2.0 ** -31 * (qm * np.abs(J64).sum(axis=1)[:, None] + jm * np.abs(Q).sum(axis=0)) +
+             3.2 * 2.0 ** -30 * J64.shape[0] * jm * qm + 4 * u * np.abs(F))
+    p_err = dt * zeta * f_err + 4 * u * (np.abs(P) + dt * (zeta * np.abs(F) + 0.5 * np.abs(Q)))
+    return 3 * u * (np.abs(Q) + dt * np.abs(P)) + 1e-45, p_err + 1e-45
+
+
+def _real(n, seed, kind="gauss"):
+    rng = np.random.default_rng(seed)
+    a = rng.standard_normal((n, n)) if kind == "gauss" else rng.uniform(1, 3, (n, n)) * 0.01
+    a = np.triu(a, 1).astype(np.float32)
+    return a + a.T
+
+
+# n around the 128-deep slabs and 128-row tiles, r around the 64-replica tiles,
+# one and several tiles per workgroup, positions and couplings of any magnitude
+@pytest.mark.parametrize("n,r,kind,scale,wall", [
+    (513, 1280, "gauss", 1.0, "clamp"), (640, 1001, "gauss", 1e-3, "inelastic"),
+    (1000, 641, "uniform", 1.0, "clamp"), (1025, 640, "gauss", 1e20, "clamp"),
+    (2305, 300, "gauss", 1e-30, "clamp"), (2000, 1025, "gauss", 1.0, "inelastic"),
+    (10001, 40, "gauss", 1.0, "clamp")])
+def test_real_one_step_at_tile_edges(n, r, kind, scale, wall):
+    import torch
+    si = ensure_built()
+    announce(f"fixed-point step, real couplings N={n} R={r} {kind} scale {scale} {wall}")
+    J = _real(n, n, kind)
+    x, p = _signed(n, r, 1, scale), _signed(n, r, 2, min(scale, 1.0))
+    S, t = 50, 7
+    m = si.SpringIsing(to_dev(J), to_dev(x), to_dev(p), total_steps=S, wall=wall)
+    assert m.info()["kernel_name"].startswith(REAL)
+    m.set_state(to_dev(x), to_dev(p), t)
+    m.step()
+    xg, pg, _ = m.state()
+    torch.cuda.synchronize()
+    m.close()
+    cols = sorted({0, 1, 31, 32, 33, r // 2, r - 2, r - 1} & set(range(r)))
+    dts, zetas = oracle_schedules(S)
+    dt, zeta = float(dts[t]), float(zetas[t])
+    J64 = J.astype(np.float64)
+    Q0, P0 = x[cols].T.astype(np.float64), p[cols].T.astype(np.float64)
+    Q1, P1 = oracle.step(J64, Q0, P0, dt, zeta, qmax=QMAX, wall=wall)
+    qb, pb = _real_bounds(J64, Q0, P0, J64 @ Q0, dt, zeta)
+    dq = np.abs(xg.cpu().numpy()[cols].T - Q1)
+    dp = np.abs(pg.cpu().numpy()[cols].T - P1)
+    assert np.all(dq <= qb), (dq / qb).max()
+    assert np.all(dp <= pb), (dp / pb).max()
+
+
+def test_real_trajectory_resident_and_infinite():
+    # a run with a field against the oracle; the resident form bit for bit;
+    # infinite and NaN positions step as on the FP32 matrix cores
+    import torch
+    si = ensure_built()
+    n, r, S = 1000, 1000, 40
+    announce(f"fixed-point, real couplings: trajectory, resident, infinite N={n} R={r}")
+    J, x0 = _real(n, 3), instances.make_x0(n, r, 3)
+    h = instances.make_x0(1, n, 4)[:, 0].copy() * np.float32(5)
+    out = []
+    for resident in (0, 2):
+        m = si.SpringIsing(to_dev(J), to_dev(x0), total_steps=S)
+        m.set_field(to_dev(h))
+        m.set_resident(resident)
+        m.run(20)
+        assert m.info()["kernel_name"].startswith(REAL) and m.info()["resident_groups"] == 128
+        out.append(m.state())
+        torch.cuda.synchronize()
+        m.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    cols = [0, 31, 32, 63, 64, 999]
+    dt, zeta = oracle_schedules(S)
+    ref = oracle.run(J.astype(np.float64), x0[cols].T.astype(np.float64), None, dt, zeta,
+                     qmax=QMAX, h=h.astype(np.float64), n_steps=20)
+    assert rel_err(out[0][0].cpu().numpy()[cols], ref["Q"]) <= 1e-5
+    assert rel_err(out[0][1].cpu().numpy()[cols], ref["P"]) <= 1e-5
+    x = instances.random_state(n, r, 7, scale=1.4)
+    x[1, 5], x[2, 6], x[2, 7], x[40, 8] = np.inf, np.inf, -np.inf, np.nan
+    x[4, :] = 0.0
+    x[999, 999] = -np.inf
+    res = []
+    for tile in (0, 14):
+        m = si.SpringIsing(to_dev(J), to_dev(x), total_steps=4, tile=tile)
+        assert m.info()["kernel_name"].startswith(REAL) == (tile == 0)
+        m.run(1)
+        xs, ps, _ = m.state()
+        torch.cuda.synchronize()
+        res.append((xs.cpu().numpy(), ps.cpu().numpy()))
+        m.close()
+    rows = [1, 2, 4, 40, 999]
+    np.testing.assert_array_equal(res[0][0], res[1][0])
+    np.testing.assert_array_equal(res[0][1][rows], res[1][1][rows])
+
+
+def test_real_route():
+    # dense rows of like couplings only, in FP32, with enough work
+    si = ensure_built()
+    n, r = 640, 1000
+    J = _real(n, 8)
+    x = to_dev(instances.make_x0(n, r, 8))
+    heavy, thin, few = J.copy(), J.copy(), J.copy()
+    heavy[3, 4] = heavy[4, 3] = 900.0        # most of the row below 1/1024 of it
+    thin[3, :41] = thin[:41, 3] = 0.0        # more than a sixteenth of row 3
+    few[3, :20] = few[:20, 3] = 0.0
+    cases = [(J, r, {}, True), (heavy, r, {}, False), (thin, r, {}, False), (few, r, {}, True),
+             (instances.make_pm1(n, 8) * np.float32(127), r, {}, True),  # N |J| beyond the integer form
+             (J, 960, {}, False), (J, r, {"precision": "bf16x_hiloj"}, False),
+             (J, r, {"order": "symplectic"}, False), (J, r, {"tile": 14}, False)]
+    for k, (Jc, rc, kw, want) in enumerate(cases):
+        m = si.SpringIsing(to_dev(Jc), x[:rc].contiguous(), total_steps=2, **kw)
+        assert m.info()["kernel_name"].startswith(REAL) == want, (k, kw)
+        m.run(2)
+        m.close()
