@@ -151,6 +151,14 @@ hipError_t launch_step_batch_f32(const StepArgs &a, const BatchDesc *descs, cons
                                  int32_t n_items, int32_t cur, int32_t btile,
                                  unsigned long long *trace, hipStream_t s);
 
+// BF16 (round to nearest even) and back.
+__device__ __forceinline__ uint32_t bf16_bits(float x) {
+  uint32_t u = __float_as_uint(x);
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return u >> 16;
+}
+__device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
+
 // Step on the BF16 matrix cores (precision forms).
 constexpr int32_t TILE_BF16_LAST = 33;
 TileShape tile_shape_bf16(int32_t tile);
@@ -263,14 +271,30 @@ hipError_t launch_adj_reduce(const double *part, int32_t nwg, int32_t mode, doub
                              hipStream_t s);
 
 // Layout conversion and validation.
+// One instance's state in the device layout, and where its rows lie in the
+// caller's arrays.
+struct StateRows {
+  float *q[2], *p[2];   // [r_pad][n_pad] ping-pong
+  uint16_t *qb[2];      // BF16 plane(s) of q, or null
+  int64_t off;          // first entry in the caller's concatenated [r][n] arrays
+  int64_t soff, plane;  // first entry in the spin buffers; entries per BF16 plane
+  int32_t n, n_pad;
+};
+// A copy of one instance's state (many null), or of all count instances'
+// (descriptors on the device).
+struct StateCopy {
+  StateRows one;
+  const StateRows *many;
+  int32_t count, cur, r, r_pad, planes, max_n_pad;
+};
+// x and, if given, p (else zeros) into the device layout, zero-padded, with
+// `planes` BF16 planes of q.
+hipError_t launch_pack_rows(const StateCopy &c, const float *x, const float *p, hipStream_t s);
+hipError_t launch_unpack_rows(const StateCopy &c, float *x, float *p, hipStream_t s);
+// Signs of q, or the spins src8 (device layout), into the caller's rows.
+hipError_t launch_unpack_spins(const StateCopy &c, const int8_t *src8, int8_t *out, hipStream_t s);
 hipError_t launch_pack_matrix(const float *src, int32_t n, float *dst, int8_t *dst8,
                               int32_t n_pad, hipStream_t s);
-hipError_t launch_pack_state(const float *src, int32_t n, int32_t r, float *dst,
-                             int32_t n_pad, int32_t r_pad, hipStream_t s);
-hipError_t launch_unpack_state(const float *src, int32_t n, int32_t r, float *dst,
-                               int32_t n_pad, hipStream_t s);
-hipError_t launch_unpack_spins(const int8_t *src, int32_t n, int32_t r, int8_t *dst,
-                               int32_t n_pad, hipStream_t s);
 hipError_t launch_pack_field(const float *h, int32_t n, float *hf, int8_t *h8,
                              int32_t n_pad, int32_t *flags, hipStream_t s);
 

@@ -120,6 +120,8 @@ struct si_ctx {
   int64_t b_total_n = 0;
   int64_t b_stot = 0;                     // elements of one state buffer (all instances)
   std::vector<int64_t> b_soff;            // offset of instance i in the state buffers
+  std::vector<StateRows> b_rows_host;     // every instance's state, for copies
+  StateRows *b_rows = nullptr;
   // grouped energy: one descriptor per instance; work items of the integer
   // instances first (eb_n_i8 of them), then those of the real ones
   std::vector<EBatchDesc> eb_desc_host;
@@ -543,6 +545,32 @@ static hipError_t i8_init(si_ctx *c) {
   return e;
 }
 
+// The current state of a context, or of all instances of a batch, for copies.
+static StateCopy state_copy(const si_ctx *c) {
+  StateCopy s{};
+  s.count = 1;
+  s.cur = c->cur;
+  s.r = c->r;
+  s.r_pad = c->r_pad;
+  if (c->n_inst) {
+    s.many = c->b_rows;
+    s.count = c->n_inst;
+    s.planes = c->b_lowp ? 1 : 0;
+    s.max_n_pad = c->b_max_npad;
+    return s;
+  }
+  for (int b = 0; b < 2; ++b) {
+    s.one.q[b] = c->q[b];
+    s.one.p[b] = c->p[b];
+    s.one.qb[b] = c->qb[b];
+  }
+  s.one.plane = (int64_t)c->n_pad * c->r_pad;
+  s.one.n = c->n;
+  s.one.n_pad = s.max_n_pad = c->n_pad;
+  s.planes = c->qplanes;
+  return s;
+}
+
 // Digits, scales and maxima of the current FP32 state: after every call that
 // wrote the state or the schedule by other means than the int8 step.  A
 // context that has the int8 form but is off it gets its BF16 planes, which
@@ -877,9 +905,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
   }
   INIT_HIP(launch_pack_matrix(J, n, c->J, c->J8, c->n_pad, c->stream));
   if (lowp) INIT_HIP(launch_pack_j_lowp(c->J, nn, prm->precision, c->Ja, c->Jb, c->stream));
-  INIT_HIP(launch_pack_state(x0, n, r, c->q[0], c->n_pad, c->r_pad, c->stream));
-  INIT_HIP(launch_pack_state(p0, n, r, c->p[0], c->n_pad, c->r_pad, c->stream));
-  if (lowp) INIT_HIP(launch_split_planes(c->q[0], c->qb[0], nr, c->qplanes, c->stream));
+  INIT_HIP(launch_pack_rows(state_copy(c), x0, p0, c->stream));
   INIT_HIP(launch_zero_i32(c->eacc, c->r_pad, c->stream));
   INIT_HIP(ensure_split_ws(c));
   build_schedules(*prm, c->host_dt, c->host_zeta);
@@ -1015,6 +1041,7 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
   }
   c->b_desc_host.resize(n_inst);
   c->b_soff.resize(n_inst);
+  c->b_rows_host.resize(n_inst);
   if (lowp) {
     c->bb_desc_host.resize(n_inst);
     for (int b = 0; b < 2; ++b) c->b_qb[b].resize(n_inst);
@@ -1033,9 +1060,6 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
     c->b_p[1][i] = sbuf[3] + so;
     so += (int64_t)c->r_pad * c->b_npad[i];
     BINIT_HIP(launch_pack_matrix(J[i], n[i], c->b_J[i], c->b_J8[i], c->b_npad[i], c->stream));
-    BINIT_HIP(launch_pack_state(x0[i], n[i], r, c->b_q[0][i], c->b_npad[i], c->r_pad, c->stream));
-    BINIT_HIP(launch_pack_state(p0 ? p0[i] : nullptr, n[i], r, c->b_p[0][i], c->b_npad[i],
-                                c->r_pad, c->stream));
     c->b_desc_host[i] = BatchDesc{c->b_J[i], c->b_q[0][i], c->b_q[1][i], c->b_p[0][i], c->b_p[1][i],
                                   c->b_npad[i], n[i]};
     if (lowp) {
@@ -1049,7 +1073,6 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
       BINIT_HIP(launch_pack_j_lowp(c->b_J[i], nn,
                                    c->b_fmt[i] == 1 ? SI_PREC_BF16X_FP8J : SI_PREC_BF16X_HILOJ,
                                    ja, jb, c->stream));
-      BINIT_HIP(launch_split_planes(c->b_q[0][i], c->b_qb[0][i], nr, 1, c->stream));
       BBatchDesc d;
       d.Ja = ja;
       d.Jb = jb;
@@ -1063,6 +1086,25 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
       d.fmt = c->b_fmt[i];
       c->bb_desc_host[i] = d;
     }
+    StateRows rows{};
+    for (int b = 0; b < 2; ++b) {
+      rows.q[b] = c->b_q[b][i];
+      rows.p[b] = c->b_p[b][i];
+      rows.qb[b] = lowp ? c->b_qb[b][i] : nullptr;
+    }
+    rows.n = n[i];
+    rows.n_pad = c->b_npad[i];
+    StateCopy one{};
+    one.one = rows;
+    one.count = 1;
+    one.r = r;
+    one.r_pad = c->r_pad;
+    one.planes = lowp ? 1 : 0;
+    one.max_n_pad = c->b_npad[i];
+    BINIT_HIP(launch_pack_rows(one, x0[i], p0 ? p0[i] : nullptr, c->stream));
+    rows.off = c->b_xoff[i];
+    rows.soff = c->b_soff[i];
+    c->b_rows_host[i] = rows;
   }
   // batch tile: the caller's, else the tile cache's, else 128-row items
   int32_t cached = 0;
@@ -1108,6 +1150,9 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
   BINIT_HIP(hipMemcpyAsync(c->eb_items, c->eb_items_host.data(),
                            sizeof(int4) * c->eb_items_host.size(), hipMemcpyHostToDevice,
                            c->stream));
+  BINIT_HIP(c->alloc(&c->b_rows, n_inst));
+  BINIT_HIP(hipMemcpyAsync(c->b_rows, c->b_rows_host.data(), sizeof(StateRows) * n_inst,
+                           hipMemcpyHostToDevice, c->stream));
   BINIT_HIP(c->alloc(&c->b_desc, n_inst));
   BINIT_HIP(hipMemcpyAsync(c->b_desc, c->b_desc_host.data(), sizeof(BatchDesc) * n_inst,
                            hipMemcpyHostToDevice, c->stream));
@@ -1844,15 +1889,6 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
 
 
 // ---- batched-context variants (instances concatenated in caller layouts) ----
-static si_status batch_spins(si_ctx *c, int8_t *s) {
-  SI_HIP(c, launch_sign(c->b_q[c->cur][0], c->S8, (int32_t)(c->b_stot / c->r_pad), c->r_pad,
-                        c->stream));
-  for (int32_t i = 0; i < c->n_inst; ++i)
-    SI_HIP(c, launch_unpack_spins(c->S8 + c->b_soff[i], c->b_n[i], c->r, s + c->b_xoff[i],
-                                  c->b_npad[i], c->stream));
-  return SI_OK;
-}
-
 // Every instance in at most two grouped launches (plus their finalisations):
 // the int8 matrix-core energy for the integer instances, the FP32 coupling
 // sum for the others.
@@ -1872,44 +1908,22 @@ static si_status batch_energy(si_ctx *c, int32_t *e_int, double *e_real) {
   return SI_OK;
 }
 
-static si_status batch_get_state(si_ctx *c, float *x, float *p) {
-  for (int32_t i = 0; i < c->n_inst; ++i) {
-    if (x)
-      SI_HIP(c, launch_unpack_state(c->b_q[c->cur][i], c->b_n[i], c->r, x + c->b_xoff[i],
-                                    c->b_npad[i], c->stream));
-    if (p)
-      SI_HIP(c, launch_unpack_state(c->b_p[c->cur][i], c->b_n[i], c->r, p + c->b_xoff[i],
-                                    c->b_npad[i], c->stream));
-  }
-  return SI_OK;
-}
-
-static si_status batch_set_state(si_ctx *c, const float *x, const float *p) {
-  for (int32_t i = 0; i < c->n_inst; ++i) {
-    SI_HIP(c, launch_pack_state(x + c->b_xoff[i], c->b_n[i], c->r, c->b_q[c->cur][i], c->b_npad[i],
-                                c->r_pad, c->stream));
-    SI_HIP(c, launch_pack_state(p ? p + c->b_xoff[i] : nullptr, c->b_n[i], c->r,
-                                c->b_p[c->cur][i], c->b_npad[i], c->r_pad, c->stream));
-    if (c->b_lowp)
-      SI_HIP(c, launch_split_planes(c->b_q[c->cur][i], c->b_qb[c->cur][i],
-                                    (int64_t)c->r_pad * c->b_npad[i], 1, c->stream));
-  }
-  return SI_OK;
-}
-
 si_status spring_ising_spins(si_ctx *c, int8_t *s) {
   SI_USABLE(c);
   if (!is_device_ptr(s)) return fail(SI_ERR_INVALID, "spins: s must be a device pointer");
-  if (c->n_inst) return batch_spins(c, s);
-  SI_HIP(c, launch_sign(c->q[c->cur], c->S8, c->n_pad, c->r_pad, c->stream));
-  SI_HIP(c, launch_unpack_spins(c->S8, c->n, c->r, s, c->n_pad, c->stream));
+  SI_HIP(c, launch_unpack_spins(state_copy(c), nullptr, s, c->stream));
   return SI_OK;
 }
 
 // Energies of the current spins into device outputs (no argument checks).
-static si_status energy_into(si_ctx *c, int32_t *e_int, double *e_real) {
+// *signs: whether it left the current spins in S8.
+static si_status energy_into(si_ctx *c, int32_t *e_int, double *e_real, bool *signs = nullptr) {
+  if (signs) *signs = false;
   if (!e_int && !e_real) return SI_OK;
-  if (c->n_inst) return batch_energy(c, e_int, e_real);
+  if (c->n_inst) {
+    if (signs) *signs = c->eb_n_i8 > 0;
+    return batch_energy(c, e_int, e_real);
+  }
   // exact int32 path: integer J (and field) with a sum that cannot overflow
   const int64_t jmax = c->hflags[6];
   const int64_t bound = (int64_t)c->n * c->n * jmax +
@@ -1920,6 +1934,7 @@ static si_status energy_into(si_ctx *c, int32_t *e_int, double *e_real) {
                 "energy: exact int32 energy needs integer |J_ij| <= 127 (and integer field)");
   const int8_t *h8 = c->has_field ? c->h8 : nullptr;
   if (exact) {
+    if (signs) *signs = true;
     SI_HIP(c, launch_sign(c->q[c->cur], c->S8, c->n_pad, c->r_pad, c->stream));
     SI_HIP(c, launch_energy_i8(c->J8, c->S8, h8, c->eacc, c->n_pad, c->r_pad,
                                energy_i8_ksplit(c->n_pad, c->r_pad, c->num_cus), c->stream));
@@ -1942,19 +1957,18 @@ si_status spring_ising_energy(si_ctx *c, int32_t *e_int, double *e_real) {
 }
 
 // Best-state update from the energies e of the current spins (out_rows()
-// doubles on the device).
-static si_status best_update_from(si_ctx *c, const double *e) {
+// doubles on the device); signs: S8 holds the current spins.
+static si_status best_update_from(si_ctx *c, const double *e, bool signs) {
   SI_HIP(c, ensure_best_buffers(c));
-  if (c->n_inst) {
-    SI_HIP(c, launch_sign(c->b_q[c->cur][0], c->S8, (int32_t)(c->b_stot / c->r_pad), c->r_pad,
-                          c->stream));
+  const float *q = c->n_inst ? c->b_q[c->cur][0] : c->q[c->cur];
+  const int32_t n_pad = c->n_inst ? (int32_t)(c->b_stot / c->r_pad) : c->n_pad;
+  if (!signs) SI_HIP(c, launch_sign(q, c->S8, n_pad, c->r_pad, c->stream));
+  if (c->n_inst)
     SI_HIP(c, launch_best_update_batch(e, c->best_e, c->best_valid, c->S8, c->best_s, c->eb_desc,
                                        c->n_inst, c->r, c->stream));
-  } else {
-    SI_HIP(c, launch_sign(c->q[c->cur], c->S8, c->n_pad, c->r_pad, c->stream));
+  else
     SI_HIP(c, launch_best_update(e, c->best_e, c->best_valid, c->S8, c->best_s, c->r, c->n_pad,
                                  c->stream));
-  }
   c->best_any = true;
   return SI_OK;
 }
@@ -1963,17 +1977,19 @@ static si_status record_check(si_ctx *c) {
   const int32_t row = c->t / c->e_every - 1;
   if (row < 0 || row >= c->e_rows) return SI_OK;
   double *e = c->etrace + (int64_t)row * c->out_rows();
-  si_status st = energy_into(c, nullptr, e);
+  bool signs = false;
+  si_status st = energy_into(c, nullptr, e, &signs);
   if (st != SI_OK) return st;
-  return best_update_from(c, e);
+  return best_update_from(c, e, signs);
 }
 
 si_status spring_ising_update_best(si_ctx *c) {
   SI_USABLE(c);
   SI_HIP(c, ensure_best_buffers(c));
-  si_status st = energy_into(c, nullptr, c->e_scratch);
+  bool signs = false;
+  si_status st = energy_into(c, nullptr, c->e_scratch, &signs);
   if (st != SI_OK) return st;
-  return best_update_from(c, c->e_scratch);
+  return best_update_from(c, c->e_scratch, signs);
 }
 
 si_status spring_ising_get_best(si_ctx *c, double *best_e, int8_t *best_s) {
@@ -1985,15 +2001,7 @@ si_status spring_ising_get_best(si_ctx *c, double *best_e, int8_t *best_s) {
   if (best_e)
     SI_HIP(c, hipMemcpyAsync(best_e, c->best_e, sizeof(double) * c->out_rows(),
                              hipMemcpyDeviceToDevice, c->stream));
-  if (best_s) {
-    if (c->n_inst) {
-      for (int32_t i = 0; i < c->n_inst; ++i)
-        SI_HIP(c, launch_unpack_spins(c->best_s + c->b_soff[i], c->b_n[i], c->r,
-                                      best_s + c->b_xoff[i], c->b_npad[i], c->stream));
-    } else {
-      SI_HIP(c, launch_unpack_spins(c->best_s, c->n, c->r, best_s, c->n_pad, c->stream));
-    }
-  }
+  if (best_s) SI_HIP(c, launch_unpack_spins(state_copy(c), c->best_s, best_s, c->stream));
   return SI_OK;
 }
 
@@ -2029,12 +2037,7 @@ si_status spring_ising_get_state(si_ctx *c, float *x, float *p, int32_t *t) {
   SI_USABLE(c);
   if ((x && !is_device_ptr(x)) || (p && !is_device_ptr(p)))
     return fail(SI_ERR_INVALID, "get_state: x and p must be device pointers");
-  if (c->n_inst) {
-    if (t) *t = c->t;
-    return batch_get_state(c, x, p);
-  }
-  if (x) SI_HIP(c, launch_unpack_state(c->q[c->cur], c->n, c->r, x, c->n_pad, c->stream));
-  if (p) SI_HIP(c, launch_unpack_state(c->p[c->cur], c->n, c->r, p, c->n_pad, c->stream));
+  SI_HIP(c, launch_unpack_rows(state_copy(c), x, p, c->stream));
   if (t) *t = c->t;
   return SI_OK;
 }
@@ -2050,16 +2053,9 @@ si_status spring_ising_set_state(si_ctx *c, const float *x, const float *p, int3
   if (c->best_valid)
     SI_HIP(c, launch_zero_i32(c->best_valid, c->n_inst ? c->out_rows() : c->r_pad, c->stream));
   c->best_any = false;
-  if (c->n_inst) {
-    si_status st = batch_set_state(c, x, p);
-    if (st == SI_OK) c->t = t;
-    return st;
-  }
-  SI_HIP(c, launch_pack_state(x, c->n, c->r, c->q[c->cur], c->n_pad, c->r_pad, c->stream));
-  SI_HIP(c, launch_pack_state(p, c->n, c->r, c->p[c->cur], c->n_pad, c->r_pad, c->stream));
-  if (c->qplanes && !c->i8.Jt)  // (i8_refresh otherwise)
-    SI_HIP(c, launch_split_planes(c->q[c->cur], c->qb[c->cur], (int64_t)c->n_pad * c->r_pad,
-                                  c->qplanes, c->stream));
+  StateCopy copy = state_copy(c);
+  if (i8_on(c)) copy.planes = 0;  // (written when a call takes the context off the int8 form)
+  SI_HIP(c, launch_pack_rows(copy, x, p, c->stream));
   c->t = t;
   SI_HIP(c, i8_refresh(c));
   return SI_OK;
