@@ -255,7 +255,11 @@ hipError_t launch_adj_step(const float *J, const float *lamq_in, const float *la
                            int32_t r_pad, hipStream_t s);
 // Backward step with the split contraction; writes adj_split_groups()
 // partial triples to part.
-int32_t adj_split_groups(int32_t n_pad, int32_t r_pad);
+int32_t adj_split_groups(int32_t n_pad, int32_t r_pad, int32_t ksplit);
+// Floats of workspace that the split forms need (0: they keep the partial
+// products in LDS).
+int64_t split_workspace(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit);
+int64_t adj_split_workspace(int32_t n_pad, int32_t r_pad, int32_t ksplit);
 hipError_t launch_adj_step_split(const float *J, const float *lamq_in, const float *lamp_in,
                                  const uint8_t *mask, const float *q_n, const float *p_n,
                                  float *lamq_out, float *lamp_out, double *part, const float *dt,

@@ -307,9 +307,8 @@ static int32_t adj_split(const si_ctx *c) {
 // Workspace for the split contraction of the current tile and of the
 // adjoint (allocated here, never while a launch sequence is captured).
 static hipError_t ensure_split_ws(si_ctx *c, bool adjoint = false) {
-  const int64_t NR = (int64_t)c->n_pad * c->r_pad;
-  int64_t need = split_for(c, c->tile) > 1 ? split_for(c, c->tile) * NR : 0;
-  if (adjoint && adj_split(c) > 1 && adj_split(c) * NR > need) need = adj_split(c) * NR;
+  int64_t need = split_workspace(c->tile, c->n_pad, c->r_pad, split_for(c, c->tile));
+  if (adjoint) need = std::max(need, adj_split_workspace(c->n_pad, c->r_pad, adj_split(c)));
   if (need <= c->fsplit_cap) return hipSuccess;
   hipError_t e = c->alloc(&c->fsplit, need);
   if (e == hipSuccess) c->fsplit_cap = need;
@@ -1372,7 +1371,7 @@ static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
   a.wall = c->prm.wall;
   a.ksplit = split_for(c, c->tile);
   a.fsplit = c->fsplit;
-  if (a.ksplit > 1 && (int64_t)a.ksplit * c->n_pad * c->r_pad > c->fsplit_cap)
+  if (split_workspace(c->tile, c->n_pad, c->r_pad, a.ksplit) > c->fsplit_cap)
     return fail(SI_ERR_STATE, "step: split-contraction workspace missing");
   for (int32_t s = 0; s < n_steps; ++s) {
     a.q_in = c->q[c->cur];
@@ -1414,7 +1413,7 @@ static si_status adj_forward(si_ctx *c, int32_t C, double *loss) {
   const int64_t NR = (int64_t)c->n_pad * c->r_pad;
   const int32_t asplit = adj_split(c);
   const int32_t nwg_seed = (c->n_pad / ADJ_BM) * (c->r_pad / ADJ_BN);
-  const int32_t nwg = asplit > 1 ? adj_split_groups(c->n_pad, c->r_pad) : nwg_seed;
+  const int32_t nwg = asplit > 1 ? adj_split_groups(c->n_pad, c->r_pad, asplit) : nwg_seed;
   SI_HIP(c, ensure_split_ws(c, true));
   if ((int64_t)nseg * 2 * NR > c->adj_ckpt_cap) {
     SI_HIP(c, c->alloc(&c->adj_ckpt, (int64_t)(nseg > 0 ? nseg : 1) * 2 * NR));
@@ -1469,7 +1468,7 @@ static si_status adj_backward(si_ctx *c, double *g_dt, double *g_zeta) {
   const int32_t nseg = (S - t0 + C - 1) / C;
   const int64_t NR = (int64_t)c->n_pad * c->r_pad;
   const int32_t asplit = adj_split(c);
-  const int32_t nwg = asplit > 1 ? adj_split_groups(c->n_pad, c->r_pad)
+  const int32_t nwg = asplit > 1 ? adj_split_groups(c->n_pad, c->r_pad, asplit)
                                  : (c->n_pad / ADJ_BM) * (c->r_pad / ADJ_BN);
   const float inv_m = 1.0f / c->prm.m, k = c->prm.k;
   SI_HIP(c, launch_fill_f64(g_dt, S, 0.0, c->stream));
