@@ -260,12 +260,14 @@ int32_t adj_split_groups(int32_t n_pad, int32_t r_pad, int32_t ksplit);
 // products in LDS).
 int64_t split_workspace(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit);
 int64_t adj_split_workspace(int32_t n_pad, int32_t r_pad, int32_t ksplit);
+// masked: the multipliers were masked with `mask` by the launch that wrote
+// them; mask_next (or null): mask of the next backward step, for the outputs.
 hipError_t launch_adj_step_split(const float *J, const float *lamq_in, const float *lamp_in,
-                                 const uint8_t *mask, const float *q_n, const float *p_n,
-                                 float *lamq_out, float *lamp_out, double *part, const float *dt,
-                                 const float *zeta, int32_t n, float k, float inv_m, int32_t n_pad,
-                                 int32_t n_spins, int32_t r_pad, int32_t ksplit, float *W,
-                                 hipStream_t s);
+                                 const uint8_t *mask, bool masked, const uint8_t *mask_next,
+                                 const float *q_n, const float *p_n, float *lamq_out,
+                                 float *lamp_out, double *part, const float *dt, const float *zeta,
+                                 int32_t n, float k, float inv_m, int32_t n_pad, int32_t n_spins,
+                                 int32_t r_pad, int32_t ksplit, float *W, hipStream_t s);
 // mode 0 (n_steps = 1): loss[0] = -1/2 * sum(part[:,0]) / r_count;  mode 1:
 // gradient entries g_dt[n + i], g_zeta[n + i] for i < n_steps from the nwg
 // partial triples of step n + i at part + i * nwg * 3.

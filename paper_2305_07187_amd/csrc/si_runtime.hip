@@ -1498,7 +1498,10 @@ static si_status adj_backward(si_ctx *c, double *g_dt, double *g_zeta) {
       const int32_t n = t_a + j;
       double *part = c->adj_part + (int64_t)(n - t0) * nwg * 3;
       if (asplit > 1)
+        // (the wall bits of an earlier segment are not recomputed yet)
         SI_HIP(c, launch_adj_step_split(c->J, lam[lc][0], lam[lc][1], c->adj_mask + (int64_t)j * NR,
+                                        j < len - 1,
+                                        j > 0 ? c->adj_mask + (int64_t)(j - 1) * NR : nullptr,
                                         sq + 2 * j * NR, sq + 2 * j * NR + NR, lam[lc ^ 1][0],
                                         lam[lc ^ 1][1], part, c->dt, c->zeta, n, k, inv_m,
                                         c->n_pad, c->n, c->r_pad, asplit, c->fsplit, c->stream));

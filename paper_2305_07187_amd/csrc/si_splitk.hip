@@ -128,8 +128,8 @@ __global__ __launch_bounds__(256) void update_split_kernel(StepArgs a, const flo
 
 struct AdjArgs {
   const float *J, *lamq_in, *lamp_in;
-  const uint8_t *mask;
-  const float *qn, *pn;  // the state before the step
+  const uint8_t *mask, *mask_next;  // wall bits of the step; null or of the step after
+  const float *qn, *pn;             // the state before the step
   float *lamq_out, *lamp_out;
   double *part;          // three partial sums per workgroup
   const float *dt, *zeta;
@@ -138,7 +138,10 @@ struct AdjArgs {
 };
 
 // Adjoint multiplier update of four elements with G = J vb; adds their
-// <ub, p_n>, <vb, q_n>, <G, q_n> to s.
+// <ub, p_n>, <vb, q_n>, <G, q_n> to s.  The next backward step only ever uses
+// the multipliers behind its own walls, so where its wall bits are known
+// already (mask_next) they are applied here, and its product then reads
+// plain operands.
 __device__ __forceinline__ void adj_update4(const AdjArgs &a, floatx4 G, int64_t off,
                                             double (&s)[3]) {
   const float dt = a.dt[a.n], zeta = a.zeta[a.n];
@@ -159,6 +162,14 @@ __device__ __forceinline__ void adj_update4(const AdjArgs &a, floatx4 G, int64_t
     s[0] += (double)ub * (double)p4[v];
     s[1] += (double)vb * (double)q4[v];
     s[2] += (double)G[v] * (double)q4[v];
+  }
+  if (a.mask_next) {
+    const uint32_t next = *reinterpret_cast<const uint32_t *>(a.mask_next + off);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      oq[v] = (next >> (8 * v) & 1u) ? oq[v] : 0.f;
+      op[v] = (next >> (8 * v) & 2u) ? op[v] : 0.f;
+    }
   }
   *reinterpret_cast<floatx4 *>(a.lamq_out + off) = oq;
   *reinterpret_cast<floatx4 *>(a.lamp_out + off) = op;
@@ -527,30 +538,39 @@ int64_t adj_split_workspace(int32_t n_pad, int32_t r_pad, int32_t ksplit) {
 }
 
 hipError_t launch_adj_step_split(const float *J, const float *lamq_in, const float *lamp_in,
-                                 const uint8_t *mask, const float *q_n, const float *p_n,
-                                 float *lamq_out, float *lamp_out, double *part, const float *dt,
-                                 const float *zeta, int32_t n, float k, float inv_m, int32_t n_pad,
-                                 int32_t n_spins, int32_t r_pad, int32_t ksplit, float *W,
-                                 hipStream_t s) {
+                                 const uint8_t *mask, bool masked, const uint8_t *mask_next,
+                                 const float *q_n, const float *p_n, float *lamq_out,
+                                 float *lamp_out, double *part, const float *dt, const float *zeta,
+                                 int32_t n, float k, float inv_m, int32_t n_pad, int32_t n_spins,
+                                 int32_t r_pad, int32_t ksplit, float *W, hipStream_t s) {
   using C = ASplitCfg;
   static_assert(C::MB == ADJ_FEW_MB, "same products");
   if (n_pad % C::BM || r_pad % C::BN || ksplit < 2) return hipErrorInvalidValue;
   int K, klen;
   split_ranges(n_spins, n_pad, ksplit, C::BK, &K, &klen);
-  const AdjArgs a{J,    lamq_in, lamp_in, mask, q_n, p_n,   lamq_out, lamp_out,
-                  part, dt,      zeta,    n,    n_pad, r_pad, k,        inv_m};
+  const AdjArgs a{J,    lamq_in, lamp_in, mask, mask_next, q_n,   p_n, lamq_out, lamp_out,
+                  part, dt,      zeta,    n,    n_pad,     r_pad, k,   inv_m};
   const int groups = adj_split_groups(n_pad, r_pad, ksplit);
   if (few_fits(n_pad, r_pad, ADJ_FEW_MB, ksplit)) {
-    if (ksplit <= 4)
-      adj_few_kernel<FewCfg<ADJ_FEW_MB, 4, true>><<<groups, 64 * ksplit, 0, s>>>(a, K, klen);
+    const int nt = 64 * ksplit;
+    if (ksplit <= 4 && masked)
+      adj_few_kernel<FewCfg<ADJ_FEW_MB, 4>><<<groups, nt, 0, s>>>(a, K, klen);
+    else if (ksplit <= 4)
+      adj_few_kernel<FewCfg<ADJ_FEW_MB, 4, true>><<<groups, nt, 0, s>>>(a, K, klen);
+    else if (masked)
+      adj_few_kernel<FewCfg<ADJ_FEW_MB, 8>><<<groups, nt, 0, s>>>(a, K, klen);
     else
-      adj_few_kernel<FewCfg<ADJ_FEW_MB, 8, true>><<<groups, 64 * ksplit, 0, s>>>(a, K, klen);
+      adj_few_kernel<FewCfg<ADJ_FEW_MB, 8, true>><<<groups, nt, 0, s>>>(a, K, klen);
     return hipGetLastError();
   }
   if (!W) return hipErrorInvalidValue;
   const int tiles = (n_pad / C::BM) * (r_pad / C::BN);
-  coupling_partial_kernel<C, B_MASKED><<<tiles * ksplit, C::NT, 0, s>>>(J, lamp_in, mask, n_pad,
-                                                                         r_pad, K, klen, W);
+  if (masked)
+    coupling_partial_kernel<C, B_PLAIN><<<tiles * ksplit, C::NT, 0, s>>>(J, lamp_in, nullptr, n_pad,
+                                                                          r_pad, K, klen, W);
+  else
+    coupling_partial_kernel<C, B_MASKED><<<tiles * ksplit, C::NT, 0, s>>>(J, lamp_in, mask, n_pad,
+                                                                           r_pad, K, klen, W);
   adj_update_split_kernel<<<groups, 256, 0, s>>>(a, W, ksplit);
   return hipGetLastError();
 }
