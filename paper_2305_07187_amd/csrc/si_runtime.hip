@@ -192,8 +192,40 @@ struct si_ctx {
   int64_t adj_part_cap = 0;       // doubles
   int64_t adj_ckpt_cap = 0, adj_seg_cap = 0;
 
+  static constexpr int64_t ARENA_ALIGN = 4096;
+  uint8_t *arena = nullptr;
+  int64_t arena_left = 0;
+
+  // One device allocation that the next alloc() calls take their buffers
+  // from: a hipMalloc and its hipFree take 10 .. 40 us each, whatever the size
+  // (a gradient at N = 2000, R = 64 creates a context and the adjoint's
+  // buffers: 18 of them).  Without the memory in one piece they allocate one by one.
+  void reserve(int64_t total) {
+    void *raw = nullptr;
+    arena = nullptr;
+    arena_left = 0;
+    if (total <= 0 || hipMalloc(&raw, (size_t)total) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    allocs.push_back(raw);
+    arena = static_cast<uint8_t *>(raw);
+    arena_left = total;
+  }
+  // Bytes that a buffer of `count` entries takes of a reservation.
+  template <class T>
+  static int64_t room(int64_t count) {
+    return (count * (int64_t)sizeof(T) + ARENA_ALIGN - 1) / ARENA_ALIGN * ARENA_ALIGN;
+  }
   template <class T>
   hipError_t alloc(T **ptr, int64_t count) {
+    if (room<T>(count) <= arena_left) {
+      *ptr = reinterpret_cast<T *>(arena);
+      arena += room<T>(count);
+      arena_left -= room<T>(count);
+      bytes += count * (int64_t)sizeof(T);
+      return hipSuccess;
+    }
     void *raw = nullptr;
     hipError_t e = hipMalloc(&raw, (size_t)count * sizeof(T));
     if (e != hipSuccess) return e;
@@ -882,6 +914,11 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
 
   const int64_t nn = (int64_t)c->n_pad * c->n_pad;
   const int64_t nr = (int64_t)c->n_pad * c->r_pad;
+  const int64_t epart = (int64_t)(c->n_pad / 64) * c->r_pad;
+  if (!lowp)
+    c->reserve(c->room<float>(nn) + (j_integer ? c->room<int8_t>(nn) : 0) + 4 * c->room<float>(nr) +
+               2 * c->room<float>(prm->total_steps) + c->room<int8_t>(nr) +
+               c->room<int32_t>(c->r_pad) + c->room<float>(epart));
   INIT_HIP(c->alloc(&c->J, nn));
   if (j_integer) INIT_HIP(c->alloc(&c->J8, nn));
   for (int b = 0; b < 2; ++b) {
@@ -892,7 +929,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
   INIT_HIP(c->alloc(&c->zeta, prm->total_steps));
   INIT_HIP(c->alloc(&c->S8, nr));
   INIT_HIP(c->alloc(&c->eacc, c->r_pad));
-  INIT_HIP(c->alloc(&c->epart, (int64_t)(c->n_pad / 64) * c->r_pad));
+  INIT_HIP(c->alloc(&c->epart, epart));
 
   if (lowp) {
     c->qplanes = prm->precision == SI_PREC_BF16X3_EXACTJ ? 3 : 1;
@@ -1415,20 +1452,28 @@ static si_status adj_forward(si_ctx *c, int32_t C, double *loss) {
   const int32_t nwg_seed = (c->n_pad / ADJ_BM) * (c->r_pad / ADJ_BN);
   const int32_t nwg = asplit > 1 ? adj_split_groups(c->n_pad, c->r_pad, asplit) : nwg_seed;
   SI_HIP(c, ensure_split_ws(c, true));
-  if ((int64_t)nseg * 2 * NR > c->adj_ckpt_cap) {
-    SI_HIP(c, c->alloc(&c->adj_ckpt, (int64_t)(nseg > 0 ? nseg : 1) * 2 * NR));
-    c->adj_ckpt_cap = (int64_t)(nseg > 0 ? nseg : 1) * 2 * NR;
+  // (partial triples of every step of the sweep, reduced in one launch at the
+  // end; the seed's triples use the start of the same buffer first)
+  const int64_t ckpt_need = (int64_t)(nseg > 0 ? nseg : 1) * 2 * NR;
+  const int64_t seg_need = (int64_t)(C + 1) * 2 * NR, mask_need = (int64_t)C * NR;
+  const int64_t part_need =
+      (int64_t)(S - t0 > 1 ? S - t0 : 1) * (nwg > nwg_seed ? nwg : nwg_seed) * 3;
+  const bool ckpt = (int64_t)nseg * 2 * NR > c->adj_ckpt_cap, seg = seg_need > c->adj_seg_cap;
+  const bool lam = !c->adj_lam, part = part_need > c->adj_part_cap;
+  c->reserve((ckpt ? c->room<float>(ckpt_need) : 0) +
+             (seg ? c->room<float>(seg_need) + c->room<uint8_t>(mask_need) : 0) +
+             (lam ? c->room<float>(4 * NR) : 0) + (part ? c->room<double>(part_need) : 0));
+  if (ckpt) {
+    SI_HIP(c, c->alloc(&c->adj_ckpt, ckpt_need));
+    c->adj_ckpt_cap = ckpt_need;
   }
-  if ((int64_t)(C + 1) * 2 * NR > c->adj_seg_cap) {
-    SI_HIP(c, c->alloc(&c->adj_seg, (int64_t)(C + 1) * 2 * NR));
-    SI_HIP(c, c->alloc(&c->adj_mask, (int64_t)C * NR));
-    c->adj_seg_cap = (int64_t)(C + 1) * 2 * NR;
+  if (seg) {
+    SI_HIP(c, c->alloc(&c->adj_seg, seg_need));
+    SI_HIP(c, c->alloc(&c->adj_mask, mask_need));
+    c->adj_seg_cap = seg_need;
   }
-  if (!c->adj_lam) SI_HIP(c, c->alloc(&c->adj_lam, 4 * NR));
-  // partial triples of every step of the sweep, reduced in one launch at the
-  // end (the seed's triples use the start of the same buffer first)
-  const int64_t part_need = (int64_t)(S - t0 > 1 ? S - t0 : 1) * (nwg > nwg_seed ? nwg : nwg_seed) * 3;
-  if (part_need > c->adj_part_cap) {
+  if (lam) SI_HIP(c, c->alloc(&c->adj_lam, 4 * NR));
+  if (part) {
     SI_HIP(c, c->alloc(&c->adj_part, part_need));
     c->adj_part_cap = part_need;
   }
