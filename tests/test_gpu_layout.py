@@ -115,3 +115,24 @@ def test_checks_of_couplings_find_every_entry(n):
     M[n - 1, n - 1] = 1.0
     with pytest.raises(si.SpringIsingError):
         init(M)
+
+
+@pytest.mark.parametrize("n,r,shift", [(2, 1, 0), (63, 127, 1), (128, 128, 0), (130, 129, 3),
+                                       (257, 20, 2), (1001, 300, 1), (1536, 640, 0)])
+def test_energy_noalloc_tile_edges(n, r, shift):
+    # tiles of 128, slabs of 64, one and several parts of the contraction, rows
+    # that start on any float; integers, so equal
+    import torch
+    si = ensure_built()
+    announce(f"energy_noalloc N={n} R={r} shift {shift}")
+    rng = np.random.default_rng(n)
+    A = np.triu(rng.integers(-127, 128, (n, n)), 1)
+    A = A + A.T
+    x = rng.uniform(-1, 1, (r, n)).astype(np.float32)
+    x[0, 0], x[-1, -1] = -0.0, 0.0
+    e = torch.zeros(r, dtype=torch.int32, device="cuda:0")
+    si.spring_ising_energy_noalloc(_shifted(A.astype(np.float32), shift), _shifted(x, shift), e)
+    torch.cuda.synchronize()
+    s = np.where(x < 0, -1.0, 1.0)
+    ref = -0.5 * np.einsum("ri,ri->r", s @ A.astype(np.float64), s)
+    assert np.array_equal(e.cpu().numpy(), ref.astype(np.int64))
