@@ -78,6 +78,12 @@ hipError_t launch_step_f32(int32_t tile, const StepArgs &a, hipStream_t s);
 // a.fsplit, then the update from their fixed-order sum.
 bool tile_has_split(int32_t tile);
 hipError_t launch_step_f32_split(int32_t tile, const StepArgs &a, hipStream_t s);
+// `steps` steps of a small problem in one launch, from q_in, p_in at step a.t
+// into q_out, p_out (which may be the same buffers): where small_fits says so
+// it gives what the steps of that tile give.
+constexpr int32_t SMALL_STEPS_MAX = 4096;
+bool small_fits(int32_t tile, int32_t n, int32_t r_pad);
+hipError_t launch_small_steps(const StepArgs &a, int32_t steps, hipStream_t s);
 
 // Resident form: one cooperative launch runs n_steps steps.  Every workgroup
 // owns one output tile for the whole launch and keeps that tile's q and p in

@@ -1410,6 +1410,27 @@ static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
   a.fsplit = c->fsplit;
   if (split_workspace(c->tile, c->n_pad, c->r_pad, a.ksplit) > c->fsplit_cap)
     return fail(SI_ERR_STATE, "step: split-contraction workspace missing");
+  if (a.ksplit <= 1 && small_fits(c->tile, c->n, c->r_pad)) {
+    // all steps up to the next energy check in one launch
+    a.mask_out = nullptr;
+    for (int32_t left = n_steps; left > 0;) {
+      int32_t len = std::min(left, SMALL_STEPS_MAX);
+      if (c->e_every > 0) len = std::min(len, c->e_every - c->t % c->e_every);
+      if (c->inject_countdown > 0) len = 1;  // (the hook counts the steps' launches)
+      const int32_t to = c->cur ^ (len & 1);
+      a.q_in = c->q[c->cur];
+      a.p_in = c->p[c->cur];
+      a.q_out = c->q[to];
+      a.p_out = c->p[to];
+      a.t = c->t;
+      SI_HIP(c, launch_small_steps(a, len, c->stream));
+      c->cur = to;
+      c->t += len;
+      left -= len;
+      SI_ENERGY_CHECK(c);
+    }
+    return SI_OK;
+  }
   for (int32_t s = 0; s < n_steps; ++s) {
     a.q_in = c->q[c->cur];
     a.p_in = c->p[c->cur];
