@@ -184,6 +184,7 @@ struct si_ctx {
     bool valid = false;
     int64_t epoch = 0;
     int32_t t0 = 0, ckpt = 0;
+    bool recorded = false;  // adj_seg, adj_mask hold the last segment
   } tape;
   // adjoint workspace
   float *adj_ckpt = nullptr, *adj_seg = nullptr, *adj_lam = nullptr;
@@ -1453,6 +1454,24 @@ static si_status do_steps(si_ctx *c, int32_t n_steps) {
   return do_steps_f32(c, n_steps);
 }
 
+// Steps t_a .. t_a + len - 1 of a segment from its first state in adj_seg
+// (state j: q at 2 j NR, p at + NR), recording every state and wall mask.
+static si_status adj_record(si_ctx *c, int32_t t_a, int32_t len) {
+  const int64_t NR = (int64_t)c->n_pad * c->r_pad;
+  StepArgs a = step_args(c);
+  for (int32_t j = 0; j < len; ++j) {
+    float *sq = c->adj_seg + 2 * j * NR;
+    a.q_in = sq;
+    a.p_in = sq + NR;
+    a.q_out = sq + 2 * NR;
+    a.p_out = sq + 3 * NR;
+    a.mask_out = c->adj_mask + (int64_t)j * NR;
+    a.t = t_a + j;
+    SI_HIP(c, launch_step_f32(c->tile, a, c->stream));
+  }
+  return SI_OK;
+}
+
 // Adjoint, forward half: run from the current step t0 to the end of the
 // schedule, keeping the state at the start of every segment of ckpt_every
 // steps, then the seed lq_S = -(1/R) J q_S, lp_S = 0 and the loss.  Records
@@ -1499,16 +1518,32 @@ static si_status adj_forward(si_ctx *c, int32_t C, double *loss) {
     c->adj_part_cap = part_need;
   }
   const float inv_r = 1.0f / (float)c->r, inv_m = 1.0f / c->prm.m, k = c->prm.k;
-  // forward with checkpoints at the start of every segment
+  // forward with checkpoints at the start of every segment; the last one is
+  // recorded at once, as the backward half would recompute it (a fourth of its
+  // recomputation at 64 steps and segments of 16; energy checks need the
+  // states in the context's own buffers)
+  c->tape.recorded = c->e_every == 0 && nseg > 0;
   for (int32_t sg = 0; sg < nseg; ++sg) {
-    float *ck = c->adj_ckpt + (int64_t)sg * 2 * NR;
+    const int32_t len = (S - c->t) < C ? (S - c->t) : C;
+    const bool record = c->tape.recorded && sg == nseg - 1;
+    float *ck = record ? c->adj_seg : c->adj_ckpt + (int64_t)sg * 2 * NR;
     SI_HIP(c, hipMemcpyAsync(ck, c->q[c->cur], NR * sizeof(float), hipMemcpyDeviceToDevice,
                              c->stream));
     SI_HIP(c, hipMemcpyAsync(ck + NR, c->p[c->cur], NR * sizeof(float),
                              hipMemcpyDeviceToDevice, c->stream));
-    const int32_t len = (S - c->t) < C ? (S - c->t) : C;
-    si_status st = do_steps_f32(c, len);  // as the backward half recomputes it
+    if (!record) {
+      si_status st = do_steps_f32(c, len);  // as the backward half recomputes it
+      if (st != SI_OK) return st;
+      continue;
+    }
+    si_status st = adj_record(c, c->t, len);
     if (st != SI_OK) return st;
+    c->t += len;
+    const float *end = c->adj_seg + 2 * len * NR;
+    SI_HIP(c, hipMemcpyAsync(c->q[c->cur], end, NR * sizeof(float), hipMemcpyDeviceToDevice,
+                             c->stream));
+    SI_HIP(c, hipMemcpyAsync(c->p[c->cur], end + NR, NR * sizeof(float), hipMemcpyDeviceToDevice,
+                             c->stream));
   }
   SI_HIP(c, i8_refresh(c));
   // seed: lq_S = -(1/R) J q_S, lp_S = 0, and the loss
@@ -1543,22 +1578,16 @@ static si_status adj_backward(si_ctx *c, double *g_dt, double *g_zeta) {
   int lc = 0;
   // the multipliers are rewritten by the sweep: one backward per forward
   c->tape.valid = false;
-  StepArgs a = step_args(c);
   for (int32_t sg = nseg - 1; sg >= 0; --sg) {
     const int32_t t_a = t0 + sg * C;
     const int32_t len = (S - t_a) < C ? (S - t_a) : C;
     const float *ck = c->adj_ckpt + (int64_t)sg * 2 * NR;
     float *sq = c->adj_seg;  // state j of the segment: q at sq + 2 j NR, p at + NR
-    SI_HIP(c, hipMemcpyAsync(sq, ck, 2 * NR * sizeof(float), hipMemcpyDeviceToDevice,
-                             c->stream));
-    for (int32_t j = 0; j < len; ++j) {  // recompute, recording the wall masks
-      a.q_in = sq + 2 * j * NR;
-      a.p_in = sq + 2 * j * NR + NR;
-      a.q_out = sq + 2 * (j + 1) * NR;
-      a.p_out = sq + 2 * (j + 1) * NR + NR;
-      a.mask_out = c->adj_mask + (int64_t)j * NR;
-      a.t = t_a + j;
-      SI_HIP(c, launch_step_f32(c->tile, a, c->stream));
+    if (!(c->tape.recorded && sg == nseg - 1)) {
+      SI_HIP(c, hipMemcpyAsync(sq, ck, 2 * NR * sizeof(float), hipMemcpyDeviceToDevice,
+                               c->stream));
+      si_status st = adj_record(c, t_a, len);
+      if (st != SI_OK) return st;
     }
     for (int32_t j = len - 1; j >= 0; --j) {
       const int32_t n = t_a + j;

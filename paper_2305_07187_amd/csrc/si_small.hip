@@ -117,8 +117,9 @@ static hipError_t small_launch(const StepArgs &a, int32_t steps, hipStream_t s) 
 // For the tiles of 16 x 16 blocks, which the automatic choice takes up to N =
 // 224 unless the replicas fill the chip with larger ones; up to 16 replicas
 // per CU (4096) every workgroup runs at once.  One CU's matrix cores take
-// N^2 / 8 cycles a step, so N = 224 still gains (3.8 us; 5.4 at R = 64, 7.9 at R = 2000) and N = 256, which
-// the split form spreads over 32 CUs (5.2 us), would not.
+// N^2 / 8 cycles a step, so N = 224 still gains (3.8 us against 5.4 at R = 64
+// and 7.9 at R = 2000), and N = 256, which the split form spreads over 32 CUs
+// (5.2 us), would not.
 bool small_fits(int32_t tile, int32_t n, int32_t r_pad) {
   switch (tile) {
 #define SI_SMALL(id, bm, bn, wm, wn, mb, bk, st, ks) \

@@ -62,3 +62,27 @@ def test_adjoint_one_launch(n, r, ksplit):
     assert abs(float(loss.cpu()[0]) - Lo) <= 1e-5 * abs(Lo)
     assert rel(gd.cpu().numpy(), gdo) <= 1e-4 and rel(gz.cpu().numpy(), gzo) <= 1e-4
     m.close()
+
+
+@pytest.mark.parametrize("S,every", [(5, 1), (5, 5), (6, 4), (9, 100), (1, 3)])
+def test_recorded_last_segment(S, every):
+    # any split into segments gives the same loss, gradient and end state, with
+    # the halves called one by one too
+    import torch
+    si = ensure_built()
+    n, r = 300, 20
+    announce(f"adjoint S={S} segments of {every}")
+    J, x0 = to_dev(instances.make_pm1(n, 9)), to_dev(instances.make_x0(n, r, 9))
+    out = []
+    for every_k, energy_every in ((every, 0), (2, 0), (every, 3)):
+        m = si.SpringIsing(J, x0, total_steps=S, energy_every=energy_every)
+        loss = m.relaxed_energy_forward(every_k)
+        x, p, t = m.state()
+        gd, gz = m.relaxed_energy_backward()
+        torch.cuda.synchronize()
+        assert t == S
+        out.append([v.cpu().numpy() for v in (loss, gd, gz, x, p)])
+        m.close()
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert np.array_equal(a, b)
