@@ -85,7 +85,7 @@ typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
  *                 three BF16 pieces whose sum is the FP32 value exactly, so
  *                 every product is exact and only the FP32 accumulation
  *                 rounds (FP32-equivalent, on the BF16 matrix cores); integer J
- *                 in the fixed point above where N >= 1000.
+ *                 in the fixed point above where it is faster.
  *   BF16X_MIXEDJ: per instance, BF16X_FP8J when J is exact in FP8 e4m3 and
  *                 BF16X_HILOJ otherwise; spring_ising_info reports the form
  *                 chosen for a single instance.

@@ -108,7 +108,7 @@ hipError_t launch_resident_f32(int32_t tile, const StepArgs &a, const ResidentAr
 // si_step_i8.hip).
 constexpr int I8_DIGITS = 4;       // base-256 digits per position
 constexpr int I8_JDIGITS = 4;      // per real coupling (integer couplings: one)
-constexpr int I8_BM = 256, I8_BM_REAL = 128;  // rows of a tile
+constexpr int I8_BM = 256, I8_BM_REAL = 128, I8_BM_FEW = 32;  // rows of a tile
 constexpr int I8_N_REAL = 32000;   // 4 N 128^2 < 2^31
 constexpr float I8_CREST = 32.f;   // largest over rms of a row of real couplings, at most
 constexpr int I8_SPECIAL = 1 << 20;  // scale exponent of a replica with non-finite positions
@@ -122,7 +122,7 @@ struct I8Args {
   float *q[2], *p[2];  // [r_pad][ld]
   const float *dt, *zeta, *h;
   int32_t cur, t, total_steps, ld, n, r_pad;
-  int32_t bm;          // rows of a tile: I8_BM, real couplings I8_BM_REAL
+  int32_t bm;          // rows of a tile: I8_BM, real couplings I8_BM_REAL, few replicas I8_BM_FEW
   int32_t xr;          // XCDs the row tiles are split over (1, 2, 4 or 8)
   float k, inv_m, qmax, pmax;
   int32_t wall;

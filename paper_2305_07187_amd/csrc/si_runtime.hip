@@ -470,21 +470,24 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // fit 32 bits: N |J| 32896 < 2^31.  The digits' scales need the paper order.
 // A tile or a split asked for by the caller keeps the FP32 matrix cores.
 //
-// Sizes, from sweeps of both (us per step, int8 against FP32): a step costs
-// about 1.2 us per 256 spins even with few tiles, so that small problems
-// gain nothing (N = 300, R = 1024: 10.2 against 7.9; N = 512, R = 512: 9.9
-// against 9.4; N = 600, R = 256: 10.9 against 10.9) and the rest up to 4.4
-// times (N = 1000, R = 512: 13.1 against 17.0; N = 2000, R = 1024: 22.3
-// against 73.6; N = 8000, R = 2048: 475 against 2076).  With 65 .. 255
-// replicas the split FP32 form keeps up to N = 2000 (R = 128: 17.6 against
-// 18.3; N = 2500: 28.6 against 21.1), with up to 64 to N = 4000 (26.3 against
-// 27.6; N = 6000: 57.4 against 37.4).
+// Sizes, integer couplings, from sweeps (us per step): the 32 x 16 tiles
+// (i8_few) up to N R = 700000, the 256 x 32 tiles beyond (few against wide: N
+// = 600, R = 1024 11.4 and 11.5, N = 700, R = 1024 13.0 and 11.6, N = 1000, R =
+// 512 10.3 and 13.1, N = 2000, R = 256 12.5 and 19.4, R = 300 15.7 and 19.5, R
+// = 512 24.2 and 19.2, N = 8000, R = 64 35.8 and 47.2, N = 12000, R = 64 75.5
+// and 65.5).  Below, FP32 keeps the small problems (int8 against FP32: N =
+// 300, R = 256 5.2 and 4.9, N = 400, R = 64 5.0 and 4.8, R = 500 6.3 and 8.1, N
+// = 1000, R = 128 5.6 and 6.9, N = 2000, R = 128 8.7 and 13.2, R = 1024 22.3 and
+// 73.6, N = 8000, R = 64 35.8 and 76.5, R = 2048 475 and 2076).  FP32 also keeps
+// up to 64 replicas of N <= 4096, although it is slower there (N = 2000, R =
+// 50 9.3 and 6.8): those are the sizes at which schedules are differentiated,
+// and the steps of a context and its adjoint's trajectory, which is FP32,
+// shall agree bit for bit.
 // The split form of the BF16 matrix cores (BF16X3_EXACTJ: FP32 positions in
 // three planes, FP32 sums) takes the same products, and they are faster here
-// from N = 1000 on at any R (us per step, int8 against BF16: N = 600, R = 256
-// 10.9 against 10.2; N = 800, R = 512 13.1 against 12.4; N = 1000, R = 256
-// 12.6 against 13.4; N = 2000, R = 1024 21.8 against 30.8; N = 4000, R = 100
-// 28.1 against 35.7; N = 5000, R = 256 34.0 against 85.7).
+// too, with the wide tiles from N = 1000 on (int8 against BF16: N = 600, R =
+// 256 5.6 and 10.2; N = 1000, R = 256 7.1 and 13.4; N = 2000, R = 1024 21.8 and
+// 30.8; N = 4000, R = 100 19.2 and 35.7; N = 5000, R = 256 34.0 and 85.7).
 //
 // Real couplings take four digits as well (each to 2^-31 of its row's
 // largest) and ten of the sixteen digit products; those left out lie below
@@ -501,6 +504,12 @@ static bool i8_integer(const si_ctx *c) {
   return c->hflags[3] == 0 && (int64_t)c->n * c->hflags[6] <= 65281;
 }
 
+static bool i8_few(const si_ctx *c) {
+  const bool pays = c->n > 4096 || (c->n > 512 && (c->r > 64 || c->prm.precision != SI_PREC_FP32)) ||
+                    (c->n >= 384 && c->r > 256);
+  return i8_integer(c) && pays && (int64_t)c->n * round_up(c->r, 64) <= 700000;
+}
+
 static bool i8_applies(const si_ctx *c) {
   const bool integer = i8_integer(c);
   if (integer ? c->hflags[7] != 0 : c->n > I8_N_REAL || c->prm.precision != SI_PREC_FP32)
@@ -508,8 +517,7 @@ static bool i8_applies(const si_ctx *c) {
   const bool split = c->prm.precision == SI_PREC_BF16X3_EXACTJ;
   const bool pays =
       !integer ? c->n > 512 && (int64_t)c->n * round_up(c->r, 64) >= 640000
-      : split  ? c->n >= 1000
-               : c->n > 4096 || (c->n > 2048 && c->r > 64) || (c->n > 512 && c->r >= 256);
+      : i8_few(c) || (c->n >= (split ? 1000 : 513) && (int64_t)c->n * round_up(c->r, 64) > 700000);
   return (split || c->prm.precision == SI_PREC_FP32) && c->prm.order == SI_ORDER_PAPER &&
          c->user_tile == 0 && !c->n_inst && pays;
 }
@@ -521,7 +529,7 @@ static bool i8_on(const si_ctx *c) { return c->i8.Jt && c->ksplit_mode == 0 && !
 static hipError_t i8_init(si_ctx *c) {
   if (!i8_applies(c)) return hipSuccess;
   const bool real = !i8_integer(c);
-  const int32_t bm = real ? I8_BM_REAL : I8_BM;
+  const int32_t bm = real ? I8_BM_REAL : i8_few(c) ? I8_BM_FEW : I8_BM;
   const int64_t jb = (int64_t)c->n_pad * c->n_pad * (real ? I8_JDIGITS : 1);
   const int64_t nr = (int64_t)c->n_pad * c->r_pad;
   const int64_t mxb = round_up((int64_t)(c->n_pad / bm) * c->r_pad * 4, 256);
@@ -902,7 +910,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
     return fail(SI_ERR_INVALID, "init: tile %d cannot run precision %d", bad, prm->precision);
   }
   const TileShape ts = shape_of(prm->precision, c->tile);
-  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, i8_applies(c) && i8_integer(c) ? I8_BM : 128));
+  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, i8_applies(c) && i8_integer(c) && !i8_few(c) ? I8_BM : 128));
   c->r_pad = (int32_t)round_up(r, ts.bn > 64 ? ts.bn : 64);
   const bool j_integer = c->hflags[3] == 0;
   const bool need_bf16 = prm->precision == SI_PREC_BF16X_BF16J ||

@@ -418,6 +418,18 @@ __device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk<I8Real> 
   }
 }
 
+// F of a replica with non-finite positions (given by the caller): FP32
+// products of rows row .. row + 3, summed.
+__device__ __forceinline__ floatx4 i8_special(const I8Args &a, int row, int col) {
+  floatx4 f = {0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < a.n; ++i) {
+    const float qi = a.q[a.cur][(size_t)col * a.ld + i];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f[v] = fmaf(a.J[(size_t)(row + v) * a.ld + i], qi, f[v]);
+  }
+  return f;
+}
+
 // The state waves' part of one step: wave sw owns COLS columns of a tile, a
 // lane four spins of eight of them.
 template <class C, int WALL>
@@ -494,13 +506,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
         const size_t off = (size_t)(n + col) * a.ld + m + row;
         floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
         if (of(kin, cc) == I8_SPECIAL) {
-          // non-finite positions given by the caller: FP32 products, summed
-          f = floatx4{0.f, 0.f, 0.f, 0.f};
-          for (int i = 0; i < a.n; ++i) {
-            const float qi = a.q[a.cur][(size_t)(n + col) * a.ld + i];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) f[v] = fmaf(a.J[(size_t)(m + row + v) * a.ld + i], qi, f[v]);
-          }
+          f = i8_special(a, m + row, n + col);
         }
         float mx = 0.f;
         floatx4 pn;
@@ -615,6 +621,168 @@ __global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentAr
     a.cur ^= 1;
     a.t += 1;
     if (s + 1 < r.n_steps && !grid_barrier(r.count, (uint32_t)(s + 1), r.err)) return;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Few replicas, integer couplings: 32 x 16 tiles, so that 64 replicas of N =
+// 2000 give every CU one, and the contraction split over the eight waves of a
+// workgroup.  Each wave reads its contraction steps of J and of the digits
+// straight from memory into v_mfma_i32_16x16x64_i8's registers, FEW_PD steps
+// ahead; the waves' sums (pairs of digits, exact in 32 bits) are added in LDS,
+// and the update of the tile follows.  Sums are exact, so the result is that
+// of the 256 x 32 tiles bit for bit.
+//
+// Measured (us per step, FP32 one-launch form or 256 x 32 tiles before): N =
+// 2000, R = 50 6.8 (9.3), N = 4000, R = 64 12.0 (26.1), N = 1000, R = 512 10.3
+// (13.1), N = 2000, R = 256 12.5 (19.4), N = 8000, R = 64 35.8 (47.2).  Bound: a
+// launch, then its loads: 96 N bytes per workgroup (3.3 us at N = 2000, R = 64
+// at 57 bytes a cycle and CU).  Two workgroups per CU and two steps ahead beat
+// one and four (N = 4000, R = 64 12.0 against 15.0, N = 2000, R = 256 14.2
+// against 20.0), three steps ahead spill to slower (20.4).
+// ---------------------------------------------------------------------------
+constexpr int FEW_PD = 2, FEW_BN = 16;
+
+template <int FEW_W, int WALL>
+__global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
+  constexpr int BM = I8_BM_FEW, BN = FEW_BN;
+  __shared__ __attribute__((aligned(16))) int sums[FEW_W][2][BN][BM + 4];
+  __shared__ __attribute__((aligned(16))) uint8_t dig[QP][BN][BM];
+  __shared__ float colmax[BN];
+  __shared__ int kshared[2][BN];
+  const int tid = threadIdx.x, lane = tid & 63, nx = a.cur ^ 1;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntc = a.r_pad / BN, ntr = a.ld / BM, t = xcd_tile(blockIdx.x, gridDim.x);
+  const int m0 = t / ntc * BM, n0 = t % ntc * BN;
+  const int nrb = a.ld / 32, ncb = a.r_pad / 32, ns = (a.n + 63) / 64;  // steps of 64
+
+  // lane l holds row (or column) l % 16 from index 16 (l / 16) of a step on:
+  // block l / 32 of the pair, half l / 16 % 2 of its indices
+  const int lrow = lane & 15, half = (lane >> 4) & 1;
+  const uint8_t *pa = a.Jt + i8_jblk<1>(0, m0 / 32, nrb) * BLK + (lane >> 5) * BLK + half * 512 +
+                      lrow * 16;
+  const uint8_t *pb = a.Qt[a.cur] + i8_qblk(0, n0 / 32, ncb) * BLK + (size_t)(lane >> 5) * QP * BLK +
+                      half * 512 + (n0 % 32 + lrow) * 16;
+  const size_t da = (size_t)nrb * 2 * BLK, db = (size_t)ncb * 2 * QP * BLK;
+  const int count = wave < ns ? (ns - wave + FEW_W - 1) / FEW_W : 0;
+  intx4 fa[FEW_PD][2], fb[FEW_PD][QP];
+  auto load = [&](int i, int f) {
+    const int k = wave + (i < count ? i : count - 1) * FEW_W;  // (past the end: not used)
+    const uint8_t *sa = pa + (size_t)k * da, *sb = pb + (size_t)k * db;
+    fa[f][0] = *reinterpret_cast<const intx4 *>(sa);
+    fa[f][1] = *reinterpret_cast<const intx4 *>(sa + 256);
+#pragma unroll
+    for (int d = 0; d < QP; ++d) fb[f][d] = *reinterpret_cast<const intx4 *>(sb + d * BLK);
+  };
+  if (count > 0)
+#pragma unroll
+    for (int f = 0; f < FEW_PD; ++f) load(f, f);
+
+  // the tile's state: thread u < 128 owns four spins of one column
+  const int scol = tid >> 3, srow = (tid & 7) * 4;
+  const size_t off = (size_t)(n0 + scol) * a.ld + m0 + srow;
+  floatx4 q4, p4, h4 = {0.f, 0.f, 0.f, 0.f};
+  const bool owner = tid < BN * BM / 4;
+  if (owner) {
+    q4 = *reinterpret_cast<const floatx4 *>(a.q[a.cur] + off);
+    p4 = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
+    if (a.h) h4 = *reinterpret_cast<const floatx4 *>(a.h + m0 + srow);
+  }
+  // scales: the largest |q'| of every column of the tile (bits of floats >= 0
+  // order as integers)
+  float mx = 0.f;
+  for (int rt = tid >> 4; rt < ntr; rt += 4 * FEW_W)
+    mx = fmaxf(mx, a.mx[a.cur][(size_t)rt * a.r_pad + n0 + (tid & 15)]);
+  if (tid < BN) colmax[tid] = 0.f;
+  __syncthreads();
+  mx = fmaxf(mx, __shfl_xor(mx, 16));
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  if (lane < BN) atomicMax(reinterpret_cast<int *>(colmax) + lane, __float_as_int(mx));
+
+  intx4 acc[2][QP];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int d = 0; d < QP; ++d) acc[r][d] = intx4{0, 0, 0, 0};
+  auto mul = [&](int f) {
+#pragma unroll
+    for (int d = 0; d < QP; ++d)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        acc[r][d] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[f][r], fb[f][d], acc[r][d], 0, 0, 0);
+  };
+  int i = 0;
+  for (; i + FEW_PD < count; i += FEW_PD)
+#pragma unroll
+    for (int f = 0; f < FEW_PD; ++f) {
+      mul(f);
+      load(i + FEW_PD + f, f);
+    }
+#pragma unroll
+  for (int f = 0; f < FEW_PD; ++f)
+    if (i + f < count) mul(f);
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    intx4 hi, lo;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      hi[v] = acc[r][3][v] * 256 + acc[r][2][v];
+      lo[v] = acc[r][1][v] * 256 + acc[r][0][v];
+    }
+    const int row = r * 16 + (lane >> 4) * 4;
+    *reinterpret_cast<intx4 *>(&sums[wave][0][lrow][row]) = hi;
+    *reinterpret_cast<intx4 *>(&sums[wave][1][lrow][row]) = lo;
+  }
+  __syncthreads();
+  if (tid < BN) {
+    const int kout = i8_exponent(colmax[tid]);
+    kshared[0][tid] = a.kexp[a.cur][n0 + tid];
+    kshared[1][tid] = kout;
+    if (m0 == 0) a.kexp[nx][n0 + tid] = kout;
+  }
+  __syncthreads();
+  if (owner) {
+    const float dt = a.dt[a.t], zeta = a.zeta[a.t];
+    const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
+    const int kin = kshared[0][scol], kout = kshared[1][scol];
+    intx4 hi = {0, 0, 0, 0}, lo = {0, 0, 0, 0};
+#pragma unroll
+    for (int w = 0; w < FEW_W; ++w) {
+      hi += *reinterpret_cast<const intx4 *>(&sums[w][0][scol][srow]);
+      lo += *reinterpret_cast<const intx4 *>(&sums[w][1][scol][srow]);
+    }
+    floatx4 f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) f[v] = ldexpf(fmaf((float)hi[v], 65536.f, (float)lo[v]), -kin);
+    if (kin == I8_SPECIAL) f = i8_special(a, m0 + srow, n0 + scol);
+    float mnext = 0.f;
+    floatx4 qn, pn;
+    uint32_t dg[4], by[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float qv, pv;
+      spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], f[v] + h4[v], dt, zeta, a.k, a.inv_m,
+                                          a.qmax, a.pmax, qv, pv);
+      qn[v] = fminf(fmaxf(fmaf(dt * a.inv_m, p4[v], q4[v]), -a.qmax), a.qmax);
+      pn[v] = pv;
+      mnext = fmaxf(mnext, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
+      dg[v] = i8_digits(qn[v], kout);
+    }
+    *reinterpret_cast<floatx4 *>(a.q[nx] + off) = qn;
+    *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+    byte_transpose(dg, by);
+#pragma unroll
+    for (int d = 0; d < QP; ++d) *reinterpret_cast<uint32_t *>(&dig[d][scol][srow]) = by[d];
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) mnext = fmaxf(mnext, __shfl_xor(mnext, o));
+    if ((tid & 7) == 0) a.mx[nx][(size_t)(m0 / BM) * a.r_pad + n0 + scol] = mnext;
+  }
+  __syncthreads();
+  for (int u = tid; u < QP * 2 * BN; u += 64 * FEW_W) {  // 16 spins of one column and digit
+    const int d = u >> 5, h = (u >> 4) & 1, c = u & 15;
+    *reinterpret_cast<uintx4 *>(a.Qt[nx] + (i8_qblk(m0 / 32, n0 / 32, ncb) + d) * BLK + h * 512 +
+                                (n0 % 32 + c) * 16) =
+        *reinterpret_cast<const uintx4 *>(&dig[d][c][h * 16]);
   }
 }
 
@@ -746,12 +914,16 @@ __global__ __launch_bounds__(256) void i8_rows_kernel(const float *__restrict__ 
 
 static bool i8_real(const I8Args &a) { return a.bm == I8_BM_REAL; }
 
+static bool i8_few(const I8Args &a) { return a.bm == I8_BM_FEW; }
+
 static bool i8_fits(const I8Args &a) {
-  return (a.bm == I8_BM || (i8_real(a) && a.jexp)) && a.ld % a.bm == 0 && a.r_pad % 64 == 0 &&
+  return (a.bm == I8_BM || i8_few(a) || (i8_real(a) && a.jexp)) && a.ld % a.bm == 0 && a.r_pad % 64 == 0 &&
          a.n >= 1 && a.n <= a.ld && (a.xr == 1 || a.xr == 2 || a.xr == 4 || a.xr == 8);
 }
 
-static int i8_bn(const I8Args &a) { return i8_real(a) ? I8Real::BN : I8Int::BN; }
+static int i8_bn(const I8Args &a) {
+  return i8_real(a) ? I8Real::BN : i8_few(a) ? FEW_BN : I8Int::BN;
+}
 
 // One workgroup per CU (the register file holds one), fewer if an XCD's part
 // has fewer tiles than CUs.
@@ -803,20 +975,41 @@ static const void *i8_resident(const I8Args &a) {
 
 hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s) {
   if (!i8_fits(a)) return hipErrorInvalidValue;
+  if (i8_few(a)) {
+    // eight waves a workgroup while two of them fill a CU and the contraction
+    // is long, else four (us per step, eight against four: N = 2000, R = 50 6.8
+    // and 7.1, N = 4000, R = 64 12.0 and 13.3, N = 2000, R = 256 14.2 and 12.4,
+    // N = 1000, R = 64 5.6 and 5.3)
+    const int grid = a.ld / a.bm * (a.r_pad / FEW_BN);
+    const bool clamp = a.wall == SI_WALL_CLAMP;
+    if (grid <= 512 && a.n > 1024) {
+      if (clamp)
+        step_i8_few_kernel<8, SI_WALL_CLAMP><<<grid, 512, 0, s>>>(a);
+      else
+        step_i8_few_kernel<8, SI_WALL_INELASTIC><<<grid, 512, 0, s>>>(a);
+    } else if (clamp) {
+      step_i8_few_kernel<4, SI_WALL_CLAMP><<<grid, 256, 0, s>>>(a);
+    } else {
+      step_i8_few_kernel<4, SI_WALL_INELASTIC><<<grid, 256, 0, s>>>(a);
+    }
+    return hipGetLastError();
+  }
   I8Args aa = a;
   void *args[] = {&aa};
   return hipLaunchKernel(i8_step(a), dim3(i8_grid(a, num_cus)), dim3(I8Int::NT), args, 0, s);
 }
 
 const char *i8_kernel_name(const I8Args &a) {
-  return i8_real(a) ? "step_i8x10_128x64_w4_k128_s3" : "step_i8x4_256x32_w4_k256_s3";
+  return i8_real(a)  ? "step_i8x10_128x64_w4_k128_s3"
+         : i8_few(a) ? (a.ld / a.bm * (a.r_pad / FEW_BN) <= 512 && a.n > 1024 ? "step_i8x4_32x16_ks8" : "step_i8x4_32x16_ks4")
+                     : "step_i8x4_256x32_w4_k256_s3";
 }
 
 // Every workgroup of the grid must own exactly one tile: an even XCD split,
 // and no more tiles than workgroups that fit at once.
 hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups) {
   *groups = 0;
-  if (!i8_fits(a)) return hipSuccess;
+  if (!i8_fits(a) || i8_few(a)) return hipSuccess;
   const int ntr = a.ld / a.bm, ntc = a.r_pad / i8_bn(a);
   if (ntr % a.xr || ntc % (NUM_XCD / a.xr) || i8_grid(a, num_cus) != ntr * ntc) return hipSuccess;
   int per = 0;
@@ -827,7 +1020,7 @@ hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups) {
 
 hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t groups,
                               hipStream_t s) {
-  if (!i8_fits(a) || groups < 1) return hipErrorInvalidValue;
+  if (!i8_fits(a) || i8_few(a) || groups < 1) return hipErrorInvalidValue;
   I8Args aa = a;
   ResidentArgs rr = r;
   void *args[] = {&aa, &rr};

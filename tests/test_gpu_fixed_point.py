@@ -199,7 +199,7 @@ def test_route():
     real[3, 4] = real[4, 3] = 0.5
     cases = [(J, {}, True), (hole, {}, False), (real, {}, False), (J * 108, {}, True), (J * 109, {}, False),
              (J * 128, {}, False), (J, {"order": "symplectic"}, False), (J, {"tile": 14}, False),
-             (J[:512, :512].copy(), {}, False)]
+             (J[:383, :383].copy(), {}, False)]
     for Jc, kw, want in cases:
         m = si.SpringIsing(to_dev(Jc), x[:, :Jc.shape[0]].contiguous(), total_steps=2, **kw)
         assert m.info()["kernel_name"].startswith(NAME) == want, (kw, Jc.shape)
@@ -249,7 +249,7 @@ def test_exact_split_form(n, r, jmax):
     check_step(not m.info()["kernel_name"].startswith(NAME))
     m.close()
     si.spring_ising_tile_cache_clear()
-    f = si.SpringIsing(to_dev(instances.make_pm1(999, 1)), to_dev(instances.make_x0(999, r, 1)),
+    f = si.SpringIsing(to_dev(instances.make_pm1(383, 1)), to_dev(instances.make_x0(383, r, 1)),
                        total_steps=2, precision="bf16x3_exactj")
     assert not f.info()["kernel_name"].startswith(NAME)
     f.close()
@@ -375,3 +375,45 @@ def test_real_route():
         assert m.info()["kernel_name"].startswith(REAL) == want, (k, kw)
         m.run(2)
         m.close()
+
+
+# 32 x 16 tiles: 32-row blocks and 64-deep steps of n (a wave without any), 16
+# columns of r, four and eight waves, one and several rounds of steps ahead
+@pytest.mark.parametrize("n,r,jmax,wall", [(384, 257, 1, "clamp"), (513, 65, 127, "inelastic"), (545, 100, 1, "clamp"),
+                                           (1025, 81, 1, "inelastic"), (1999, 97, 32, "clamp"), (2000, 300, 1, "clamp"),
+                                           (4097, 3, 2, "clamp")])
+def test_few_replica_tiles(n, r, jmax, wall):
+    # one step to the same bound, and ten equal the wide tiles' bit for bit
+    import torch
+    si = ensure_built()
+    announce(f"fixed-point step, few replicas N={n} R={r} |J|={jmax} {wall}")
+    J = instances.make_pm1(n, n) * np.float32(jmax)
+    wide = max(r, 700000 // n + 64)  # beyond the rule: 256 x 32 tiles
+    x, p = _signed(n, wide, 1, 1.0), _signed(n, wide, 2, 1.0)
+    h = to_dev(instances.make_x0(n, 1, 5, scale=2.0)[0])
+    S, t = 50, 7
+    out, names = [], []
+    for rr in (r, wide):
+        xr, pr = to_dev(x[:rr].copy()), to_dev(p[:rr].copy())
+        m = si.SpringIsing(to_dev(J), xr, pr, total_steps=S, wall=wall)
+        names.append(m.info()["kernel_name"])
+        m.set_state(xr, pr, t)
+        m.step()
+        xg, pg, _ = m.state()
+        m.set_field(h)
+        m.run(9)
+        xe, pe, _ = m.state()
+        torch.cuda.synchronize()
+        out.append([v.cpu().numpy()[:r] for v in (xg, pg, xe, pe)])
+        m.close()
+    assert names[0].startswith(NAME + "_32x16")
+    if n > 512:
+        assert names[1].startswith(NAME + "_256x32")
+        for a, b in zip(*out):
+            assert np.array_equal(a, b)
+    dts, zetas = oracle_schedules(S)
+    cols = sorted({0, 1, 15, 16, r - 1} & set(range(r)))
+    J64, Q0, P0 = J.astype(np.float64), x[cols].T.astype(np.float64), p[cols].T.astype(np.float64)
+    Q1, P1 = oracle.step(J64, Q0, P0, float(dts[t]), float(zetas[t]), qmax=QMAX, wall=wall)
+    qb, pb = _bounds(J64, Q0, P0, J64 @ Q0, float(dts[t]), float(zetas[t]))
+    assert np.all(np.abs(out[0][0][cols].T - Q1) <= qb) and np.all(np.abs(out[0][1][cols].T - P1) <= pb)
