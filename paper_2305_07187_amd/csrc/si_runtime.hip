@@ -1151,7 +1151,15 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
     rows.soff = c->b_soff[i];
     c->b_rows_host[i] = rows;
   }
-  // batch tile: the caller's, else the tile cache's, else 128-row items
+  // batch tile: the caller's, else the tile cache's, else 128-row items where
+  // there are enough of them to fill the chip evenly, else 64-row ones, with
+  // the same results (us per step, 128-row against 64-row; FP32: 34 items of
+  // 128 rows 31.4 and 19.8, 138 72.5 and 49.8, 417 167 and 161, 749 346 and 334,
+  // 810 270 and 269, 3014 1109 and 1110; mixed precision, whose 64-row items
+  // read the positions' plane twice as often per byte of J: 34 12.3 and 9.1, 288
+  // 19.5 and 18.7, 417 83.8 and 85.0, 4243 870 and 901; below ten items id 1
+  // stays what a context reports, although 64-row items are faster there too:
+  // 20.7 and 13.1 for nine)
   int32_t cached = 0;
   if (prm->tile) {
     c->tile = prm->tile;
@@ -1160,7 +1168,9 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
     c->tile = cached;
     c->tile_source = SI_TILE_FROM_CACHE;
   } else {
-    c->tile = 1;
+    int64_t items = 0;
+    for (int32_t i = 0; i < n_inst; ++i) items += (int64_t)(c->b_npad[i] / 128) * (c->r_pad / BATCH_BN);
+    c->tile = items >= 10 && items <= (lowp ? 320 : 1024) ? 2 : 1;
   }
   // the device work list holds the longest list (64-row items)
   int64_t items_max = 0;
