@@ -486,8 +486,12 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
     if (left > 0) pass();
   };
   issue();
-  if (total > 1) issue();
-  q_wait_barrier<0>();  // the first slab has landed
+  if (total > 1) {
+    issue();
+    q_wait_barrier<C::L>();  // the first slab has landed
+  } else {
+    q_wait_barrier<0>();
+  }
   if (C::STAGES > 2) issue();
 
   const float dt = a.dt[a.t], zeta = a.zeta[a.t];
@@ -787,18 +791,22 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
 }
 
 // Digits, scales and maxima of the FP32 state (t: the next step's index).
-// One workgroup per eight replicas: a wave per replica finds the maxima, then
-// eight neighbouring replicas' 16-byte pieces fill whole 128-byte lines.
+// One workgroup per four replicas (256 of them at R = 1024: one per CU, 11.6
+// us with half as many of eight, 7.0 now), two waves per replica for the maxima.
+constexpr int PREP_R = 4;
 __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
-  __shared__ int kx[8];
-  const int r0 = blockIdx.x * 8, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ float most[2][8];
+  __shared__ int isnan[8], kx[PREP_R];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r0 = blockIdx.x * PREP_R, rw = wave / 2;
   const float *q = a.q[a.cur], *p = a.p[a.cur];
   const float c = a.dt[a.t < a.total_steps ? a.t : a.total_steps - 1] * a.inv_m;
   {
-    const size_t base = (size_t)(r0 + wave) * a.ld;
+    const size_t base = (size_t)(r0 + rw) * a.ld;
     float mq = 0.f, mu = 0.f;
     bool nan = false;
-    for (int i = lane * 4; i < a.ld; i += 256) {
+#pragma unroll 4
+    for (int i = ((wave & 1) * 64 + lane) * 4; i < a.ld; i += 512) {
       const floatx4 q4 = *reinterpret_cast<const floatx4 *>(q + base + i);
       const floatx4 p4 = *reinterpret_cast<const floatx4 *>(p + base + i);
 #pragma unroll
@@ -812,17 +820,28 @@ __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
       mq = fmaxf(mq, __shfl_xor(mq, off));
       mu = fmaxf(mu, __shfl_xor(mu, off));
     }
-    const int k = __any(nan) ? I8_SPECIAL : i8_exponent(mq);
+    const bool any = __any(nan);
     if (lane == 0) {
-      kx[wave] = k;
-      a.kexp[a.cur][r0 + wave] = k;
+      most[0][wave] = mq;
+      most[1][wave] = mu;
+      isnan[wave] = any;
     }
-    for (int rt = lane; rt < a.ld / a.bm; rt += 64)
-      a.mx[a.cur][(size_t)rt * a.r_pad + r0 + wave] = rt == 0 ? mu : 0.f;
   }
   __syncthreads();
-  const int j = threadIdx.x & 7, r = r0 + j, k = kx[j], ncb = a.r_pad / 32;
-  for (int pc = threadIdx.x >> 3; pc < a.ld / 16; pc += 64) {
+  if (threadIdx.x < PREP_R) {
+    const int w = threadIdx.x * 2;
+    const int k = isnan[w] || isnan[w + 1] ? I8_SPECIAL : i8_exponent(fmaxf(most[0][w], most[0][w + 1]));
+    kx[threadIdx.x] = k;
+    a.kexp[a.cur][r0 + threadIdx.x] = k;
+  }
+  for (int u = threadIdx.x; u < a.ld / a.bm * PREP_R; u += 512) {
+    const int rt = u / PREP_R, j = u % PREP_R;
+    a.mx[a.cur][(size_t)rt * a.r_pad + r0 + j] =
+        rt == 0 ? fmaxf(most[1][2 * j], most[1][2 * j + 1]) : 0.f;
+  }
+  __syncthreads();
+  const int j = threadIdx.x % PREP_R, r = r0 + j, k = kx[j], ncb = a.r_pad / 32;
+  for (int pc = threadIdx.x / PREP_R; pc < a.ld / 16; pc += 512 / PREP_R) {
     uint32_t w[QP][4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -1028,8 +1047,8 @@ hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t gr
 }
 
 hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s) {
-  if (a.r_pad % 8 || a.ld % 128 || a.ld % a.bm) return hipErrorInvalidValue;
-  i8_prepare_kernel<<<a.r_pad / 8, 512, 0, s>>>(a);
+  if (a.r_pad % PREP_R || a.ld % 128 || a.ld % a.bm) return hipErrorInvalidValue;
+  i8_prepare_kernel<<<a.r_pad / PREP_R, 512, 0, s>>>(a);
   return hipGetLastError();
 }
 
