@@ -235,6 +235,11 @@ hipError_t launch_hamiltonian_partial(const float *J, const float *q, const floa
                                       hipStream_t s);
 hipError_t launch_best_update(const double *e, double *best_e, int32_t *valid, const int8_t *S8,
                               int8_t *best_s, int32_t r, int32_t n_pad, hipStream_t s);
+// From the integer sums of launch_energy_i8: also writes the energies e and
+// clears the sums (in place of launch_energy_i8_finalize).
+hipError_t launch_best_update_i8(int32_t *acc, double *e, double *best_e, int32_t *valid,
+                                 const int8_t *S8, int8_t *best_s, int32_t r, int32_t n_pad,
+                                 hipStream_t s);
 hipError_t launch_fill_f64(double *p, int64_t count, double v, hipStream_t s);
 
 // Exact energy: s = sign(q) as int8 into S8, then G = J8.S8 on int8 MFMA,
@@ -303,8 +308,10 @@ struct StateCopy {
 // `planes` BF16 planes of q.
 hipError_t launch_pack_rows(const StateCopy &c, const float *x, const float *p, hipStream_t s);
 hipError_t launch_unpack_rows(const StateCopy &c, float *x, float *p, hipStream_t s);
-// Signs of q, or the spins src8 (device layout), into the caller's rows.
-hipError_t launch_unpack_spins(const StateCopy &c, const int8_t *src8, int8_t *out, hipStream_t s);
+// Signs of q, or the spins src8 (device layout), into the caller's rows; and,
+// unless null, the count x r values e_src to e_out.
+hipError_t launch_unpack_spins(const StateCopy &c, const int8_t *src8, int8_t *out,
+                               const double *e_src, double *e_out, hipStream_t s);
 hipError_t launch_pack_matrix(const float *src, int32_t n, float *dst, int8_t *dst8,
                               int32_t n_pad, hipStream_t s);
 hipError_t launch_pack_field(const float *h, int32_t n, float *hf, int8_t *h8,

@@ -209,9 +209,15 @@ __global__ __launch_bounds__(256) void unpack_rows_kernel(StateCopy c, float *__
 // Spins into the caller's rows: the signs of q, or of the kept spins src8.
 __global__ __launch_bounds__(256) void unpack_spins_kernel(StateCopy c,
                                                            const int8_t *__restrict__ src8,
-                                                           int8_t *__restrict__ out) {
+                                                           int8_t *__restrict__ out,
+                                                           const double *__restrict__ e_src,
+                                                           double *__restrict__ e_out) {
   const RowAt at(c);
   if (at.row >= c.r) return;
+  if (e_out && blockIdx.y == 0 && at.lane == 0) {
+    const int64_t k = (int64_t)(blockIdx.x / (c.r_pad / 4)) * c.r + at.row;
+    e_out[k] = e_src[k];
+  }
   const int n = at.d->n;
   const int64_t from = (int64_t)at.row * at.d->n_pad;
   const float *q = at.d->q[c.cur] + from;
@@ -309,10 +315,10 @@ hipError_t launch_unpack_rows(const StateCopy &c, float *x, float *p, hipStream_
 }
 
 hipError_t launch_unpack_spins(const StateCopy &c, const int8_t *src8, int8_t *out,
-                               hipStream_t s) {
+                               const double *e_src, double *e_out, hipStream_t s) {
   dim3 grid;
   if (copy_grid(c, &grid) != hipSuccess) return hipErrorInvalidValue;
-  unpack_spins_kernel<<<grid, 256, 0, s>>>(c, src8, out);
+  unpack_spins_kernel<<<grid, 256, 0, s>>>(c, src8, out, e_src, e_out);
   return hipGetLastError();
 }
 

@@ -2026,33 +2026,39 @@ static si_status batch_energy(si_ctx *c, int32_t *e_int, double *e_real) {
 si_status spring_ising_spins(si_ctx *c, int8_t *s) {
   SI_USABLE(c);
   if (!is_device_ptr(s)) return fail(SI_ERR_INVALID, "spins: s must be a device pointer");
-  SI_HIP(c, launch_unpack_spins(state_copy(c), nullptr, s, c->stream));
+  SI_HIP(c, launch_unpack_spins(state_copy(c), nullptr, s, nullptr, nullptr, c->stream));
+  return SI_OK;
+}
+
+// The exact int32 energy of a single context: integer J (and field) with a
+// sum that cannot overflow.
+static bool energy_exact(const si_ctx *c) {
+  const int64_t jmax = c->hflags[6];
+  const int64_t bound = (int64_t)c->n * c->n * jmax +
+                        (c->has_field ? 2 * (int64_t)c->n * c->field_maxabs : 0);
+  return c->J8 && (!c->has_field || c->field_integer) && bound < (1LL << 31);
+}
+
+// Its sums into eacc, the current spins into S8.
+static si_status energy_sums(si_ctx *c) {
+  SI_HIP(c, launch_sign(c->q[c->cur], c->S8, c->n_pad, c->r_pad, c->stream));
+  SI_HIP(c, launch_energy_i8(c->J8, c->S8, c->has_field ? c->h8 : nullptr, c->eacc, c->n_pad,
+                             c->r_pad, energy_i8_ksplit(c->n_pad, c->r_pad, c->num_cus),
+                             c->stream));
   return SI_OK;
 }
 
 // Energies of the current spins into device outputs (no argument checks).
-// *signs: whether it left the current spins in S8.
-static si_status energy_into(si_ctx *c, int32_t *e_int, double *e_real, bool *signs = nullptr) {
-  if (signs) *signs = false;
+static si_status energy_into(si_ctx *c, int32_t *e_int, double *e_real) {
   if (!e_int && !e_real) return SI_OK;
-  if (c->n_inst) {
-    if (signs) *signs = c->eb_n_i8 > 0;
-    return batch_energy(c, e_int, e_real);
-  }
-  // exact int32 path: integer J (and field) with a sum that cannot overflow
-  const int64_t jmax = c->hflags[6];
-  const int64_t bound = (int64_t)c->n * c->n * jmax +
-                        (c->has_field ? 2 * (int64_t)c->n * c->field_maxabs : 0);
-  const bool exact = c->J8 && (!c->has_field || c->field_integer) && bound < (1LL << 31);
+  if (c->n_inst) return batch_energy(c, e_int, e_real);
+  const bool exact = energy_exact(c);
   if (e_int && !exact)
     return fail(SI_ERR_UNSUPPORTED,
                 "energy: exact int32 energy needs integer |J_ij| <= 127 (and integer field)");
-  const int8_t *h8 = c->has_field ? c->h8 : nullptr;
   if (exact) {
-    if (signs) *signs = true;
-    SI_HIP(c, launch_sign(c->q[c->cur], c->S8, c->n_pad, c->r_pad, c->stream));
-    SI_HIP(c, launch_energy_i8(c->J8, c->S8, h8, c->eacc, c->n_pad, c->r_pad,
-                               energy_i8_ksplit(c->n_pad, c->r_pad, c->num_cus), c->stream));
+    si_status st = energy_sums(c);
+    if (st != SI_OK) return st;
     SI_HIP(c, launch_energy_i8_finalize(c->eacc, c->r, e_int, e_real, c->stream));
   } else {
     const float *hf = c->has_field ? c->hf : nullptr;
@@ -2071,20 +2077,30 @@ si_status spring_ising_energy(si_ctx *c, int32_t *e_int, double *e_real) {
   return energy_into(c, e_int, e_real);
 }
 
-// Best-state update from the energies e of the current spins (out_rows()
-// doubles on the device); signs: S8 holds the current spins.
-static si_status best_update_from(si_ctx *c, const double *e, bool signs) {
+// Energies of the current spins into e (out_rows() doubles on the device) and
+// the best-state update from them.
+static si_status best_update_into(si_ctx *c, double *e) {
   SI_HIP(c, ensure_best_buffers(c));
+  c->best_any = true;
+  if (!c->n_inst && energy_exact(c)) {
+    si_status st = energy_sums(c);
+    if (st != SI_OK) return st;
+    SI_HIP(c, launch_best_update_i8(c->eacc, e, c->best_e, c->best_valid, c->S8, c->best_s, c->r,
+                                    c->n_pad, c->stream));
+    return SI_OK;
+  }
+  si_status st = energy_into(c, nullptr, e);
+  if (st != SI_OK) return st;
   const float *q = c->n_inst ? c->b_q[c->cur][0] : c->q[c->cur];
   const int32_t n_pad = c->n_inst ? (int32_t)(c->b_stot / c->r_pad) : c->n_pad;
-  if (!signs) SI_HIP(c, launch_sign(q, c->S8, n_pad, c->r_pad, c->stream));
+  if (!(c->n_inst && c->eb_n_i8))  // (the energy of integer instances left the signs in S8)
+    SI_HIP(c, launch_sign(q, c->S8, n_pad, c->r_pad, c->stream));
   if (c->n_inst)
     SI_HIP(c, launch_best_update_batch(e, c->best_e, c->best_valid, c->S8, c->best_s, c->eb_desc,
                                        c->n_inst, c->r, c->stream));
   else
     SI_HIP(c, launch_best_update(e, c->best_e, c->best_valid, c->S8, c->best_s, c->r, c->n_pad,
                                  c->stream));
-  c->best_any = true;
   return SI_OK;
 }
 
@@ -2092,19 +2108,13 @@ static si_status record_check(si_ctx *c) {
   const int32_t row = c->t / c->e_every - 1;
   if (row < 0 || row >= c->e_rows) return SI_OK;
   double *e = c->etrace + (int64_t)row * c->out_rows();
-  bool signs = false;
-  si_status st = energy_into(c, nullptr, e, &signs);
-  if (st != SI_OK) return st;
-  return best_update_from(c, e, signs);
+  return best_update_into(c, e);
 }
 
 si_status spring_ising_update_best(si_ctx *c) {
   SI_USABLE(c);
   SI_HIP(c, ensure_best_buffers(c));
-  bool signs = false;
-  si_status st = energy_into(c, nullptr, c->e_scratch, &signs);
-  if (st != SI_OK) return st;
-  return best_update_from(c, c->e_scratch, signs);
+  return best_update_into(c, c->e_scratch);
 }
 
 si_status spring_ising_get_best(si_ctx *c, double *best_e, int8_t *best_s) {
@@ -2113,10 +2123,12 @@ si_status spring_ising_get_best(si_ctx *c, double *best_e, int8_t *best_s) {
     return fail(SI_ERR_STATE, "get_best: no best-state update since init or set_state");
   if ((best_e && !is_device_ptr(best_e)) || (best_s && !is_device_ptr(best_s)))
     return fail(SI_ERR_INVALID, "get_best: outputs must be device pointers");
-  if (best_e)
+  if (best_s)
+    SI_HIP(c, launch_unpack_spins(state_copy(c), c->best_s, best_s, best_e ? c->best_e : nullptr,
+                                  best_e, c->stream));
+  else if (best_e)
     SI_HIP(c, hipMemcpyAsync(best_e, c->best_e, sizeof(double) * c->out_rows(),
                              hipMemcpyDeviceToDevice, c->stream));
-  if (best_s) SI_HIP(c, launch_unpack_spins(state_copy(c), c->best_s, best_s, c->stream));
   return SI_OK;
 }
 

@@ -513,6 +513,21 @@ __global__ void best_update_kernel(const double *e, double *best_e, int32_t *val
                   best_s + (size_t)r * n_pad, n_pad);
 }
 
+// The same from the integer sums of the exact energy, which it turns into
+// energies (e) and clears for the next evaluation: one launch instead of two.
+__global__ void best_update_i8_kernel(int32_t *acc, double *e, double *best_e, int32_t *valid,
+                                      const int8_t *S8, int8_t *best_s, int n_pad) {
+  const int r = blockIdx.x;
+  const double en = (double)-(acc[r] / 2);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    acc[r] = 0;
+    e[r] = en;
+  }
+  best_update_one(en, best_e + r, valid + r, S8 + (size_t)r * n_pad, best_s + (size_t)r * n_pad,
+                  n_pad);
+}
+
 // Batch: block i * r + col updates replica col of instance i (energies and
 // records in the instances-by-replicas order of the batch outputs; spins in
 // the batch's state layout).
@@ -529,6 +544,13 @@ __global__ void best_update_batch_kernel(const double *e, double *best_e, int32_
 hipError_t launch_best_update(const double *e, double *best_e, int32_t *valid, const int8_t *S8,
                               int8_t *best_s, int32_t r, int32_t n_pad, hipStream_t s) {
   best_update_kernel<<<r, 256, 0, s>>>(e, best_e, valid, S8, best_s, n_pad);
+  return hipGetLastError();
+}
+
+hipError_t launch_best_update_i8(int32_t *acc, double *e, double *best_e, int32_t *valid,
+                                 const int8_t *S8, int8_t *best_s, int32_t r, int32_t n_pad,
+                                 hipStream_t s) {
+  best_update_i8_kernel<<<r, 256, 0, s>>>(acc, e, best_e, valid, S8, best_s, n_pad);
   return hipGetLastError();
 }
 
