@@ -118,8 +118,9 @@ typedef struct {
   int32_t precision;  /* si_precision */
   int32_t tile;       /* 0 = automatic kernel choice (the process's tile
                          cache when it holds this context's key, else the
-                         built-in preference order); otherwise a tile id
-                         reported by spring_ising_info (tuning override).
+                         built-in preference order; where the fixed-point form
+                         of FP32 or BF16X3_EXACTJ applies, that form); otherwise
+                         a tile id reported by spring_ising_info (tuning override).
                          A batch takes 0, 1 (128 x 64 work items) or 2
                          (64 x 64). */
   int32_t energy_every; /* E >= 0.  E > 0: in-run energy checks.  After every

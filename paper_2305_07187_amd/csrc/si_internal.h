@@ -82,6 +82,10 @@ hipError_t launch_step_f32_split(int32_t tile, const StepArgs &a, hipStream_t s)
 // into q_out, p_out (which may be the same buffers): where small_fits says so
 // it gives what the steps of that tile give.
 constexpr int32_t SMALL_STEPS_MAX = 4096;
+// Steps from which that is faster than a launch each: it first reads J into
+// every workgroup (us for one step, this against the tile's launch: N = 100, R
+// = 8 5.4 and 4.3, N = 224, R = 2000 12.8 and 8.1; then 1.1 and 3.7 us a step).
+inline int32_t small_steps_least(int32_t n) { return n <= 128 ? 2 : 6; }
 bool small_fits(int32_t tile, int32_t n, int32_t r_pad);
 hipError_t launch_small_steps(const StepArgs &a, int32_t steps, hipStream_t s);
 

@@ -1429,37 +1429,29 @@ static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
   a.fsplit = c->fsplit;
   if (split_workspace(c->tile, c->n_pad, c->r_pad, a.ksplit) > c->fsplit_cap)
     return fail(SI_ERR_STATE, "step: split-contraction workspace missing");
-  if (a.ksplit <= 1 && small_fits(c->tile, c->n, c->r_pad)) {
-    // all steps up to the next energy check in one launch
-    a.mask_out = nullptr;
-    for (int32_t left = n_steps; left > 0;) {
-      int32_t len = std::min(left, SMALL_STEPS_MAX);
+  a.mask_out = nullptr;
+  const bool small = a.ksplit <= 1 && small_fits(c->tile, c->n, c->r_pad);
+  for (int32_t left = n_steps; left > 0;) {
+    // small problems: all steps up to the next energy check in one launch
+    int32_t len = 1;
+    if (small && c->inject_countdown <= 0) {  // (the hook counts the steps' launches)
+      len = std::min(left, SMALL_STEPS_MAX);
       if (c->e_every > 0) len = std::min(len, c->e_every - c->t % c->e_every);
-      if (c->inject_countdown > 0) len = 1;  // (the hook counts the steps' launches)
-      const int32_t to = c->cur ^ (len & 1);
-      a.q_in = c->q[c->cur];
-      a.p_in = c->p[c->cur];
-      a.q_out = c->q[to];
-      a.p_out = c->p[to];
-      a.t = c->t;
-      SI_HIP(c, launch_small_steps(a, len, c->stream));
-      c->cur = to;
-      c->t += len;
-      left -= len;
-      SI_ENERGY_CHECK(c);
+      if (len < small_steps_least(c->n)) len = 1;
     }
-    return SI_OK;
-  }
-  for (int32_t s = 0; s < n_steps; ++s) {
+    const int32_t to = c->cur ^ (len & 1);
     a.q_in = c->q[c->cur];
     a.p_in = c->p[c->cur];
-    a.q_out = c->q[c->cur ^ 1];
-    a.p_out = c->p[c->cur ^ 1];
+    a.q_out = c->q[to];
+    a.p_out = c->p[to];
     a.t = c->t;
-    a.mask_out = nullptr;
-    SI_HIP(c, launch_step_f32(c->tile, a, c->stream));
-    c->cur ^= 1;
-    c->t += 1;
+    if (len > 1)
+      SI_HIP(c, launch_small_steps(a, len, c->stream));
+    else
+      SI_HIP(c, launch_step_f32(c->tile, a, c->stream));
+    c->cur = to;
+    c->t += len;
+    left -= len;
     SI_ENERGY_CHECK(c);
   }
   return SI_OK;

@@ -72,3 +72,26 @@ def test_checks_graph_and_oracle():
     assert rel_err(xa.cpu().numpy(), ref["Q"]) <= 1e-5 and rel_err(pa.cpu().numpy(), ref["P"]) <= 1e-5
     for m in (a, b, c):
         m.close()
+
+
+@pytest.mark.parametrize("n", [128, 129])
+def test_short_runs_take_the_tile(n):
+    # below the least number of steps a run is launched step by step: any way
+    # of cutting a run gives the same states
+    import torch
+    si = ensure_built()
+    r, S = 20, 40
+    announce(f"small problem, short runs N={n}")
+    J, x0 = to_dev(instances.make_gauss(n, 4)), to_dev(instances.make_x0(n, r, 4))
+    out = []
+    for cuts in ([14], [1] * 14, [2, 5, 1, 6], [7, 7], [3, 11]):
+        m = si.SpringIsing(J, x0, total_steps=S, energy_every=4 if len(cuts) == 2 else 0)
+        for k in cuts:
+            m.run(k)
+        x, p, t = m.state()
+        torch.cuda.synchronize()
+        assert t == 14
+        out.append((x.cpu().numpy(), p.cpu().numpy()))
+        m.close()
+    for x, p in out[1:]:
+        assert np.array_equal(x, out[0][0]) and np.array_equal(p, out[0][1])
