@@ -75,7 +75,10 @@ typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
  *                 position to 2^-31 of its replica's largest, sums exact,
  *                 the result rounded to FP32.  Other couplings up to N =
  *                 32000 likewise, each to 2^-31 of its row's largest, where
- *                 every row is dense and without outliers.
+ *                 every row is dense and without outliers.  A replica whose
+ *                 positions are mostly far below its largest (fewer than half
+ *                 of its groups of four hold one of a sixteenth of it) or not
+ *                 all finite takes the FP32 product in that step.
  *   BF16X_FP8J  : J stored as FP8 e4m3 (must be exact, e.g. +-1), positions
  *                 as a BF16 copy of the FP32 master state.
  *   BF16X_BF16J : J stored as BF16 (must be exact), positions BF16.

@@ -116,13 +116,19 @@ constexpr int I8_BM = 256, I8_BM_REAL = 128, I8_BM_FEW = 32;  // rows of a tile
 constexpr int I8_N_REAL = 32000;   // 4 N 128^2 < 2^31
 constexpr float I8_CREST = 32.f;   // largest over rms of a row of real couplings, at most
 constexpr int I8_SPECIAL = 1 << 20;  // scale exponent of a replica with non-finite positions
+constexpr int I8_ZERO = 512;         // ... of one whose positions are all zero
+constexpr float I8_LARGE = 134217728.f;  // 2^27: a sixteenth to an eighth of the largest position
+struct I8Peak {  // of one replica's positions in the rows of one tile
+  float mx;      // largest |q| after the next step
+  int large;     // groups of four that hold one reaching I8_LARGE
+};
 struct I8Args {
   const uint8_t *Jt;   // digits of J in 1 KB blocks
   const int *jexp;     // scale exponent per row of real couplings; null: integers
   const float *J;      // FP32 J [ld][ld]
   uint8_t *Qt[2];      // digits of the positions in 1 KB blocks
   int *kexp[2];        // scale exponent per replica: digits are of rint(q 2^kexp)
-  float *mx[2];        // [ld/bm][r_pad]: largest |q| after the next step, per row tile
+  I8Peak *peak[2];     // [ld/bm][r_pad], per row tile
   float *q[2], *p[2];  // [r_pad][ld]
   const float *dt, *zeta, *h;
   int32_t cur, t, total_steps, ld, n, r_pad;

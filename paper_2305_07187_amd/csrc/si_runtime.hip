@@ -460,10 +460,12 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 
 // The FP32 step runs on the int8 matrix cores (si_step_i8.hip) where its
 // result is at least as exact as the FP32 matrix cores': integer couplings
-// of a complete graph.  There every row's sum holds the replica's largest
-// positions, whose products the FP32 sum rounds to 24 bits, while the fixed
-// point keeps every position to 2^-31 of the largest.  With couplings left
-// out a row may hold small positions only, and its FP32 sum would be finer.
+// of a complete graph.  There every row's sum holds large positions of the
+// replica, whose products the FP32 sum rounds to 24 bits, while the fixed
+// point keeps every position to 2^-31 of the largest (replicas in which few
+// positions are large are left to FP32 products step by step).  With
+// couplings left out a row may hold small positions only, whatever the
+// replica, and its FP32 sum would be finer.
 // (Error against 64 bits after 20 steps at N = 2000, R = 1024: 5e-8 against
 // 4.6e-7; N = 512 .. 4000, R = 256 .. 2048, positions scaled by 1 .. 1e-30:
 // 3e-8 .. 6e-8 against 1.3e-7 .. 6.6e-7.)  Two paired digits of the sums must
@@ -532,7 +534,7 @@ static hipError_t i8_init(si_ctx *c) {
   const int32_t bm = real ? I8_BM_REAL : i8_few(c) ? I8_BM_FEW : I8_BM;
   const int64_t jb = (int64_t)c->n_pad * c->n_pad * (real ? I8_JDIGITS : 1);
   const int64_t nr = (int64_t)c->n_pad * c->r_pad;
-  const int64_t mxb = round_up((int64_t)(c->n_pad / bm) * c->r_pad * 4, 256);
+  const int64_t mxb = round_up((int64_t)(c->n_pad / bm) * c->r_pad * (int64_t)sizeof(I8Peak), 256);
   const int64_t kb = round_up((int64_t)c->r_pad * 4, 256);
   int32_t *jexp = nullptr;
   uint8_t *buf = nullptr;
@@ -561,7 +563,7 @@ static hipError_t i8_init(si_ctx *c) {
   for (int b = 0; b < 2; ++b) {
     a.Qt[b] = at;
     at += nr * I8_DIGITS;
-    a.mx[b] = reinterpret_cast<float *>(at);
+    a.peak[b] = reinterpret_cast<I8Peak *>(at);
     at += mxb;
     a.kexp[b] = reinterpret_cast<int *>(at);
     at += kb;

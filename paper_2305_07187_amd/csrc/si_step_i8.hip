@@ -9,11 +9,26 @@
 // digits exactly in 32 bits, then one FP32 conversion of each half and one
 // fused multiply-add.  Positions within a factor of 64 of the replica's
 // largest enter without any error, smaller ones with at most 2^-31 of the
-// largest (a complete graph couples every other row to that largest one, and
-// in its own row -k q_i dwarfs the error); the FP32 matrix cores round every
-// partial sum to 24 bits instead.  Against 64 bits, final positions after 20
-// steps: 5.3e-8 (FP32 4.6e-7) at N = 2000, R = 1024.  The sum does not depend
-// on its order, so neither the tile nor a split changes a result.
+// largest; the FP32 matrix cores round every partial sum to 24 bits instead.
+// Against 64 bits, final positions after 20 steps: 5.3e-8 (FP32 4.6e-7) at N =
+// 2000, R = 1024.  The sum does not depend on its order, so neither the tile
+// nor a split changes a result.
+//
+// Uneven replicas.  2^-31 of the largest is less than what FP32 sums lose as
+// long as every row sums products of large positions.  Where a few positions
+// tower over the rest, a row that does not contain them (their own; in real
+// couplings also one whose couplings to them vanish) is a sum of small
+// positions only, which FP32 forms to 24 bits of its own size.  So a replica
+// takes the fixed point in a step only if at least half of its groups of four
+// neighbouring positions hold one that reaches a sixteenth of its scale
+// (I8_LARGE; of random positions and positions between the walls 58 % and more
+// do, so that 97 % of the groups count); the step that forms positions counts
+// their groups.  The others' products are formed on the FP32 matrix cores by
+// the same launch (i8_uneven): one position of 1.4 among ones of 1e-6, k = 0, N
+// = 1000, R = 704, largest relative error of a momentum 4e-5 (15 in fixed
+// point, 3e-4 on the FP32 tiles).  N = 2000, R = 1024 with every replica uneven
+// 122 us a step (111 with real couplings; the FP32 tiles 74), with none 22.4
+// (22.0 without the counts); the 32 x 16 tiles 11.6 (11.4) at N = 600, R = 1024.
 //
 // Measured (MI355X, us per step, FP32 matrix cores before): N = 2000, R = 1024
 // 22.3 (73.6), R = 2048 42 (141), N = 4000, R = 2048 128 (532), N = 8000,
@@ -37,14 +52,16 @@
 // so the largest |q_{n+1}| of a replica has to be known before: in the paper
 // order q_{n+1} = clamp(q_n + (Delta_n/m) p_n) depends on the state n alone,
 // and the previous step, which produced that state, leaves the maximum per
-// row tile and replica in mx.  After set_state, set_schedule or steps by
+// row tile and replica in peak.  After set_state, set_schedule or steps by
 // other kernels a preparation kernel derives digits, scales and maxima from
 // the FP32 state.  Every entry q_{n+1} lies within the walls, so only
 // positions given by the caller can be non-finite: their replicas carry
-// I8_SPECIAL and the step sums their FP32 products directly.
+// I8_SPECIAL and are stepped as uneven ones.
 #include <algorithm>
+#include <type_traits>
 
 #include "si_epilogue.h"
+#include "si_f32_gemm.h"
 #include "si_grid_barrier.h"
 #include "si_internal.h"
 
@@ -75,10 +92,10 @@ __device__ __forceinline__ size_t i8_qblk(int kb, int cb, int ncb) {
 }
 
 // Exponent k of a replica whose largest |q| is m: |rint(q 2^k)| fits four
-// balanced digits (at most 0x7F7F7F7F).
+// balanced digits (at most 0x7F7F7F7F).  I8_ZERO where every position is zero.
 __device__ __forceinline__ int i8_exponent(float m) {
   if (!(m <= 3.402823466e38f)) return I8_SPECIAL;
-  if (m == 0.f) return 0;
+  if (m == 0.f) return I8_ZERO;
   int e;
   (void)frexpf(m, &e);
   int k = 31 - e;
@@ -86,10 +103,24 @@ __device__ __forceinline__ int i8_exponent(float m) {
   return k;
 }
 
-// The four digits of q as the bytes of one word, lowest digit first.
-__device__ __forceinline__ uint32_t i8_digits(float q, int k) {
-  const float v = fminf(fmaxf(rintf(ldexpf(q, k)), -2139062016.f), 2139062016.f);
+// q in fixed point, and its four digits as the bytes of one word, lowest
+// digit first.
+__device__ __forceinline__ float i8_fixed(float q, int k) {
+  return fminf(fmaxf(rintf(ldexpf(q, k)), -2139062016.f), 2139062016.f);
+}
+__device__ __forceinline__ uint32_t i8_digits(float v) {
   return ((uint32_t)(int)v + 0x80808080u) ^ 0x80808080u;
+}
+
+// Whether one of four positions in fixed point reaches I8_LARGE.
+__device__ __forceinline__ bool i8_is_large(const float (&v)[4]) {
+  return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))) >= I8_LARGE;
+}
+
+// Whether a replica's product is formed in FP32: scale k, and the number of
+// groups of four positions that i8_is_large holds for.
+__device__ __forceinline__ bool i8_is_uneven(int k, int large, int n) {
+  return k == I8_SPECIAL || (k != I8_ZERO && 2 * large < (n + 3) / 4);
 }
 
 // Bytes of four words regrouped by digit: out[d] = digit d of the four.
@@ -182,6 +213,7 @@ template <class C>
 struct I8Smem {
   __attribute__((aligned(16))) uint8_t ring[C::STAGES * C::SLOT];
   __attribute__((aligned(16))) float tile[C::BN * C::LDT];
+  int uneven, odd[C::BN];  // some column of this workgroup's tiles; the columns of one tile
 };
 
 // Tile i of this workgroup.  Every XCD (workgroup b runs on XCD b % 8) takes
@@ -242,6 +274,8 @@ __device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk<I8Int> &
   for (int i = 0; i < PD; ++i) load_a(cur, i, fa[i]);
   int rd = 0;
   const uint8_t *st = sm.ring + lane * 16;
+  if (threadIdx.x == 0) sm.uneven = 0;
+  q_wait_lds();
   q_barrier();  // the first slab has landed
   read_b(st, 0, 0);
   for (int tile = 0; tile < walk.count; ++tile) {
@@ -347,6 +381,8 @@ __device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk<I8Real> 
   for (int i = 0; i < PD; ++i) load_a(cur, i, fa[i]);
   int rd = 0;
   const uint8_t *st = sm.ring + lane * 16;
+  if (threadIdx.x == 0) sm.uneven = 0;
+  q_wait_lds();
   q_barrier();  // the first slab has landed
   read_b(st, 0, 0);
   read_b(st, 0, 1);
@@ -418,16 +454,83 @@ __device__ __forceinline__ void i8_matrix(const I8Args &a, const I8Walk<I8Real> 
   }
 }
 
-// F of a replica with non-finite positions (given by the caller): FP32
-// products of rows row .. row + 3, summed.
-__device__ __forceinline__ floatx4 i8_special(const I8Args &a, int row, int col) {
-  floatx4 f = {0.f, 0.f, 0.f, 0.f};
-  for (int i = 0; i < a.n; ++i) {
-    const float qi = a.q[a.cur][(size_t)col * a.ld + i];
+// p' and the next step's maxima of the uneven replicas in this workgroup's
+// tiles, again, from products on the FP32 matrix cores (all waves; q', its
+// digits and counts need no product and stand).  128 rows at a time, with the
+// main loops of the FP32 tiles in the ring's LDS.
+template <class C, int WALL>
+__device__ __forceinline__ void i8_uneven(const I8Args &a, const I8Walk<C> &walk, I8Smem<C> &sm) {
+  using F = std::conditional_t<C::REAL, F32Cfg<128, 64, 4, 2, 32, 32, 4, 1>,
+                               F32Cfg<128, 32, 8, 1, 16, 64, 0, 1>>;
+  static_assert(F::NT == C::NT && F::BN == C::BN && C::BM % F::BM == 0 &&
+                F::LDS_FLOATS * 4 <= (int)sizeof sm.ring, "FP32 product");
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nx = a.cur ^ 1, ntr = a.ld / C::BM;
+  const int wy = wave / F::WN, wx = wave % F::WN;
+  const int row = threadIdx.x % C::LPC * 4;
+  const float dt = a.dt[a.t], zeta = a.zeta[a.t];
+  const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
+  for (int i = 0; i < walk.count; ++i) {
+    int m0, n0;
+    walk.at(i, m0, n0);
+    __syncthreads();  // (the tile before this one has been read)
+    if (threadIdx.x == 0) sm.uneven = 0;
+    __syncthreads();
+    if (threadIdx.x < C::BN) {
+      const int col = n0 + threadIdx.x;
+      int large = 0;
+      for (int rt = 0; rt < ntr; ++rt) large += a.peak[a.cur][(size_t)rt * a.r_pad + col].large;
+      const bool odd = i8_is_uneven(a.kexp[a.cur][col], large, a.n);
+      sm.odd[threadIdx.x] = odd;
+      if (odd) sm.uneven = 1;
+    }
+    __syncthreads();
+    if (!sm.uneven) continue;
+    for (int mh = 0; mh < C::BM; mh += F::BM) {
+      typename F::acc_t acc[F::TM][F::TN];
+      const int K = (a.n + F::BK - 1) / F::BK * F::BK;
+      float *ring = reinterpret_cast<float *>(sm.ring);
+      if constexpr (F::STAGES > 0)
+        f32_mainloop_dma<F>(a.J, a.q[a.cur], a.ld, K, m0 + mh, n0, acc, ring);
+      else
+        f32_mainloop<F, B_PLAIN>(a.J, a.q[a.cur], a.ld, K, m0 + mh, n0, acc, ring);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) f[v] = fmaf(a.J[(size_t)(row + v) * a.ld + i], qi, f[v]);
+      for (int i = 0; i < F::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < F::TN; ++j)
+#pragma unroll
+          for (int g = 0; g < F::M::NACC / 4; ++g)
+            epi_put(sm.tile, C::LDT,
+                    mh + wy * F::WTM + i * F::MB + g * 8 + (lane / F::MB) * 4,
+                    wx * F::WTN + j * F::MB + lane % F::MB, acc[i][j][4 * g],
+                    acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+    }
+    __syncthreads();
+    floatx4 h4 = {0.f, 0.f, 0.f, 0.f};
+    if (a.h) h4 = *reinterpret_cast<const floatx4 *>(a.h + m0 + row);
+    for (int col = threadIdx.x / C::LPC; col < C::BN; col += C::NT / C::LPC) {
+      if (!sm.odd[col]) continue;
+      const size_t off = (size_t)(n0 + col) * a.ld + m0 + row;
+      const floatx4 q4 = *reinterpret_cast<const floatx4 *>(a.q[a.cur] + off);
+      const floatx4 p4 = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
+      const floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
+      floatx4 pn;
+      float mx = 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float qv, pv;
+        // (an infinite position times the rows' zero padding is not a number)
+        const float fv = m0 + row + v < a.n ? f[v] : 0.f;
+        spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], fv + h4[v], dt, zeta, a.k, a.inv_m,
+                                            a.qmax, a.pmax, qv, pv);
+        pn[v] = pv;
+        mx = fmaxf(mx, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
+      }
+      *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+#pragma unroll
+      for (int o = 1; o < C::LPC; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+      if (row == 0) a.peak[nx][(size_t)(m0 / C::BM) * a.r_pad + n0 + col].mx = mx;
+    }
   }
-  return f;
 }
 
 // The state waves' part of one step: wave sw owns COLS columns of a tile, a
@@ -498,7 +601,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
   const float cdt = dt * a.inv_m;
   const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
   floatx4 q4[C::PERL], p4[C::PERL], h4;
-  int kin = 0;
+  int many = 0;  // groups of large new positions of column lc + lane % LPC
   // p' of tile (m, n) from F in LDS, and the next step's maxima
   auto finish = [&](int m, int n) {
 #pragma unroll
@@ -508,10 +611,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
       for (int c = 0; c < 4; ++c) {
         const int cc = set * 4 + c, col = sw * C::COLS + lc + cc;
         const size_t off = (size_t)(n + col) * a.ld + m + row;
-        floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
-        if (of(kin, cc) == I8_SPECIAL) {
-          f = i8_special(a, m + row, n + col);
-        }
+        const floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
         float mx = 0.f;
         floatx4 pn;
 #pragma unroll
@@ -530,8 +630,9 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
                        fmaxf(__uint_as_float(um[2]), __uint_as_float(um[3])));
 #pragma unroll
       for (int off = 4; off < C::LPC; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      if (lane % C::LPC < 4)
-        a.mx[nx][(size_t)(m / C::BM) * a.r_pad + n + sw * C::COLS + lc + set * 4 + (lane & 3)] = mx;
+      if (lane % C::LPC / 4 == set)
+        a.peak[nx][(size_t)(m / C::BM) * a.r_pad + n + sw * C::COLS + lc + lane % C::LPC] =
+            I8Peak{mx, many};
       tick();
     }
   };
@@ -540,13 +641,18 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
     if (tile > 0) finish(m0, n0);
     walk.at(tile, m0, n0);
     const int col0 = n0 + sw * C::COLS;
-    // scales of the new positions: maxima of this wave's columns, one column
-    // and every (64 / COLS)th row tile per lane
+    // scales of the new positions (maxima of this wave's columns) and counts
+    // of the current ones' large entries: one column and every (64 / COLS)th
+    // row tile per lane
     float mx = 0.f;
+    int large = 0;
     const int mine = col0 + lane % C::COLS;
-    for (int rt = lane / C::COLS; rt < ntr; rt += 64 / C::COLS)
-      mx = fmaxf(mx, a.mx[a.cur][(size_t)rt * a.r_pad + mine]);
-    kin = a.kexp[a.cur][mine];
+    for (int rt = lane / C::COLS; rt < ntr; rt += 64 / C::COLS) {
+      const I8Peak pk = a.peak[a.cur][(size_t)rt * a.r_pad + mine];
+      mx = fmaxf(mx, pk.mx);
+      large += pk.large;
+    }
+    const int kin = a.kexp[a.cur][mine];
     h4 = floatx4{0.f, 0.f, 0.f, 0.f};
     if (a.h) h4 = *reinterpret_cast<const floatx4 *>(a.h + m0 + row);
 #pragma unroll
@@ -556,7 +662,11 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
       p4[c] = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
     }
 #pragma unroll
-    for (int off = C::COLS; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    for (int off = C::COLS; off < 64; off <<= 1) {
+      mx = fmaxf(mx, __shfl_xor(mx, off));
+      large += __shfl_xor(large, off);
+    }
+    if (i8_is_uneven(kin, large, a.n)) sm.uneven = 1;
     const int kout = i8_exponent(mx);
     if (m0 == 0 && lane < C::COLS) a.kexp[nx][col0 + lane] = kout;
     tick();
@@ -569,12 +679,17 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
         const int cc = set * 4 + c, k = of(kout, cc);
         uint32_t dg[4], by[4];
         floatx4 qn;
+        float fx[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const float u = fmaf(cdt, p4[cc][v], q4[cc][v]);
           qn[v] = fminf(fmaxf(u, -a.qmax), a.qmax);
-          dg[v] = i8_digits(qn[v], k);
+          fx[v] = i8_fixed(qn[v], k);
+          dg[v] = i8_digits(fx[v]);
         }
+        const uint64_t big = __ballot(i8_is_large(fx));
+        if (lane % C::LPC == cc)
+          many = C::LPC == 64 ? __popcll(big) : __popc((uint32_t)(lane < 32 ? big : big >> 32));
         *reinterpret_cast<floatx4 *>(a.q[nx] + (size_t)(col0 + lc + cc) * a.ld + m0 + row) = qn;
         byte_transpose(dg, by);
 #pragma unroll
@@ -599,15 +714,23 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
   finish(m0, n0);
 }
 
+// One step of this workgroup's tiles.
+template <class C, int WALL>
+__device__ __forceinline__ void i8_step(const I8Args &a, const I8Walk<C> &walk, I8Smem<C> &sm) {
+  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < C::NM)
+    i8_matrix(a, walk, sm);
+  else
+    i8_state<C, WALL>(a, walk, sm);
+  __syncthreads();
+  if (__builtin_expect(sm.uneven, 0)) i8_uneven<C, WALL>(a, walk, sm);
+}
+
 template <class C, int WALL>
 __global__ __launch_bounds__(C::NT) void step_i8_kernel(I8Args a) {
   __shared__ I8Smem<C> sm;
   const I8Walk<C> walk(a);
   if (walk.count == 0) return;
-  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < C::NM)
-    i8_matrix(a, walk, sm);
-  else
-    i8_state<C, WALL>(a, walk, sm);
+  i8_step<C, WALL>(a, walk, sm);
 }
 
 // Resident form: one cooperative launch runs n_steps steps with a grid-wide
@@ -618,10 +741,7 @@ __global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentAr
   const I8Walk<C> walk(a);
   if (walk.count == 0) return;
   for (int s = 0; s < r.n_steps; ++s) {
-    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < C::NM)
-      i8_matrix(a, walk, sm);
-    else
-      i8_state<C, WALL>(a, walk, sm);
+    i8_step<C, WALL>(a, walk, sm);
     a.cur ^= 1;
     a.t += 1;
     if (s + 1 < r.n_steps && !grid_barrier(r.count, (uint32_t)(s + 1), r.err)) return;
@@ -647,13 +767,48 @@ __global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentAr
 // ---------------------------------------------------------------------------
 constexpr int FEW_PD = 2, FEW_BN = 16;
 
+// FP32 products of 16 RB rows and 16 CB columns over the contraction indices
+// k0 .. k1 (multiples of 64), operands straight from memory: rows (columns) of
+// 64 lanes' four consecutive indices each, as the 16 x 16 x 4 products take
+// them.  J, Q: this lane's row and column, l % 16, from index 4 (l / 16) on.
+template <int RB, int CB>
+__device__ __forceinline__ void i8_f32_product(const float *__restrict__ J,
+                                               const float *__restrict__ Q, int ld, int k0, int k1,
+                                               floatx4 (&acc)[RB][CB]) {
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int k = k0; k < k1; k += 32) {
+    floatx4 a[2][RB], b[2][CB];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+        a[u][i] = *reinterpret_cast<const floatx4 *>(J + (size_t)i * 16 * ld + k + u * 16);
+#pragma unroll
+      for (int j = 0; j < CB; ++j)
+        b[u][j] = *reinterpret_cast<const floatx4 *>(Q + (size_t)j * 16 * ld + k + u * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int j = 0; j < CB; ++j)
+            acc[i][j] = MfmaF32<16>::mma(a[u][i][v], b[u][j][v], acc[i][j]);
+  }
+}
+
 template <int FEW_W, int WALL>
 __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
   constexpr int BM = I8_BM_FEW, BN = FEW_BN;
   __shared__ __attribute__((aligned(16))) int sums[FEW_W][2][BN][BM + 4];
   __shared__ __attribute__((aligned(16))) uint8_t dig[QP][BN][BM];
   __shared__ float colmax[BN];
-  __shared__ int kshared[2][BN];
+  __shared__ int kshared[2][BN], collarge[BN], uneven;
   const int tid = threadIdx.x, lane = tid & 63, nx = a.cur ^ 1;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntc = a.r_pad / BN, ntr = a.ld / BM, t = xcd_tile(blockIdx.x, gridDim.x);
@@ -694,14 +849,22 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
   }
   // scales: the largest |q'| of every column of the tile (bits of floats >= 0
   // order as integers)
+  const int kin = a.kexp[a.cur][n0 + (tid & 15)];
   float mx = 0.f;
-  for (int rt = tid >> 4; rt < ntr; rt += 4 * FEW_W)
-    mx = fmaxf(mx, a.mx[a.cur][(size_t)rt * a.r_pad + n0 + (tid & 15)]);
-  if (tid < BN) colmax[tid] = 0.f;
+  int large = 0;
+  for (int rt = tid >> 4; rt < ntr; rt += 4 * FEW_W) {
+    const I8Peak pk = a.peak[a.cur][(size_t)rt * a.r_pad + n0 + (tid & 15)];
+    mx = fmaxf(mx, pk.mx);
+    large += pk.large;
+  }
+  if (tid < BN) {
+    colmax[tid] = 0.f;
+    collarge[tid] = 0;
+  }
+  if (tid == 0) uneven = 0;
   __syncthreads();
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
-  if (lane < BN) atomicMax(reinterpret_cast<int *>(colmax) + lane, __float_as_int(mx));
+  atomicMax(reinterpret_cast<int *>(colmax) + (tid & 15), __float_as_int(mx));
+  atomicAdd(collarge + (tid & 15), large);
 
   intx4 acc[2][QP];
 #pragma unroll
@@ -740,28 +903,56 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
   __syncthreads();
   if (tid < BN) {
     const int kout = i8_exponent(colmax[tid]);
-    kshared[0][tid] = a.kexp[a.cur][n0 + tid];
+    const bool odd = i8_is_uneven(kin, collarge[tid], a.n);
+    if (odd) uneven = 1;
+    kshared[0][tid] = odd ? I8_SPECIAL : kin;
     kshared[1][tid] = kout;
     if (m0 == 0) a.kexp[nx][n0 + tid] = kout;
   }
   __syncthreads();
+  floatx4 f = {0.f, 0.f, 0.f, 0.f};
   if (owner) {
-    const float dt = a.dt[a.t], zeta = a.zeta[a.t];
-    const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
-    const int kin = kshared[0][scol], kout = kshared[1][scol];
     intx4 hi = {0, 0, 0, 0}, lo = {0, 0, 0, 0};
 #pragma unroll
     for (int w = 0; w < FEW_W; ++w) {
       hi += *reinterpret_cast<const intx4 *>(&sums[w][0][scol][srow]);
       lo += *reinterpret_cast<const intx4 *>(&sums[w][1][scol][srow]);
     }
-    floatx4 f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) f[v] = ldexpf(fmaf((float)hi[v], 65536.f, (float)lo[v]), -kin);
-    if (kin == I8_SPECIAL) f = i8_special(a, m0 + srow, n0 + scol);
+    for (int v = 0; v < 4; ++v)
+      f[v] = ldexpf(fmaf((float)hi[v], 65536.f, (float)lo[v]), -kshared[0][scol]);
+  }
+  if (__builtin_expect(uneven, 0)) {
+    // the uneven columns' products on the FP32 matrix cores, a range of the
+    // contraction per wave, added in the order of the ranges
+    const int K = (a.n + 63) / 64 * 64, klen = (K / 64 + FEW_W - 1) / FEW_W * 64;
+    floatx4 part[2][1];
+    i8_f32_product(a.J + (size_t)(m0 + lrow) * a.ld + (lane >> 4) * 4,
+                   a.q[a.cur] + (size_t)(n0 + lrow) * a.ld + (lane >> 4) * 4, a.ld, wave * klen,
+                   min(K, (wave + 1) * klen), part);
+    __syncthreads();  // the digits' sums have been read
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      *reinterpret_cast<floatx4 *>(&sums[wave][0][lrow][r * 16 + (lane >> 4) * 4]) = part[r][0];
+    __syncthreads();
+    if (owner && kshared[0][scol] == I8_SPECIAL) {
+      f = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < FEW_W; ++w)
+        f += *reinterpret_cast<const floatx4 *>(&sums[w][0][scol][srow]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)  // (infinite positions times the rows' zero padding)
+        if (m0 + srow + v >= a.n) f[v] = 0.f;
+    }
+  }
+  if (owner) {
+    const float dt = a.dt[a.t], zeta = a.zeta[a.t];
+    const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
+    const int kout = kshared[1][scol];
     float mnext = 0.f;
     floatx4 qn, pn;
     uint32_t dg[4], by[4];
+    float fx[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       float qv, pv;
@@ -770,16 +961,20 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
       qn[v] = fminf(fmaxf(fmaf(dt * a.inv_m, p4[v], q4[v]), -a.qmax), a.qmax);
       pn[v] = pv;
       mnext = fmaxf(mnext, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
-      dg[v] = i8_digits(qn[v], kout);
+      fx[v] = i8_fixed(qn[v], kout);
+      dg[v] = i8_digits(fx[v]);
     }
     *reinterpret_cast<floatx4 *>(a.q[nx] + off) = qn;
     *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
     byte_transpose(dg, by);
 #pragma unroll
     for (int d = 0; d < QP; ++d) *reinterpret_cast<uint32_t *>(&dig[d][scol][srow]) = by[d];
+    // (the eight lanes of a column)
+    const int many = __popc((uint32_t)(__ballot(i8_is_large(fx)) >> (lane & 56)) & 255u);
 #pragma unroll
     for (int o = 1; o < 8; o <<= 1) mnext = fmaxf(mnext, __shfl_xor(mnext, o));
-    if ((tid & 7) == 0) a.mx[nx][(size_t)(m0 / BM) * a.r_pad + n0 + scol] = mnext;
+    if ((tid & 7) == 0)
+      a.peak[nx][(size_t)(m0 / BM) * a.r_pad + n0 + scol] = I8Peak{mnext, many};
   }
   __syncthreads();
   for (int u = tid; u < QP * 2 * BN; u += 64 * FEW_W) {  // 16 spins of one column and digit
@@ -790,13 +985,13 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
   }
 }
 
-// Digits, scales and maxima of the FP32 state (t: the next step's index).
+// Digits, scales, counts and maxima of the FP32 state (t: the next step's index).
 // One workgroup per four replicas (256 of them at R = 1024: one per CU, 11.6
 // us with half as many of eight, 7.0 now), two waves per replica for the maxima.
 constexpr int PREP_R = 4;
 __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
   __shared__ float most[2][8];
-  __shared__ int isnan[8], kx[PREP_R];
+  __shared__ int isnan[8], kx[PREP_R], count[PREP_R];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r0 = blockIdx.x * PREP_R, rw = wave / 2;
   const float *q = a.q[a.cur], *p = a.p[a.cur];
@@ -832,23 +1027,31 @@ __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
     const int w = threadIdx.x * 2;
     const int k = isnan[w] || isnan[w + 1] ? I8_SPECIAL : i8_exponent(fmaxf(most[0][w], most[0][w + 1]));
     kx[threadIdx.x] = k;
+    count[threadIdx.x] = 0;
     a.kexp[a.cur][r0 + threadIdx.x] = k;
   }
   for (int u = threadIdx.x; u < a.ld / a.bm * PREP_R; u += 512) {
     const int rt = u / PREP_R, j = u % PREP_R;
-    a.mx[a.cur][(size_t)rt * a.r_pad + r0 + j] =
-        rt == 0 ? fmaxf(most[1][2 * j], most[1][2 * j + 1]) : 0.f;
+    I8Peak *pk = a.peak[a.cur] + (size_t)rt * a.r_pad + r0 + j;
+    pk->mx = rt == 0 ? fmaxf(most[1][2 * j], most[1][2 * j + 1]) : 0.f;
+    if (rt > 0) pk->large = 0;  // (all counted in the first row tile's entry, below)
   }
   __syncthreads();
   const int j = threadIdx.x % PREP_R, r = r0 + j, k = kx[j], ncb = a.r_pad / 32;
+  int large = 0;
   for (int pc = threadIdx.x / PREP_R; pc < a.ld / 16; pc += 512 / PREP_R) {
     uint32_t w[QP][4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const floatx4 q4 = *reinterpret_cast<const floatx4 *>(q + (size_t)r * a.ld + pc * 16 + g * 4);
       uint32_t dg[4], by[4];
+      float fx[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dg[v] = k == I8_SPECIAL ? 0u : i8_digits(q4[v], k);
+      for (int v = 0; v < 4; ++v) {
+        fx[v] = k == I8_SPECIAL ? 0.f : i8_fixed(q4[v], k);
+        dg[v] = i8_digits(fx[v]);
+      }
+      large += i8_is_large(fx);
       byte_transpose(dg, by);
 #pragma unroll
       for (int d = 0; d < QP; ++d) w[d][g] = by[d];
@@ -859,6 +1062,9 @@ __global__ __launch_bounds__(512) void i8_prepare_kernel(I8Args a) {
     for (int d = 0; d < QP; ++d)
       *reinterpret_cast<uintx4 *>(out + d * BLK) = uintx4{w[d][0], w[d][1], w[d][2], w[d][3]};
   }
+  atomicAdd(count + j, large);
+  __syncthreads();
+  if (threadIdx.x < PREP_R) a.peak[a.cur][r0 + threadIdx.x].large = count[threadIdx.x];
 }
 
 // Couplings into blocks of digits: one wave per block, 16 couplings per lane.
@@ -882,7 +1088,7 @@ __global__ __launch_bounds__(256) void i8_pack_j_kernel(const float *__restrict_
       } else {
         uint32_t dg[4], by[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) dg[v] = i8_digits(x[v], k);
+        for (int v = 0; v < 4; ++v) dg[v] = i8_digits(i8_fixed(x[v], k));
         byte_transpose(dg, by);
 #pragma unroll
         for (int d = 0; d < JD; ++d) w[d][g] = by[d];
@@ -974,7 +1180,7 @@ int32_t i8_xcd_rows(const I8Args &a) {
   return best;
 }
 
-static const void *i8_step(const I8Args &a) {
+static const void *i8_step_entry(const I8Args &a) {
   const bool clamp = a.wall == SI_WALL_CLAMP;
   if (i8_real(a))
     return clamp ? reinterpret_cast<const void *>(&step_i8_kernel<I8Real, SI_WALL_CLAMP>)
@@ -1015,7 +1221,7 @@ hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s) {
   }
   I8Args aa = a;
   void *args[] = {&aa};
-  return hipLaunchKernel(i8_step(a), dim3(i8_grid(a, num_cus)), dim3(I8Int::NT), args, 0, s);
+  return hipLaunchKernel(i8_step_entry(a), dim3(i8_grid(a, num_cus)), dim3(I8Int::NT), args, 0, s);
 }
 
 const char *i8_kernel_name(const I8Args &a) {
