@@ -130,6 +130,7 @@ struct I8Args {
   int *kexp[2];        // scale exponent per replica: digits are of rint(q 2^kexp)
   I8Peak *peak[2];     // [ld/bm][r_pad], per row tile
   float *q[2], *p[2];  // [r_pad][ld]
+  uint8_t *mask_out;   // null, or the wall bits for the adjoint, [r_pad][ld]
   const float *dt, *zeta, *h;
   int32_t cur, t, total_steps, ld, n, r_pad;
   int32_t bm;          // rows of a tile: I8_BM, real couplings I8_BM_REAL, few replicas I8_BM_FEW

@@ -482,9 +482,7 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // = 1000, R = 128 5.6 and 6.9, N = 2000, R = 128 8.7 and 13.2, R = 1024 22.3 and
 // 73.6, N = 8000, R = 64 35.8 and 76.5, R = 2048 475 and 2076).  FP32 also keeps
 // up to 64 replicas of N <= 4096, although it is slower there (N = 2000, R =
-// 50 9.3 and 6.8): those are the sizes at which schedules are differentiated,
-// and the steps of a context and its adjoint's trajectory, which is FP32,
-// shall agree bit for bit.
+// 50 9.3 and 6.8).
 // The split form of the BF16 matrix cores (BF16X3_EXACTJ: FP32 positions in
 // three planes, FP32 sums) takes the same products, and they are faster here
 // too, with the wide tiles from N = 1000 on (int8 against BF16: N = 600, R =
@@ -1467,9 +1465,27 @@ static si_status do_steps(si_ctx *c, int32_t n_steps) {
 }
 
 // Steps t_a .. t_a + len - 1 of a segment from its first state in adj_seg
-// (state j: q at 2 j NR, p at + NR), recording every state and wall mask.
-static si_status adj_record(si_ctx *c, int32_t t_a, int32_t len) {
+// (state j: q at 2 j NR, p at + NR), recording every state and wall mask, with
+// the kernels that run() takes.  cur: the parity of the first state's digits,
+// or, with `prepare`, where the fixed-point form shall derive them from it.
+static si_status adj_record(si_ctx *c, int32_t t_a, int32_t len, int cur, bool prepare) {
   const int64_t NR = (int64_t)c->n_pad * c->r_pad;
+  if (i8_on(c)) {
+    I8Args a = i8_args(c);
+    for (int32_t j = 0; j < len; ++j) {
+      float *sq = c->adj_seg + 2 * j * NR;
+      a.cur = (cur + j) & 1;
+      a.q[a.cur] = sq;
+      a.p[a.cur] = sq + NR;
+      a.q[a.cur ^ 1] = sq + 2 * NR;
+      a.p[a.cur ^ 1] = sq + 3 * NR;
+      a.mask_out = c->adj_mask + (int64_t)j * NR;
+      a.t = t_a + j;
+      if (j == 0 && prepare) SI_HIP(c, launch_i8_prepare(a, c->stream));
+      SI_HIP(c, launch_step_i8(a, c->num_cus, c->stream));
+    }
+    return SI_OK;
+  }
   StepArgs a = step_args(c);
   for (int32_t j = 0; j < len; ++j) {
     float *sq = c->adj_seg + 2 * j * NR;
@@ -1544,20 +1560,20 @@ static si_status adj_forward(si_ctx *c, int32_t C, double *loss) {
     SI_HIP(c, hipMemcpyAsync(ck + NR, c->p[c->cur], NR * sizeof(float),
                              hipMemcpyDeviceToDevice, c->stream));
     if (!record) {
-      si_status st = do_steps_f32(c, len);  // as the backward half recomputes it
+      si_status st = do_steps(c, len);
       if (st != SI_OK) return st;
       continue;
     }
-    si_status st = adj_record(c, c->t, len);
+    si_status st = adj_record(c, c->t, len, c->cur, false);
     if (st != SI_OK) return st;
     c->t += len;
+    c->cur ^= len & 1;
     const float *end = c->adj_seg + 2 * len * NR;
     SI_HIP(c, hipMemcpyAsync(c->q[c->cur], end, NR * sizeof(float), hipMemcpyDeviceToDevice,
                              c->stream));
     SI_HIP(c, hipMemcpyAsync(c->p[c->cur], end + NR, NR * sizeof(float), hipMemcpyDeviceToDevice,
                              c->stream));
   }
-  SI_HIP(c, i8_refresh(c));
   // seed: lq_S = -(1/R) J q_S, lp_S = 0, and the loss
   SI_HIP(c, launch_adj_seed(c->J, c->q[c->cur], c->adj_lam, c->adj_lam + NR, c->adj_part,
                             c->n_pad, c->r_pad, inv_r, c->stream));
@@ -1598,7 +1614,9 @@ static si_status adj_backward(si_ctx *c, double *g_dt, double *g_zeta) {
     if (!(c->tape.recorded && sg == nseg - 1)) {
       SI_HIP(c, hipMemcpyAsync(sq, ck, 2 * NR * sizeof(float), hipMemcpyDeviceToDevice,
                                c->stream));
-      si_status st = adj_record(c, t_a, len);
+      // (overwrites the digits of the current state, the schedule's last:
+      // only set_state, which derives them anew, leads to further steps)
+      si_status st = adj_record(c, t_a, len, 0, true);
       if (st != SI_OK) return st;
     }
     for (int32_t j = len - 1; j >= 0; --j) {

@@ -160,6 +160,20 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&w)[4]) {
   }
 }
 
+// Wall bits of four positions and momenta before clamping, as the FP32 tiles
+// record them for the adjoint (bit 0: q within its walls, bit 1: p).
+__device__ __forceinline__ uint32_t i8_wall_bits(const I8Args &a, floatx4 q4, floatx4 p4, floatx4 f,
+                                                 float dt, float zeta) {
+  uint32_t mk = 0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float uu = fmaf(dt * a.inv_m, p4[v], q4[v]);
+    const float vv = fmaf(dt, fmaf(zeta, f[v], -a.k * q4[v]), p4[v]);
+    mk |= ((fabsf(uu) <= a.qmax ? 1u : 0u) | (fabsf(vv) <= a.pmax ? 2u : 0u)) << (8 * v);
+  }
+  return mk;
+}
+
 // Wait until at most N memory operations of this wave are in flight, then
 // synchronise the workgroup.  The wait goes through the builtin, which the
 // compiler's own wait insertion accounts for.
@@ -513,19 +527,21 @@ __device__ __forceinline__ void i8_uneven(const I8Args &a, const I8Walk<C> &walk
       const floatx4 q4 = *reinterpret_cast<const floatx4 *>(a.q[a.cur] + off);
       const floatx4 p4 = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
       const floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
-      floatx4 pn;
+      floatx4 pn, fh;
       float mx = 0.f;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         float qv, pv;
         // (an infinite position times the rows' zero padding is not a number)
-        const float fv = m0 + row + v < a.n ? f[v] : 0.f;
-        spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], fv + h4[v], dt, zeta, a.k, a.inv_m,
-                                            a.qmax, a.pmax, qv, pv);
+        fh[v] = (m0 + row + v < a.n ? f[v] : 0.f) + h4[v];
+        spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], fh[v], dt, zeta, a.k, a.inv_m, a.qmax,
+                                            a.pmax, qv, pv);
         pn[v] = pv;
         mx = fmaxf(mx, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
       }
       *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+      if (a.mask_out)
+        *reinterpret_cast<uint32_t *>(a.mask_out + off) = i8_wall_bits(a, q4, p4, fh, dt, zeta);
 #pragma unroll
       for (int o = 1; o < C::LPC; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
       if (row == 0) a.peak[nx][(size_t)(m0 / C::BM) * a.r_pad + n0 + col].mx = mx;
@@ -611,18 +627,22 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
       for (int c = 0; c < 4; ++c) {
         const int cc = set * 4 + c, col = sw * C::COLS + lc + cc;
         const size_t off = (size_t)(n + col) * a.ld + m + row;
-        const floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
+        floatx4 f = *reinterpret_cast<const floatx4 *>(sm.tile + col * C::LDT + row);
         float mx = 0.f;
         floatx4 pn;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           float qv, pv;
-          spring_update<SI_ORDER_PAPER, WALL>(q4[cc][v], p4[cc][v], f[v] + h4[v], dt, zeta, a.k,
-                                              a.inv_m, a.qmax, a.pmax, qv, pv);
+          f[v] += h4[v];
+          spring_update<SI_ORDER_PAPER, WALL>(q4[cc][v], p4[cc][v], f[v], dt, zeta, a.k, a.inv_m,
+                                              a.qmax, a.pmax, qv, pv);
           pn[v] = pv;
           mx = fmaxf(mx, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
         }
         *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+        if (a.mask_out)
+          *reinterpret_cast<uint32_t *>(a.mask_out + off) =
+              i8_wall_bits(a, q4[cc], p4[cc], f, dt, zeta);
         um[c] = __float_as_uint(mx);
       }
       quad_transpose(um);
@@ -956,8 +976,9 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       float qv, pv;
-      spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], f[v] + h4[v], dt, zeta, a.k, a.inv_m,
-                                          a.qmax, a.pmax, qv, pv);
+      f[v] += h4[v];
+      spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], f[v], dt, zeta, a.k, a.inv_m, a.qmax,
+                                          a.pmax, qv, pv);
       qn[v] = fminf(fmaxf(fmaf(dt * a.inv_m, p4[v], q4[v]), -a.qmax), a.qmax);
       pn[v] = pv;
       mnext = fmaxf(mnext, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
@@ -966,6 +987,8 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
     }
     *reinterpret_cast<floatx4 *>(a.q[nx] + off) = qn;
     *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+    if (a.mask_out)
+      *reinterpret_cast<uint32_t *>(a.mask_out + off) = i8_wall_bits(a, q4, p4, f, dt, zeta);
     byte_transpose(dg, by);
 #pragma unroll
     for (int d = 0; d < QP; ++d) *reinterpret_cast<uint32_t *>(&dig[d][scol][srow]) = by[d];
