@@ -479,10 +479,10 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // = 512 24.2 and 19.2, N = 8000, R = 64 35.8 and 47.2, N = 12000, R = 64 75.5
 // and 65.5).  Below, FP32 keeps the small problems (int8 against FP32: N =
 // 300, R = 256 5.2 and 4.9, N = 400, R = 64 5.0 and 4.8, R = 500 6.3 and 8.1, N
-// = 1000, R = 128 5.6 and 6.9, N = 2000, R = 128 8.7 and 13.2, R = 1024 22.3 and
-// 73.6, N = 8000, R = 64 35.8 and 76.5, R = 2048 475 and 2076).  FP32 also keeps
-// up to 64 replicas of N <= 4096, although it is slower there (N = 2000, R =
-// 50 9.3 and 6.8).
+// = 1000, R = 128 5.6 and 6.9, N = 513, R = 8 5.5 and 5.6, N = 1000, R = 64 5.9
+// and 6.5, N = 2000, R = 50 6.9 and 9.3, R = 128 8.7 and 13.2, R = 1024 22.4 and
+// 73.6, N = 4096, R = 64 12.3 and 26.2, N = 8000, R = 64 36.1 and 76.5, R = 2048
+// 475 and 2076).
 // The split form of the BF16 matrix cores (BF16X3_EXACTJ: FP32 positions in
 // three planes, FP32 sums) takes the same products, and they are faster here
 // too, with the wide tiles from N = 1000 on (int8 against BF16: N = 600, R =
@@ -505,8 +505,7 @@ static bool i8_integer(const si_ctx *c) {
 }
 
 static bool i8_few(const si_ctx *c) {
-  const bool pays = c->n > 4096 || (c->n > 512 && (c->r > 64 || c->prm.precision != SI_PREC_FP32)) ||
-                    (c->n >= 384 && c->r > 256);
+  const bool pays = c->n > 512 || (c->n >= 384 && c->r > 256);
   return i8_integer(c) && pays && (int64_t)c->n * round_up(c->r, 64) <= 700000;
 }
 
