@@ -113,6 +113,7 @@ hipError_t launch_resident_f32(int32_t tile, const StepArgs &a, const ResidentAr
 constexpr int I8_DIGITS = 4;       // base-256 digits per position
 constexpr int I8_JDIGITS = 4;      // per real coupling (integer couplings: one)
 constexpr int I8_BM = 256, I8_BM_REAL = 128, I8_BM_FEW = 32;  // rows of a tile
+constexpr int I8_NJ_MAX = 65281;   // N |J| of integer couplings
 constexpr int I8_N_REAL = 32000;   // 4 N 128^2 < 2^31
 constexpr float I8_CREST = 32.f;   // largest over rms of a row of real couplings, at most
 constexpr int I8_SPECIAL = 1 << 20;  // scale exponent of a replica with non-finite positions
@@ -146,8 +147,10 @@ hipError_t launch_resident_i8(const I8Args &a, const ResidentArgs &r, int32_t gr
 int32_t i8_xcd_rows(const I8Args &a);
 const char *i8_kernel_name(const I8Args &a);
 hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s);
-// *heavy (device): set if a row's largest coupling is too far above the rest.
-hipError_t launch_i8_rows(const float *J, int32_t ld, int32_t n, int32_t *jexp, int32_t *heavy,
+// Scale exponents of J's n rows (caller's layout) and flags[8], after
+// launch_validate has set the flags before it; nothing for integer couplings
+// within I8_NJ_MAX.
+hipError_t launch_i8_rows(const float *J, int32_t n, int32_t *jexp, int32_t *flags,
                           hipStream_t s);
 hipError_t launch_i8_pack_j(const float *J, int32_t ld, const int32_t *jexp, uint8_t *out,
                             hipStream_t s);
@@ -339,6 +342,8 @@ hipError_t launch_noalloc_energy(const float *J, const float *x, int32_t n, int3
 // flags[0]: asymmetric, [1]: nonzero diagonal, [2]: non-finite,
 // [3]: non-integer or |J|>127, [4]: not FP8-e4m3 exact, [5]: not BF16 exact,
 // [6]: largest |J_ij| of an integer J, [7]: a zero off the diagonal
+// ([8]: see launch_i8_rows)
+constexpr int VALIDATE_FLAGS = 16;
 hipError_t launch_validate(const float *J, int32_t n, int32_t *flags, hipStream_t s);
 
 }  // namespace si

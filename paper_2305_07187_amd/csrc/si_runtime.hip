@@ -95,8 +95,8 @@ struct si_ctx {
   int8_t *S8 = nullptr;
   int32_t *eacc = nullptr;
   float *epart = nullptr;
-  int32_t *flags = nullptr;  // device validation flags [8]
-  int32_t hflags[8] = {0};
+  int32_t *flags = nullptr;  // device validation flags, then the rows' exponents of real J
+  int32_t hflags[VALIDATE_FLAGS] = {0};
   int32_t t = 0;
   bool poisoned = false;
   int32_t inject_countdown = 0;  // test hook: > 0 fails the n-th checked HIP call
@@ -501,7 +501,12 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // 54.8 against 42.5; N = 8000, R = 50 102 against 77, R = 100 108 against 143,
 // R = 2048 1050 against 2080).
 static bool i8_integer(const si_ctx *c) {
-  return c->hflags[3] == 0 && (int64_t)c->n * c->hflags[6] <= 65281;
+  return c->hflags[3] == 0 && (int64_t)c->n * c->hflags[6] <= I8_NJ_MAX;
+}
+
+// Sizes from which real couplings would take the fixed point.
+static bool i8_real_pays(int32_t n, int32_t r) {
+  return n > 512 && n <= I8_N_REAL && (int64_t)n * round_up(r, 64) >= 640000;
 }
 
 static bool i8_few(const si_ctx *c) {
@@ -511,11 +516,11 @@ static bool i8_few(const si_ctx *c) {
 
 static bool i8_applies(const si_ctx *c) {
   const bool integer = i8_integer(c);
-  if (integer ? c->hflags[7] != 0 : c->n > I8_N_REAL || c->prm.precision != SI_PREC_FP32)
+  if (integer ? c->hflags[7] != 0 : c->hflags[8] != 0 || c->prm.precision != SI_PREC_FP32)
     return false;
   const bool split = c->prm.precision == SI_PREC_BF16X3_EXACTJ;
   const bool pays =
-      !integer ? c->n > 512 && (int64_t)c->n * round_up(c->r, 64) >= 640000
+      !integer ? i8_real_pays(c->n, c->r)
       : i8_few(c) || (c->n >= (split ? 1000 : 513) && (int64_t)c->n * round_up(c->r, 64) > 700000);
   return (split || c->prm.precision == SI_PREC_FP32) && c->prm.order == SI_ORDER_PAPER &&
          c->user_tile == 0 && !c->n_inst && pays;
@@ -533,21 +538,8 @@ static hipError_t i8_init(si_ctx *c) {
   const int64_t nr = (int64_t)c->n_pad * c->r_pad;
   const int64_t mxb = round_up((int64_t)(c->n_pad / bm) * c->r_pad * (int64_t)sizeof(I8Peak), 256);
   const int64_t kb = round_up((int64_t)c->r_pad * 4, 256);
-  int32_t *jexp = nullptr;
+  const int32_t *jexp = real ? c->flags + VALIDATE_FLAGS : nullptr;
   uint8_t *buf = nullptr;
-  if (real) {
-    // (see i8_rows_kernel: not for rows with couplings far above the rest)
-    if (c->alloc(&jexp, c->n_pad + 1) != hipSuccess) {
-      (void)hipGetLastError();
-      return hipSuccess;
-    }
-    int32_t heavy = 0, *flag = jexp + c->n_pad;
-    hipError_t e = launch_zero_i32(flag, 1, c->stream);
-    if (e == hipSuccess) e = launch_i8_rows(c->J, c->n_pad, c->n, jexp, flag, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&heavy, flag, 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess || heavy) return e;
-  }
   if (c->alloc(&buf, jb + 2 * (nr * I8_DIGITS + mxb + kb)) != hipSuccess) {
     (void)hipGetLastError();
     return hipSuccess;
@@ -868,9 +860,13 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
   }
 
   // validation of J: one host round trip
-  INIT_HIP(c->alloc(&c->flags, 8));
-  INIT_HIP(launch_zero_i32(c->flags, 8, c->stream));
+  const bool rows = prm->precision == SI_PREC_FP32 && prm->order == SI_ORDER_PAPER &&
+                    prm->tile == 0 && i8_real_pays(n, r);
+  const int64_t nflags = VALIDATE_FLAGS + (rows ? round_up(n, 256) : 0);
+  INIT_HIP(c->alloc(&c->flags, nflags));
+  INIT_HIP(launch_zero_i32(c->flags, nflags, c->stream));
   INIT_HIP(launch_validate(J, n, c->flags, c->stream));
+  if (rows) INIT_HIP(launch_i8_rows(J, n, c->flags + VALIDATE_FLAGS, c->flags, c->stream));
   INIT_HIP(hipMemcpyAsync(c->hflags, c->flags, sizeof c->hflags, hipMemcpyDeviceToHost,
                           c->stream));
   INIT_HIP(hipStreamSynchronize(c->stream));

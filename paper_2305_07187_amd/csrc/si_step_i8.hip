@@ -1124,31 +1124,30 @@ __global__ __launch_bounds__(256) void i8_pack_j_kernel(const float *__restrict_
   }
 }
 
-// Exponent of every row of real couplings, as for a replica's positions.
-// *heavy is set if a row is not a dense one of like couplings: its largest
-// exceeds I8_CREST times the root mean square of its n entries, or more than
-// a sixteenth of them lie below 1/1024 of the largest (a Gaussian row: 0.4 %;
-// the diagonal is one).  Such rows' sums may be finer in FP32 than 2^-31 of
-// their largest product.  One wave per row.
-__global__ __launch_bounds__(256) void i8_rows_kernel(const float *__restrict__ J, int ld, int n,
-                                                      int *__restrict__ jexp, int *heavy) {
+// Exponent of every row of real couplings (caller's layout), as for a replica's
+// positions.  flags[8] is set if a row is not a dense one of like couplings:
+// its largest exceeds I8_CREST times the root mean square of its n entries, or
+// more than a sixteenth of them lie below 1/1024 of the largest (a Gaussian
+// row: 0.4 %; the diagonal is one).  Such rows' sums may be finer in FP32 than
+// 2^-31 of their largest product.  One wave per row; nothing to do for
+// couplings that the checks before it (flags) found to take one digit.
+__global__ __launch_bounds__(256) void i8_rows_kernel(const float *__restrict__ J, int n,
+                                                      int *__restrict__ jexp, int *flags) {
+  if (flags[3] == 0 && (int64_t)n * flags[6] <= I8_NJ_MAX) return;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= n) return;
+  const float *x = J + (size_t)row * n;
   float m = 0.f;
-  for (int i = lane * 4; i < ld; i += 256) {
-    const floatx4 x = *reinterpret_cast<const floatx4 *>(J + (size_t)row * ld + i);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(x[v]));
-  }
+#pragma unroll 4
+  for (int i = lane; i < n; i += 64) m = fmaxf(m, fabsf(x[i]));
   for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
   float s = 0.f;  // sum of squares in units of the largest
   int small = 0;
-  for (int i = lane * 4; i < ld && m > 0.f; i += 256) {
-    const floatx4 x = *reinterpret_cast<const floatx4 *>(J + (size_t)row * ld + i);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      s = fmaf(x[v] / m, x[v] / m, s);
-      small += i + v < n && fabsf(x[v]) < m * (1.f / 1024.f);
-    }
+#pragma unroll 4
+  for (int i = lane; i < n; i += 64) {
+    const float v = m > 0.f ? x[i] / m : 0.f;
+    s = fmaf(v, v, s);
+    small += fabsf(x[i]) < m * (1.f / 1024.f);
   }
   for (int off = 32; off >= 1; off >>= 1) {
     s += __shfl_xor(s, off);
@@ -1156,7 +1155,7 @@ __global__ __launch_bounds__(256) void i8_rows_kernel(const float *__restrict__ 
   }
   if (lane == 0) {
     jexp[row] = i8_exponent(m);
-    if (row < n && (s * (I8_CREST * I8_CREST) < (float)n || small > n / 16 || m == 0.f)) *heavy = 1;
+    if (s * (I8_CREST * I8_CREST) < (float)n || small > n / 16 || m == 0.f) flags[8] = 1;
   }
 }
 
@@ -1281,10 +1280,10 @@ hipError_t launch_i8_prepare(const I8Args &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_i8_rows(const float *J, int32_t ld, int32_t n, int32_t *jexp, int32_t *heavy,
+hipError_t launch_i8_rows(const float *J, int32_t n, int32_t *jexp, int32_t *flags,
                           hipStream_t s) {
-  if (ld % 4) return hipErrorInvalidValue;
-  i8_rows_kernel<<<ld / 4, 256, 0, s>>>(J, ld, n, jexp, heavy);
+  if (n < 1) return hipErrorInvalidValue;
+  i8_rows_kernel<<<(n + 3) / 4, 256, 0, s>>>(J, n, jexp, flags);
   return hipGetLastError();
 }
 
