@@ -137,6 +137,11 @@ typedef struct {
                          energy over the iterations (Fig. 4).  0 = off. */
 } si_params;
 
+/* Tile id of the fixed-point form of FP32 and BF16X3_EXACTJ (see si_precision).
+ * As si_params.tile it asks for that form: SI_ERR_INVALID where it does not
+ * apply to the couplings, sizes or order. */
+#define SI_TILE_FIXED_POINT 100
+
 /* Where the step kernel's tile of a context came from (si_info.tile_source). */
 typedef enum {
   SI_TILE_FROM_TABLE = 0,   /* built-in preference order (from tile sweeps) */
@@ -154,9 +159,7 @@ typedef struct {
   int32_t j_integer;        /* 1 if every J_ij is an integer with |J_ij| <= 127 */
   int32_t j_fp8_exact;      /* 1 if every J_ij is exact in FP8 e4m3 */
   int32_t j_bf16_exact;     /* 1 if every J_ij is exact in BF16 */
-  int32_t tile;             /* tile id of the step kernel in use (of the FP32 tile
-                               that stands by, where kernel_name is the
-                               fixed-point form's) */
+  int32_t tile;             /* tile id of the step kernel in use */
   int32_t precision;        /* si_precision in use */
   int32_t graph_steps;      /* steps per captured HIP graph (0: not captured) */
   int64_t device_bytes;     /* device memory owned by the context */
@@ -285,9 +288,9 @@ si_status spring_ising_set_resident(si_ctx *ctx, int32_t min_steps);
  * context (its precision and padded shape; on a batch, both batch tiles),
  * starting from the current state, in two rounds over all candidates (each
  * candidate keeps its faster round), restore the state after each run, and
- * keep the fastest for later steps (the fixed-point form of FP32, where the
- * context has it, if it beats every tile).  The choice is also stored in the
- * process's tile cache under this context's key, so that later contexts of
+ * keep the fastest for later steps.  The fixed-point form, where the context
+ * has it, is timed as tile SI_TILE_FIXED_POINT.  The choice is also stored in
+ * the process's tile cache under this context's key, so that later contexts of
  * that key created with tile 0 start on it.  *best_tile and *best_us (host,
  * nullable) receive the choice and its time per step.  Kernels with a
  * different MFMA shape add the contraction in a different order, so later
@@ -315,7 +318,8 @@ si_status spring_ising_batch_timeline(si_ctx *ctx, int32_t n_steps, uint64_t *ou
 
 /* Tile cache of the process (shared by every context and thread; library
  * bookkeeping with no counterpart in the paper).  Key:
- *   single instance: (precision, N-bucket, R rounded up to 64, CU count);
+ *   single instance: (precision, N-bucket, R rounded up to 64, CU count,
+ *          whether the context has the fixed-point form);
  *   batch: (precision, bucket of the sum of the padded N_i, bucket of the
  *          largest padded N_i, R rounded up to 64, CU count);
  * the N-bucket of x is b with 2^(b-1) < x <= 2^b.  Value: tile id and its
@@ -324,7 +328,8 @@ si_status spring_ising_batch_timeline(si_ctx *ctx, int32_t n_steps, uint64_t *ou
  *   line 1: "# spring_ising tile cache 1"
  *   line 2: "build <build id>"
  *   then one line per entry: "<kind> <precision> <nb> <mb> <r64> <cus>
- *   <tile> <us>" (kind 0: single instance, mb 0; kind 1: batch).
+ *   <tile> <us>" (kind 0: single instance, mb 1 with the fixed-point form,
+ *   else 0; kind 1: batch).
  * save writes every entry (SI_ERR_INVALID if the file cannot be written).
  * load merges a file's entries into the cache and sets *n_loaded (host,
  * nullable): SI_ERR_INVALID, with nothing loaded, for a file that does not

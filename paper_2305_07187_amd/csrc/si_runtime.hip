@@ -158,6 +158,7 @@ struct si_ctx {
   I8Args i8{};
   int32_t i8_groups = -1;       // workgroups of its resident form (-1: not asked yet)
   bool i8_off = false;          // autotune found an FP32 tile faster, or is timing one
+  bool i8_declined = false;     // the tile cache says so for this context's key
   float *fsplit = nullptr;      // partial products of the split contraction
   int64_t fsplit_cap = 0;       // floats
   int32_t *res_sync = nullptr;  // [0] time-out flag, [64 ..] per-group step counts
@@ -295,7 +296,9 @@ static si_status check_params(const si_params *p) {
   if (p->precision < SI_PREC_FP32 || p->precision > SI_PREC_BF16X_MIXEDJ)
     return fail(SI_ERR_INVALID, "params: unknown precision %d", p->precision);
   const int32_t last = p->precision == SI_PREC_FP32 ? TILE_F32_LAST : TILE_BF16_LAST;
-  if (p->tile < 0 || p->tile > last)
+  const bool fixed = p->tile == SI_TILE_FIXED_POINT &&
+                     (p->precision == SI_PREC_FP32 || p->precision == SI_PREC_BF16X3_EXACTJ);
+  if ((p->tile < 0 || p->tile > last) && !fixed)
     return fail(SI_ERR_INVALID, "params: unknown tile %d", p->tile);
   if (p->energy_every < 0) return fail(SI_ERR_INVALID, "params: energy_every must be >= 0");
   return SI_OK;
@@ -531,7 +534,7 @@ static bool i8_on(const si_ctx *c) { return c->i8.Jt && c->ksplit_mode == 0 && !
 // Buffers of the int8 form, the large ones in one allocation.  Without the memory for it the
 // context simply runs on the FP32 matrix cores.
 static hipError_t i8_init(si_ctx *c) {
-  if (!i8_applies(c)) return hipSuccess;
+  if (!i8_applies(c) || c->i8_declined) return hipSuccess;
   const bool real = !i8_integer(c);
   const int32_t bm = real ? I8_BM_REAL : i8_few(c) ? I8_BM_FEW : I8_BM;
   const int64_t jb = (int64_t)c->n_pad * c->n_pad * (real ? I8_JDIGITS : 1);
@@ -650,7 +653,9 @@ static const char k_build_id[] = "SI_BUILD_ID:" SI_BUILD_ID;
 
 // The process's tile cache: (kind, precision, N-bucket, largest-N bucket,
 // R rounded to 64, CU count) -> (tile, us per step).  Kind 0: single
-// instance (largest-N bucket 0), kind 1: batch.
+// instance (in place of the largest-N bucket 1 where the context has the
+// fixed-point form, whose entry says which of the two to run, else 0), kind 1:
+// batch.
 namespace {
 using TileKey = std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t, int32_t>;
 struct TileEntry {
@@ -666,19 +671,22 @@ int32_t n_bucket(int64_t x) {
   return b;
 }
 
-TileKey tile_key(const si_ctx *c) {
+TileKey tile_key(const si_ctx *c, bool fixed_point) {
   if (c->n_inst) {
     int64_t rows = 0;
     for (int32_t np : c->b_npad) rows += np;
     return TileKey{1, c->prm.precision, n_bucket(rows), n_bucket(c->b_max_npad),
                    (int32_t)round_up(c->r, 64), c->num_cus};
   }
-  return TileKey{0, c->prm.precision, n_bucket(c->n), 0, (int32_t)round_up(c->r, 64),
-                 c->num_cus};
+  return TileKey{0, c->prm.precision, n_bucket(c->n), fixed_point ? 1 : 0,
+                 (int32_t)round_up(c->r, 64), c->num_cus};
 }
 
 // Can `tile` serve contexts of this key at all (padding aside)?
-bool tile_serves(int32_t kind, int32_t precision, int32_t tile) {
+bool tile_serves(int32_t kind, int32_t precision, int32_t mb, int32_t tile) {
+  if (tile == SI_TILE_FIXED_POINT)
+    return kind == 0 && mb == 1 &&
+           (precision == SI_PREC_FP32 || precision == SI_PREC_BF16X3_EXACTJ);
   if (kind == 1) return tile >= 1 && tile <= BATCH_TILE_LAST;
   if (precision == SI_PREC_FP32) return tile >= 1 && tile <= TILE_F32_LAST;
   return tile >= 1 && tile <= TILE_BF16_LAST && tile_valid_bf16(tile, precision);
@@ -861,7 +869,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
 
   // validation of J: one host round trip
   const bool rows = prm->precision == SI_PREC_FP32 && prm->order == SI_ORDER_PAPER &&
-                    prm->tile == 0 && i8_real_pays(n, r);
+                    (prm->tile == 0 || prm->tile == SI_TILE_FIXED_POINT) && i8_real_pays(n, r);
   const int64_t nflags = VALIDATE_FLAGS + (rows ? round_up(n, 256) : 0);
   INIT_HIP(c->alloc(&c->flags, nflags));
   INIT_HIP(launch_zero_i32(c->flags, nflags, c->stream));
@@ -881,17 +889,26 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
   prm = &c->prm;
 
   const bool lowp = prm->precision != SI_PREC_FP32;
-  c->user_tile = prm->tile;
+  const bool fixed = prm->tile == SI_TILE_FIXED_POINT;
+  c->user_tile = fixed ? 0 : prm->tile;  // (its FP32 or BF16 tile stands by)
   c->n = n;
   c->r = r;
+  const bool has_fixed = i8_applies(c);
+  if (fixed && !has_fixed) {
+    delete c;
+    return fail(SI_ERR_INVALID, "init: tile %d (fixed point) does not apply to these couplings "
+                "and sizes", SI_TILE_FIXED_POINT);
+  }
   int32_t cached = 0;
-  if (prm->tile) {
-    c->tile = prm->tile;
-    c->tile_source = SI_TILE_FROM_CALLER;
-  } else if (tile_cache_get(tile_key(c), &cached) &&
-             tile_serves(0, prm->precision, cached)) {
+  const bool hit = !prm->tile && tile_cache_get(tile_key(c, has_fixed), &cached) &&
+                   tile_serves(0, prm->precision, has_fixed, cached);
+  if (hit) c->tile_source = SI_TILE_FROM_CACHE;
+  if (prm->tile) c->tile_source = SI_TILE_FROM_CALLER;
+  c->i8_declined = hit && has_fixed && cached != SI_TILE_FIXED_POINT;
+  if (c->user_tile) {
+    c->tile = c->user_tile;
+  } else if (hit && cached != SI_TILE_FIXED_POINT) {
     c->tile = cached;
-    c->tile_source = SI_TILE_FROM_CACHE;
   } else if (!lowp && c->num_cus == 256 &&
              few_replica_default(n, r, &c->table_tile, &c->table_split)) {
     c->tile = c->table_tile;
@@ -905,7 +922,7 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
     return fail(SI_ERR_INVALID, "init: tile %d cannot run precision %d", bad, prm->precision);
   }
   const TileShape ts = shape_of(prm->precision, c->tile);
-  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, i8_applies(c) && i8_integer(c) && !i8_few(c) ? I8_BM : 128));
+  c->n_pad = (int32_t)round_up(n, std::max(ts.bm, has_fixed && !c->i8_declined && i8_integer(c) && !i8_few(c) ? I8_BM : 128));
   c->r_pad = (int32_t)round_up(r, ts.bn > 64 ? ts.bn : 64);
   const bool j_integer = c->hflags[3] == 0;
   const bool need_bf16 = prm->precision == SI_PREC_BF16X_BF16J ||
@@ -1159,7 +1176,8 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
   if (prm->tile) {
     c->tile = prm->tile;
     c->tile_source = SI_TILE_FROM_CALLER;
-  } else if (tile_cache_get(tile_key(c), &cached) && tile_serves(1, prm->precision, cached)) {
+  } else if (tile_cache_get(tile_key(c, false), &cached) &&
+             tile_serves(1, prm->precision, 0, cached)) {
     c->tile = cached;
     c->tile_source = SI_TILE_FROM_CACHE;
   } else {
@@ -1886,7 +1904,7 @@ static si_status autotune_batch(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   SI_HIP(c, batch_items(c));
   c->tile_source = SI_TILE_FROM_AUTOTUNE;
   c->drop_graphs();
-  tile_cache_put(tile_key(c), best, best_t);
+  tile_cache_put(tile_key(c, false), best, best_t);
   if (best_tile) *best_tile = best;
   if (best_us) *best_us = best_t;
   return SI_OK;
@@ -1977,7 +1995,6 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   }
   c->tile = best;
   SI_HIP(c, ensure_split_ws(c));
-  tile_cache_put(tile_key(c), best, best_t);
   if (has_i8) {
     c->i8_off = false;
     float i8_t = 1e30f;
@@ -2000,8 +2017,12 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
     }
     c->i8_off = best_t < i8_t;
     SI_HIP(c, i8_refresh(c));
-    best_t = std::min(best_t, i8_t);
+    if (!c->i8_off) {
+      best = SI_TILE_FIXED_POINT;
+      best_t = i8_t;
+    }
   }
+  tile_cache_put(tile_key(c, has_i8 || c->i8_declined), best, best_t);
   c->drop_graphs();
   c->tile_source = SI_TILE_FROM_AUTOTUNE;
   if (best_tile) *best_tile = best;
@@ -2314,7 +2335,7 @@ si_status spring_ising_tile_cache_load(const char *path, int32_t *n_loaded) {
     }
     if (!ok || fields != 8 || (v[0] != 0 && v[0] != 1) || v[1] < SI_PREC_FP32 ||
         v[1] > SI_PREC_BF16X_MIXEDJ || v[2] < 0 || v[3] < 0 || v[4] < 64 || v[4] % 64 ||
-        v[5] < 1 || !tile_serves(v[0], v[1], v[6])) {
+        v[5] < 1 || !tile_serves(v[0], v[1], v[3], v[6])) {
       st = fail(SI_ERR_INVALID, "tile_cache_load: %s line %d: bad entry", path, lineno);
       break;
     }
@@ -2354,7 +2375,7 @@ si_status spring_ising_info(si_ctx *c, si_info *info) {
   }
   info->j_fp8_exact = c->hflags[4] == 0;
   info->j_bf16_exact = c->hflags[5] == 0;
-  info->tile = c->tile;
+  info->tile = !c->n_inst && i8_on(c) ? SI_TILE_FIXED_POINT : c->tile;
   info->tile_source = c->tile_source;
   info->n_inst = c->n_inst;
   info->precision = c->prm.precision;

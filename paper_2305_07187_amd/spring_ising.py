@@ -362,6 +362,7 @@ def spring_ising_autotune(ctx, steps):
     return tile.value, us.value
 
 
+SI_TILE_FIXED_POINT = 100  # tile id of the fixed-point form of FP32 and BF16X3_EXACTJ
 TILE_SOURCES = {0: "table", 1: "cache", 2: "caller", 3: "autotune"}
 
 
