@@ -476,6 +476,13 @@ const char *spring_ising_build_id(void);
  * injection; SI_ERR_INVALID if n < 0. */
 si_status spring_ising_debug_inject_hip_error(si_ctx *ctx, int32_t n);
 
+/* Test hook: the next n device allocations of the context (n >= 0; 0 cancels)
+ * fail as they do without free memory.  A context that has the fixed-point
+ * form gives that form's buffers back before a call fails for memory, and
+ * goes on with the tile that stands by; others return SI_ERR_OOM.
+ * SI_ERR_INVALID if n < 0. */
+si_status spring_ising_debug_fail_allocs(si_ctx *ctx, int32_t n);
+
 #ifdef __cplusplus
 }
 #endif

@@ -100,6 +100,7 @@ struct si_ctx {
   int32_t t = 0;
   bool poisoned = false;
   int32_t inject_countdown = 0;  // test hook: > 0 fails the n-th checked HIP call
+  int32_t fail_allocs = 0;       // test hook: allocations yet to fail
   uint16_t *tune_qb = nullptr;    // autotune: saved BF16 planes of q
   float *tune_save = nullptr;     // autotune of a batch: saved q and p
   hipEvent_t tune_ev[2] = {nullptr, nullptr};
@@ -156,6 +157,9 @@ struct si_ctx {
   int64_t b_trace_cap = 0;                // records
   // FP32 step on the int8 matrix cores (i8.Jt: set when this context has it)
   I8Args i8{};
+  uint8_t *i8_buf = nullptr;    // its digits, scales and counts
+  int64_t i8_bytes = 0;
+  bool i8_keep = false;         // not to be given back for the allocation at hand
   int32_t i8_groups = -1;       // workgroups of its resident form (-1: not asked yet)
   bool i8_off = false;          // autotune found an FP32 tile faster, or is timing one
   bool i8_declined = false;     // the tile cache says so for this context's key
@@ -198,6 +202,15 @@ struct si_ctx {
   uint8_t *arena = nullptr;
   int64_t arena_left = 0;
 
+  hipError_t device_malloc(void **raw, int64_t size) {
+    if (fail_allocs > 0) {
+      --fail_allocs;
+      return hipErrorOutOfMemory;
+    }
+    return hipMalloc(raw, (size_t)size);
+  }
+  hipError_t release_i8();
+
   // One device allocation that the next alloc() calls take their buffers
   // from: a hipMalloc and its hipFree take 10 .. 40 us each, whatever the size
   // (a gradient at N = 2000, R = 64 creates a context and the adjoint's
@@ -206,7 +219,7 @@ struct si_ctx {
     void *raw = nullptr;
     arena = nullptr;
     arena_left = 0;
-    if (total <= 0 || hipMalloc(&raw, (size_t)total) != hipSuccess) {
+    if (total <= 0 || device_malloc(&raw, total) != hipSuccess) {
       (void)hipGetLastError();
       return;
     }
@@ -229,7 +242,14 @@ struct si_ctx {
       return hipSuccess;
     }
     void *raw = nullptr;
-    hipError_t e = hipMalloc(&raw, (size_t)count * sizeof(T));
+    hipError_t e = device_malloc(&raw, count * (int64_t)sizeof(T));
+    // the fixed-point form's buffers are the only ones that a context can do
+    // without: given back before a call fails that would have fitted
+    if (e == hipErrorOutOfMemory && i8_buf && !i8_keep) {
+      (void)hipGetLastError();
+      e = release_i8();
+      if (e == hipSuccess) e = device_malloc(&raw, count * (int64_t)sizeof(T));
+    }
     if (e != hipSuccess) return e;
     allocs.push_back(raw);
     bytes += count * (int64_t)sizeof(T);
@@ -248,6 +268,7 @@ struct si_ctx {
     for (hipEvent_t e : tune_ev)
       if (e) (void)hipEventDestroy(e);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
+    if (i8_buf) (void)hipFree(i8_buf);
     for (void *a : allocs) (void)hipFree(a);
   }
 };
@@ -542,11 +563,15 @@ static hipError_t i8_init(si_ctx *c) {
   const int64_t mxb = round_up((int64_t)(c->n_pad / bm) * c->r_pad * (int64_t)sizeof(I8Peak), 256);
   const int64_t kb = round_up((int64_t)c->r_pad * 4, 256);
   const int32_t *jexp = real ? c->flags + VALIDATE_FLAGS : nullptr;
-  uint8_t *buf = nullptr;
-  if (c->alloc(&buf, jb + 2 * (nr * I8_DIGITS + mxb + kb)) != hipSuccess) {
+  const int64_t size = jb + 2 * (nr * I8_DIGITS + mxb + kb);
+  void *raw = nullptr;
+  if (c->device_malloc(&raw, size) != hipSuccess) {
     (void)hipGetLastError();
     return hipSuccess;
   }
+  uint8_t *buf = c->i8_buf = static_cast<uint8_t *>(raw);
+  c->i8_bytes = size;
+  c->bytes += size;
   I8Args &a = c->i8;
   a.J = c->J;
   a.jexp = jexp;
@@ -618,6 +643,20 @@ static hipError_t i8_refresh(si_ctx *c) {
   c->i8.cur = c->cur;
   c->i8.t = c->t;
   return launch_i8_prepare(c->i8, c->stream);
+}
+
+// Gives the int8 form's buffers back: later steps run on the tile that stands
+// by.  (No call allocates between a step's launches or during a capture.)
+hipError_t si_ctx::release_i8() {
+  hipError_t e = hipStreamSynchronize(stream);
+  drop_graphs();
+  if (e == hipSuccess) e = hipFree(i8_buf);
+  i8_buf = nullptr;
+  bytes -= i8_bytes;
+  i8 = I8Args{};
+  if (e == hipSuccess && qplanes)
+    e = launch_split_planes(q[cur], qb[cur], (int64_t)n_pad * r_pad, qplanes, stream);
+  return e;
 }
 
 // Buffers of the best-state record (allocated once, records invalid).
@@ -809,6 +848,13 @@ si_status spring_ising_debug_inject_hip_error(si_ctx *c, int32_t n) {
   SI_USABLE(c);
   if (n < 0) return fail(SI_ERR_INVALID, "debug_inject_hip_error: n=%d < 0", n);
   c->inject_countdown = n;
+  return SI_OK;
+}
+
+si_status spring_ising_debug_fail_allocs(si_ctx *c, int32_t n) {
+  SI_USABLE(c);
+  if (n < 0) return fail(SI_ERR_INVALID, "debug_fail_allocs: n=%d < 0", n);
+  c->fail_allocs = n;
   return SI_OK;
 }
 
@@ -1758,8 +1804,10 @@ static int32_t resident_groups(si_ctx *c) {
 static si_status run_resident(si_ctx *c, int32_t n_steps, int32_t groups) {
   // res_sync: [0] time-out flag, [64 ..] one completed-step count per group
   if (c->res_sync_cap < groups) {
+    const bool fixed = i8_on(c);
     SI_HIP(c, c->alloc(&c->res_sync, 64 + (int64_t)groups));
     c->res_sync_cap = groups;
+    if (fixed != i8_on(c)) return do_steps(c, n_steps);  // (given back: another kernel)
   }
   SI_HIP(c, launch_zero_i32(c->res_sync, 64 + (int64_t)groups, c->stream));
   StepArgs a = step_args(c);
@@ -1918,13 +1966,6 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   c->epoch++;
   if (c->n_inst) return autotune_batch(c, steps, best_tile, best_us);
   const int64_t NR = (int64_t)c->n_pad * c->r_pad;
-  // the int8 form, where the context has it, is timed against the fastest
-  // tile of the others below
-  const bool has_i8 = c->i8.Jt && c->ksplit_mode == 0;
-  if (has_i8) {
-    c->i8_off = true;
-    SI_HIP(c, i8_refresh(c));
-  }
   // saved state: q and p in the adjoint's segment buffer, the BF16 planes of
   // q in a buffer of their own; both kept for later calls
   if (!c->adj_seg || c->adj_seg_cap < 2 * NR) {
@@ -1935,6 +1976,18 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   float *save = c->adj_seg;
   if (c->qplanes && !c->tune_qb) SI_HIP(c, c->alloc(&c->tune_qb, NR * c->qplanes));
   uint16_t *save_b = c->qplanes ? c->tune_qb : nullptr;
+  // the int8 form, where the context has it, is timed against the fastest
+  // tile of the others below (and not given up for a candidate's workspace)
+  const bool has_i8 = c->i8.Jt && c->ksplit_mode == 0;
+  struct KeepI8 {
+    si_ctx *c;
+    ~KeepI8() { c->i8_keep = false; }
+  } keep_i8{c};
+  c->i8_keep = has_i8;
+  if (has_i8) {
+    c->i8_off = true;
+    SI_HIP(c, i8_refresh(c));
+  }
   const int32_t t0 = c->t, cur0 = c->cur, tile0 = c->tile;
   SI_HIP(c, hipMemcpyAsync(save, c->q[cur0], NR * 4, hipMemcpyDeviceToDevice, c->stream));
   SI_HIP(c, hipMemcpyAsync(save + NR, c->p[cur0], NR * 4, hipMemcpyDeviceToDevice, c->stream));

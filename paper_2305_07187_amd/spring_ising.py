@@ -108,6 +108,7 @@ _SIGNATURES = {
     "spring_ising_init_batch": [ctypes.POINTER(_P), _I, _P, _I, _P, _P, _P,
                                 ctypes.POINTER(si_params), _P],
     "spring_ising_debug_inject_hip_error": [_P, _I],
+    "spring_ising_debug_fail_allocs": [_P, _I],
     "spring_ising_energy_noalloc": [_I, _I, _P, _P, _P, _P],
     "spring_ising_get_energy_trace": [_P, _P, ctypes.POINTER(_I)],
     "spring_ising_destroy": [_P],
@@ -175,6 +176,10 @@ def spring_ising_get_energy_trace(ctx, e=None):
 
 def spring_ising_debug_inject_hip_error(ctx, n):
     _check(load_library().spring_ising_debug_inject_hip_error(ctx, int(n)))
+
+
+def spring_ising_debug_fail_allocs(ctx, n):
+    _check(load_library().spring_ising_debug_fail_allocs(ctx, int(n)))
 
 
 def _check(status: int):
