@@ -1921,14 +1921,15 @@ static si_status autotune_batch(si_ctx *c, int32_t steps, int32_t *best_tile, fl
     ~KeepEvery() { c->e_every = v; }
   } keep{c, c->e_every};
   c->e_every = 0;
-  const int32_t timed = steps - 1 > 0 ? steps - 1 : 1;
+  // (a single step has no warm-up: the schedule may end after it)
+  const int32_t warm = steps > 1 ? 1 : 0, timed = steps - warm;
   int32_t best = tile0;
   float best_t = 1e30f;
   for (int round = 0; round < 2; ++round)  // as for single instances
   for (int32_t tile = 1; tile <= BATCH_TILE_LAST; ++tile) {
     c->tile = tile;
     SI_HIP(c, batch_items(c));
-    si_status st = do_steps(c, 1);  // warm-up
+    si_status st = do_steps(c, warm);  // warm-up
     if (st != SI_OK) return st;
     SI_HIP(c, hipEventRecord(e0, c->stream));
     st = do_steps(c, timed);
@@ -2008,7 +2009,8 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
   } keep{c, c->e_every};
   c->e_every = 0;
   const int32_t last = lowp ? TILE_BF16_LAST : TILE_F32_LAST;
-  const int32_t timed = steps - 1 > 0 ? steps - 1 : 1;
+  // (a single step has no warm-up: the schedule may end after it)
+  const int32_t warm = steps > 1 ? 1 : 0, timed = steps - warm;
   int32_t best = tile0;
   float best_t = 1e30f;
   // two rounds over the candidates, each keeping its faster round: the first
@@ -2023,7 +2025,7 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
       (void)hipGetLastError();
       continue;
     }
-    si_status st = do_steps(c, 1);  // warm-up (also loads the code object)
+    si_status st = do_steps(c, warm);  // warm-up (also loads the code object)
     if (st != SI_OK) return st;
     SI_HIP(c, hipEventRecord(e0, c->stream));
     st = do_steps(c, timed);
@@ -2053,7 +2055,7 @@ si_status spring_ising_autotune(si_ctx *c, int32_t steps, int32_t *best_tile, fl
     float i8_t = 1e30f;
     for (int round = 0; round < 2; ++round) {
       SI_HIP(c, i8_refresh(c));
-      si_status st = do_steps(c, 1);
+      si_status st = do_steps(c, warm);
       if (st != SI_OK) return st;
       SI_HIP(c, hipEventRecord(e0, c->stream));
       st = do_steps(c, timed);
