@@ -472,8 +472,8 @@ const char *spring_ising_build_id(void);
  * checks after this call (n >= 1) reports a failure although the call itself
  * succeeded, which poisons the context exactly as a real HIP failure does
  * (that call returns SI_ERR_HIP, every later call other than destroy
- * SI_ERR_STATE).  No device operation is altered.  n = 0 cancels a pending
- * injection; SI_ERR_INVALID if n < 0. */
+ * SI_ERR_STATE).  No device operation is altered; a launch of several steps
+ * counts as one call per step.  n = 0 cancels a pending injection; SI_ERR_INVALID if n < 0. */
 si_status spring_ising_debug_inject_hip_error(si_ctx *ctx, int32_t n);
 
 /* Test hook: the next n device allocations of the context (n >= 0; 0 cancels)

@@ -1493,7 +1493,7 @@ static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
   for (int32_t left = n_steps; left > 0;) {
     // small problems: all steps up to the next energy check in one launch
     int32_t len = 1;
-    if (small && c->inject_countdown <= 0) {  // (the hook counts the steps' launches)
+    if (small) {
       len = std::min(left, SMALL_STEPS_MAX);
       if (c->e_every > 0) len = std::min(len, c->e_every - c->t % c->e_every);
       if (len < small_steps_least(c->n)) len = 1;
@@ -1504,10 +1504,13 @@ static si_status do_steps_f32(si_ctx *c, int32_t n_steps) {
     a.q_out = c->q[to];
     a.p_out = c->p[to];
     a.t = c->t;
-    if (len > 1)
+    if (len > 1) {
+      // (the failure hook counts one call per step, however they are launched)
+      if (c->inject_countdown > 0) c->inject_countdown = std::max(1, c->inject_countdown - (len - 1));
       SI_HIP(c, launch_small_steps(a, len, c->stream));
-    else
+    } else {
       SI_HIP(c, launch_step_f32(c->tile, a, c->stream));
+    }
     c->cur = to;
     c->t += len;
     left -= len;
