@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("after,ok_runs", [(1, 0), (9, 0), (10, 0), (11, 1), (25, 2)])
 def test_failure_in_many_steps(n, after, ok_runs):
     import torch
+    from torch.profiler import ProfilerActivity, profile
     si = ensure_built()
     announce(f"injected failure after {after} steps' calls N={n}")
     J, x0 = to_dev(instances.make_pm1(n, 1)), to_dev(instances.make_x0(n, 8, 1))
@@ -35,7 +36,11 @@ def test_failure_in_many_steps(n, after, ok_runs):
     # armed and never reached: the same states
     a = si.SpringIsing(J, x0, total_steps=100)
     si.spring_ising_debug_inject_hip_error(a.ctx, 1000)
-    a.run(5 + 10 * ok_runs)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        a.run(5 + 10 * ok_runs)
+        torch.cuda.synchronize()
+    if n <= 128 or ok_runs:  # (N = 200: from six steps on)
+        assert any("small_steps_kernel" in ev.name for ev in prof.events())
     for u, v in zip(a.state()[:2], clean.state()[:2]):
         assert torch.equal(u, v)
     a.close()
