@@ -163,7 +163,8 @@ typedef struct {
   int32_t precision;        /* si_precision in use */
   int32_t graph_steps;      /* steps per captured HIP graph (0: not captured) */
   int64_t device_bytes;     /* device memory owned by the context */
-  char kernel_name[64];     /* name of the step kernel in use */
+  char kernel_name[64];     /* name of the step kernel in use (small problems: of
+                               runs whose steps share a launch) */
   int32_t resident_steps;   /* run() calls of at least this many steps use the
                                resident launch (0: off or not available) */
   int32_t resident_groups;  /* workgroups of that launch (0: not available) */

@@ -87,6 +87,7 @@ constexpr int32_t SMALL_STEPS_MAX = 4096;
 // = 8 5.4 and 4.3, N = 224, R = 2000 12.8 and 8.1; then 1.1 and 3.7 us a step).
 inline int32_t small_steps_least(int32_t n) { return n <= 128 ? 2 : 6; }
 bool small_fits(int32_t tile, int32_t n, int32_t r_pad);
+int32_t small_rows(int32_t n);  // rows that its kernel for n spins holds
 hipError_t launch_small_steps(const StepArgs &a, int32_t steps, hipStream_t s);
 
 // Resident form: one cooperative launch runs n_steps steps.  Every workgroup
@@ -283,6 +284,9 @@ hipError_t launch_adj_step(const float *J, const float *lamq_in, const float *la
 int32_t adj_split_groups(int32_t n_pad, int32_t r_pad, int32_t ksplit);
 // Floats of workspace that the split forms need (0: they keep the partial
 // products in LDS).
+// Rows of the one-launch form's tile (32 columns) where it stands in for
+// `tile`, else 0.
+int32_t split_few_rows(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit);
 int64_t split_workspace(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit);
 int64_t adj_split_workspace(int32_t n_pad, int32_t r_pad, int32_t ksplit);
 // masked: the multipliers were masked with `mask` by the launch that wrote

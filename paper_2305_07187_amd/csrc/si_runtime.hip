@@ -2446,6 +2446,15 @@ si_status spring_ising_info(si_ctx *c, si_info *info) {
              c->b_lowp ? "bf16" : "f32", batch_tile_rows(c->tile), BATCH_BN, c->n_inst);
   else if (i8_on(c))
     snprintf(info->kernel_name, sizeof info->kernel_name, "%s", i8_kernel_name(c->i8));
+  else if (!c->qplanes && split_for(c, c->tile) <= 1 && !info->resident_steps &&
+           small_fits(c->tile, c->n, c->r_pad))
+    snprintf(info->kernel_name, sizeof info->kernel_name, "step_f32_small_%dx16_w8_mfma16",
+             small_rows(c->n));
+  else if (const int32_t rows = split_for(c, c->tile) > 1
+                                    ? split_few_rows(c->tile, c->n_pad, c->r_pad, split_for(c, c->tile))
+                                    : 0)
+    snprintf(info->kernel_name, sizeof info->kernel_name, "step_f32_few_%dx32_mfma%d_k32_ks%d",
+             rows, rows, split_for(c, c->tile));
   else if (split_for(c, c->tile) > 1)
     snprintf(info->kernel_name, sizeof info->kernel_name, "%s_ks%d",
              shape_of(c->prm.precision, c->tile).name, split_for(c, c->tile));

@@ -131,21 +131,31 @@ bool small_fits(int32_t tile, int32_t n, int32_t r_pad) {
   }
 }
 
+// The kernel's row blocks for n spins.
+static int small_blocks(int32_t n) {
+  const int kb = (n + 15) / 16;
+  return kb == 7 ? 7 : (kb + 1) / 2 * 2;
+}
+
+int32_t small_rows(int32_t n) { return small_blocks(n) * 16; }
+
 hipError_t launch_small_steps(const StepArgs &a, int32_t steps, hipStream_t s) {
-  const int kb = (a.n + 15) / 16;
-  // (row blocks beyond kb, up to the next size below, lie in J's padding)
+  const int kb = small_blocks(a.n);
+  // (row blocks beyond n lie in J's padding)
   if (steps < 1 || a.r_pad % SMALL_COLS || a.n < 1 || a.ld % 64 ||
       kb * 16 > a.ld || a.mask_out)
     return hipErrorInvalidValue;
-  if (kb <= 2) return small_launch<2>(a, steps, s);
-  if (kb <= 4) return small_launch<4>(a, steps, s);
-  if (kb <= 6) return small_launch<6>(a, steps, s);
-  if (kb <= 7) return small_launch<7>(a, steps, s);
-  if (kb <= 8) return small_launch<8>(a, steps, s);
-  if (kb <= 10) return small_launch<10>(a, steps, s);
-  if (kb <= 12) return small_launch<12>(a, steps, s);
-  if (kb <= 14) return small_launch<14>(a, steps, s);
-  return hipErrorInvalidValue;
+  switch (kb) {
+    case 2: return small_launch<2>(a, steps, s);
+    case 4: return small_launch<4>(a, steps, s);
+    case 6: return small_launch<6>(a, steps, s);
+    case 7: return small_launch<7>(a, steps, s);
+    case 8: return small_launch<8>(a, steps, s);
+    case 10: return small_launch<10>(a, steps, s);
+    case 12: return small_launch<12>(a, steps, s);
+    case 14: return small_launch<14>(a, steps, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace si

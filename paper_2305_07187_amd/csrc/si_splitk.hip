@@ -519,17 +519,26 @@ int32_t adj_split_groups(int32_t n_pad, int32_t r_pad, int32_t ksplit) {
   return (int32_t)(blocks > 1024 ? 1024 : blocks);
 }
 
-// Partial products that a split step or backward step keeps in memory.
-int64_t split_workspace(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit) {
-  int32_t mb = 0;
+// Matrix block edge of a tile (0: no such tile).
+static int32_t tile_mb(int32_t tile) {
   switch (tile) {
-#define SI_MB(id, bm, bn, wm, wn, mb_, bk, st, ks) \
-  case id: mb = mb_; break;
+#define SI_MB(id, bm, bn, wm, wn, mb, bk, st, ks) \
+  case id: return mb;
     SI_F32_TILES(SI_MB)
 #undef SI_MB
     default: return 0;
   }
-  return ksplit < 2 || few_fits(n_pad, r_pad, mb, ksplit) ? 0 : (int64_t)ksplit * n_pad * r_pad;
+}
+
+int32_t split_few_rows(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit) {
+  const int32_t mb = tile_mb(tile);
+  return mb && few_fits(n_pad, r_pad, mb, ksplit) ? mb : 0;
+}
+
+// Partial products that a split step or backward step keeps in memory.
+int64_t split_workspace(int32_t tile, int32_t n_pad, int32_t r_pad, int32_t ksplit) {
+  if (ksplit < 2 || !tile_mb(tile) || split_few_rows(tile, n_pad, r_pad, ksplit)) return 0;
+  return (int64_t)ksplit * n_pad * r_pad;
 }
 
 int64_t adj_split_workspace(int32_t n_pad, int32_t r_pad, int32_t ksplit) {
