@@ -275,8 +275,9 @@ si_status spring_ising_set_ksplit(si_ctx *ctx, int32_t ksplit);
  * tile's q and p in registers, only q (which every other tile's coupling
  * product reads) passes through memory, and a grid-wide barrier separates
  * consecutive steps (the fixed-point form passes q and p).  Used only when all workgroups of the step kernel in
- * use fit on the device at once (cooperative launch); otherwise run()
- * launches per step.  Results are bit-identical to per-step launches.  A
+ * use fit on the device at once (cooperative launch; the fixed-point form also
+ * needs 256 x 32 or real tiles, one for every workgroup: its launches are
+ * faster elsewhere); otherwise run() launches per step.  Results are bit-identical to per-step launches.  A
  * resident run() returns after the launch has completed, having checked the
  * barrier's time-out flag: a barrier that does not open within about 2 s
  * ends the launch and poisons the context (SI_ERR_HIP).  The barrier costs

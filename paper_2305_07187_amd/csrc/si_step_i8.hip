@@ -1253,7 +1253,13 @@ const char *i8_kernel_name(const I8Args &a) {
 }
 
 // Every workgroup of the grid must own exactly one tile: an even XCD split,
-// and no more tiles than workgroups that fit at once.
+// and no more tiles than workgroups that fit at once.  Elsewhere a barrier
+// between the steps costs more than their launches, so those contexts launch
+// (us per step, launches against resident: N = 384, R = 400 5.9 and 18.8, N =
+// 600, R = 1024 11.7 and 42, N = 8000, R = 64 36.5 and 73 with a resident form of
+// the 32 x 16 tiles; N = 1100, R = 700 15.8 and 28.5, N = 3000, R = 1100 51 and 74
+// with several or uneven tiles of the others; N = 2000, R = 1024, which has one,
+// 21.8 and 37.7).
 hipError_t resident_i8_groups(const I8Args &a, int num_cus, int32_t *groups) {
   *groups = 0;
   if (!i8_fits(a) || i8_few(a)) return hipSuccess;
