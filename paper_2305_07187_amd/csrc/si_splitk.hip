@@ -288,11 +288,13 @@ __device__ __forceinline__ void few_product(const float *__restrict__ J,
     if (i < nk) issue(i, i);
   int rd = 0, wr = S - 1;
   for (int kt = 0; kt < nk; ++kt) {
-    // this slab has landed (its successors are still under way)
+    // this slab has landed (its successors are still under way), and the one
+    // before it has been read: its slot is filled below.  No other wave reads
+    // this ring, so the wave's own wait is all that takes.
     if (kt + S - 1 < nk)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * C::L) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * C::L) : "memory");
     else
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     const float *st = ring + rd * C::SLAB;
     floatx4 a[C::BK / C::KSTEP], b[C::BK / C::KSTEP][TN];
 #pragma unroll
@@ -313,7 +315,7 @@ __device__ __forceinline__ void few_product(const float *__restrict__ J,
         }
       }
     }
-    // (the slot filled here was read a slab ago)
+    // (the slot filled here has been read, see the wait above)
     if (kt + S - 1 < nk) issue(kt + S - 1, wr);
     wr = wr + 1 == S ? 0 : wr + 1;
     rd = rd + 1 == S ? 0 : rd + 1;
