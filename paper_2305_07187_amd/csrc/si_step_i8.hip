@@ -1163,8 +1163,11 @@ static bool i8_real(const I8Args &a) { return a.bm == I8_BM_REAL; }
 
 static bool i8_few(const I8Args &a) { return a.bm == I8_BM_FEW; }
 
+// (Two slabs at least: the state waves read a tile's F between the slabs of
+// the next one, whose last barrier lets the matrix waves write again.)
 static bool i8_fits(const I8Args &a) {
-  return (a.bm == I8_BM || i8_few(a) || (i8_real(a) && a.jexp)) && a.ld % a.bm == 0 && a.r_pad % 64 == 0 &&
+  return (i8_few(a) || a.n > 32 * (i8_real(a) ? I8Real::BKB : I8Int::BKB)) &&
+         (a.bm == I8_BM || i8_few(a) || (i8_real(a) && a.jexp)) && a.ld % a.bm == 0 && a.r_pad % 64 == 0 &&
          a.n >= 1 && a.n <= a.ld && (a.xr == 1 || a.xr == 2 || a.xr == 4 || a.xr == 8);
 }
 
