@@ -39,13 +39,6 @@ __device__ __forceinline__ void spring_update(float q, float p, float f, float d
   if (WALL == SI_WALL_INELASTIC && fabsf(u) > qmax) pn = 0.f;
 }
 
-// FP32 -> BF16 bits, round to nearest even (finite inputs).
-__device__ __forceinline__ uint32_t epi_bf16(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
 // The BM (spins) x BN (replicas) output tile in LDS, replica-major: element
 // (row i, column j) at t[j * LD + i].  Rows are padded by four floats so that
 // the 16-byte writes of 16 consecutive columns fall on distinct banks.  The
@@ -116,12 +109,12 @@ __device__ __forceinline__ void epi_apply(const float *t, const EpiArgs &e,
                                  e.qmax, e.pmax, qv, pv);
       qn[v] = qv;
       pn[v] = pv;
-      if (QP >= 1) b0[v] = epi_bf16(qv);
+      if (QP >= 1) b0[v] = bf16_bits(qv);
       if (QP == 3) {
         const float r1 = qv - __uint_as_float(b0[v] << 16);  // exact
-        b1[v] = epi_bf16(r1);
+        b1[v] = bf16_bits(r1);
         const float r2 = r1 - __uint_as_float(b1[v] << 16);  // exact
-        b2[v] = epi_bf16(r2);
+        b2[v] = bf16_bits(r2);
       }
       if (QP == 0 && e.mask_out) {
         // the unclamped values, recomputed exactly as in spring_update()
@@ -166,12 +159,12 @@ __device__ __forceinline__ void epi_apply_q(const EpiArgs &e, const floatx4 (&q4
     for (int v = 0; v < 4; ++v) {
       const float u = fmaf(cdt, p4[c][v], q4[c][v]);
       qn[v] = fminf(fmaxf(u, -e.qmax), e.qmax);
-      if (QP >= 1) b0[v] = epi_bf16(qn[v]);
+      if (QP >= 1) b0[v] = bf16_bits(qn[v]);
       if (QP == 3) {
         const float r1 = qn[v] - __uint_as_float(b0[v] << 16);  // exact
-        b1[v] = epi_bf16(r1);
+        b1[v] = bf16_bits(r1);
         const float r2 = r1 - __uint_as_float(b1[v] << 16);  // exact
-        b2[v] = epi_bf16(r2);
+        b2[v] = bf16_bits(r2);
       }
     }
     *reinterpret_cast<floatx4 *>(e.q_out + off) = qn;

@@ -32,7 +32,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 
-
 // FP8 e4m3 (bias 7, no infinities) -> BF16 bits; exact because every e4m3
 // value has at most 4 significant bits.
 __device__ __forceinline__ uint32_t fp8_to_bf16_bits(uint32_t b) {
