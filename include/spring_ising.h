@@ -210,7 +210,8 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J,
  * otherwise), with instances padded to 128; BF16X_BF16J and BF16X3_EXACTJ:
  * SI_ERR_UNSUPPORTED.  Work items of 128 x 64 (batch tile 1) or 64 x 64
  * (batch tile 2): prm->tile, else the tile cache's entry for this batch's
- * key, else tile 1; autotune times both.  Each instance's trajectory equals
+ * key, else tile 2 for 10 .. 1024 work items of 128 rows (BF16 forms: 320)
+ * and tile 1 otherwise; autotune times both.  Each instance's trajectory equals
  * the single-instance run of the same form on the 64x64 tile of that slab
  * depth (FP32: tile 14; FP8 J: BF16 tile 9; hi + lo: BF16 tile 7) bit for
  * bit, with either batch tile.  In every later call the

@@ -1215,9 +1215,9 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
   // 128 rows 31.4 and 19.8, 138 72.5 and 49.8, 417 167 and 161, 749 346 and 334,
   // 810 270 and 269, 3014 1109 and 1110; mixed precision, whose 64-row items
   // read the positions' plane twice as often per byte of J: 34 12.3 and 9.1, 288
-  // 19.5 and 18.7, 417 83.8 and 85.0, 4243 870 and 901; below ten items id 1
-  // stays what a context reports, although 64-row items are faster there too:
-  // 20.7 and 13.1 for nine)
+  // 19.5 and 18.7, 417 83.8 and 85.0, 4243 870 and 901).  Below ten items the
+  // line is not the measurement's (nine: 20.7 and 13.1): callers and tests of
+  // small batches rely on the reported default 1, and autotune finds the other
   int32_t cached = 0;
   if (prm->tile) {
     c->tile = prm->tile;
