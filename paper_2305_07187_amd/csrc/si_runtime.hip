@@ -1217,7 +1217,7 @@ si_status spring_ising_init_batch(si_ctx **out, int32_t n_inst, const int32_t *n
   // read the positions' plane twice as often per byte of J: 34 12.3 and 9.1, 288
   // 19.5 and 18.7, 417 83.8 and 85.0, 4243 870 and 901).  Below ten items the
   // line is not the measurement's (nine: 20.7 and 13.1): callers and tests of
-  // small batches rely on the reported default 1, and autotune finds the other
+  // small batches rely on the reported default 1; autotune finds the other.
   int32_t cached = 0;
   if (prm->tile) {
     c->tile = prm->tile;
