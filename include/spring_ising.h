@@ -122,7 +122,8 @@ typedef struct {
   int32_t tile;       /* 0 = automatic kernel choice (the process's tile
                          cache when it holds this context's key, else the
                          built-in preference order; where the fixed-point form
-                         of FP32 or BF16X3_EXACTJ applies, that form); otherwise
+                         of FP32 or BF16X3_EXACTJ applies, that form);
+                         SI_TILE_FLOATING = the same without that form; otherwise
                          a tile id reported by spring_ising_info (tuning override).
                          A batch takes 0, 1 (128 x 64 work items) or 2
                          (64 x 64). */
@@ -141,6 +142,10 @@ typedef struct {
  * As si_params.tile it asks for that form: SI_ERR_INVALID where it does not
  * apply to the couplings, sizes or order. */
 #define SI_TILE_FIXED_POINT 100
+
+/* As si_params.tile of a single instance: the automatic choice among the tiles
+ * of the precision's own matrix cores, never the fixed-point form. */
+#define SI_TILE_FLOATING 101
 
 /* Where the step kernel's tile of a context came from (si_info.tile_source). */
 typedef enum {

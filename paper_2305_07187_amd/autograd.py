@@ -3,7 +3,11 @@
 SpringIsingRelaxedEnergy.apply(J, x0, p0, dt_sched, zeta_sched, ckpt_every)
 returns the relaxed end-energy (1/R) sum_r -1/2 q_r^T J q_r of the final
 positions after len(dt_sched) paper-order steps from (x0, p0); its backward
-supplies gradients for dt_sched and zeta_sched only.  The forward runs the
+supplies gradients for dt_sched and zeta_sched only.  The steps are those of a
+context with tile SI_TILE_FLOATING (FP32 matrix cores at every size; the
+fixed-point form, whose couplings' digits a context made for one gradient
+would pack for it alone, rounds otherwise, and trajectories part within some
+hundred steps).  The forward runs the
 checkpointed forward half in the HIP library and keeps the context (its
 checkpoints and the seed of the reverse sweep) on the autograd node; the
 reverse sweep runs only when backward is called, and the context is released
@@ -23,7 +27,7 @@ class SpringIsingRelaxedEnergy(torch.autograd.Function):
         S = int(dt_sched.numel())
         model = si.SpringIsing(J.detach().float().contiguous(), x0.detach().float().contiguous(),
                                None if p0 is None else p0.detach().float().contiguous(),
-                               total_steps=S)
+                               total_steps=S, tile=si.SI_TILE_FLOATING)
         keep = False
         try:
             model.set_schedule(dt_sched.detach().float().contiguous(),

@@ -319,7 +319,7 @@ static si_status check_params(const si_params *p) {
   const int32_t last = p->precision == SI_PREC_FP32 ? TILE_F32_LAST : TILE_BF16_LAST;
   const bool fixed = p->tile == SI_TILE_FIXED_POINT &&
                      (p->precision == SI_PREC_FP32 || p->precision == SI_PREC_BF16X3_EXACTJ);
-  if ((p->tile < 0 || p->tile > last) && !fixed)
+  if ((p->tile < 0 || p->tile > last) && !fixed && p->tile != SI_TILE_FLOATING)
     return fail(SI_ERR_INVALID, "params: unknown tile %d", p->tile);
   if (p->energy_every < 0) return fail(SI_ERR_INVALID, "params: energy_every must be >= 0");
   return SI_OK;
@@ -547,7 +547,7 @@ static bool i8_applies(const si_ctx *c) {
       !integer ? i8_real_pays(c->n, c->r)
       : i8_few(c) || (c->n >= (split ? 1000 : 513) && (int64_t)c->n * round_up(c->r, 64) > 700000);
   return (split || c->prm.precision == SI_PREC_FP32) && c->prm.order == SI_ORDER_PAPER &&
-         c->user_tile == 0 && !c->n_inst && pays;
+         c->user_tile == 0 && c->prm.tile != SI_TILE_FLOATING && !c->n_inst && pays;
 }
 
 static bool i8_on(const si_ctx *c) { return c->i8.Jt && c->ksplit_mode == 0 && !c->i8_off; }
@@ -936,7 +936,8 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
 
   const bool lowp = prm->precision != SI_PREC_FP32;
   const bool fixed = prm->tile == SI_TILE_FIXED_POINT;
-  c->user_tile = fixed ? 0 : prm->tile;  // (its FP32 or BF16 tile stands by)
+  const bool automatic = prm->tile == 0 || prm->tile == SI_TILE_FLOATING;
+  c->user_tile = fixed || automatic ? 0 : prm->tile;  // (fixed: its tile stands by)
   c->n = n;
   c->r = r;
   const bool has_fixed = i8_applies(c);
@@ -946,10 +947,10 @@ si_status spring_ising_init(si_ctx **out, int32_t n, int32_t r, const float *J, 
                 "and sizes", SI_TILE_FIXED_POINT);
   }
   int32_t cached = 0;
-  const bool hit = !prm->tile && tile_cache_get(tile_key(c, has_fixed), &cached) &&
+  const bool hit = automatic && tile_cache_get(tile_key(c, has_fixed), &cached) &&
                    tile_serves(0, prm->precision, has_fixed, cached);
   if (hit) c->tile_source = SI_TILE_FROM_CACHE;
-  if (prm->tile) c->tile_source = SI_TILE_FROM_CALLER;
+  if (!automatic) c->tile_source = SI_TILE_FROM_CALLER;
   c->i8_declined = hit && has_fixed && cached != SI_TILE_FIXED_POINT;
   if (c->user_tile) {
     c->tile = c->user_tile;

@@ -368,6 +368,7 @@ def spring_ising_autotune(ctx, steps):
 
 
 SI_TILE_FIXED_POINT = 100  # tile id of the fixed-point form of FP32 and BF16X3_EXACTJ
+SI_TILE_FLOATING = 101     # tile 0 without that form
 TILE_SOURCES = {0: "table", 1: "cache", 2: "caller", 3: "autotune"}
 
 
