@@ -27,8 +27,8 @@
 // the same launch (i8_uneven): one position of 1.4 among ones of 1e-6, k = 0, N
 // = 1000, R = 704, largest relative error of a momentum 4e-5 (15 in fixed
 // point, 3e-4 on the FP32 tiles).  N = 2000, R = 1024 with every replica uneven
-// 122 us a step (111 with real couplings; the FP32 tiles 74), with none 22.4
-// (22.0 without the counts); the 32 x 16 tiles 11.6 (11.4) at N = 600, R = 1024.
+// 122 us a step (111 with real couplings; the FP32 tiles 74), with none 22.3
+// (22.2 without the counts); the 32 x 16 tiles 11.5 (11.4) at N = 600, R = 1024.
 //
 // Measured (MI355X, us per step, FP32 matrix cores before): N = 2000, R = 1024
 // 22.3 (73.6), R = 2048 42 (141), N = 4000, R = 2048 128 (532), N = 8000,
@@ -551,7 +551,7 @@ __device__ __forceinline__ void i8_uneven(const I8Args &a, const I8Walk<C> &walk
 
 // The state waves' part of one step: wave sw owns COLS columns of a tile, a
 // lane four spins of eight of them.
-template <class C, int WALL>
+template <class C, int WALL, bool REC>
 __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk, I8Smem<C> &sm) {
   const int sw = __builtin_amdgcn_readfirstlane(((int)threadIdx.x >> 6) - C::NM);
   const int lane = threadIdx.x & 63, row = lane % C::LPC * 4, nx = a.cur ^ 1;
@@ -640,7 +640,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
           mx = fmaxf(mx, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
         }
         *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
-        if (a.mask_out)
+        if constexpr (REC)
           *reinterpret_cast<uint32_t *>(a.mask_out + off) =
               i8_wall_bits(a, q4[cc], p4[cc], f, dt, zeta);
         um[c] = __float_as_uint(mx);
@@ -682,11 +682,7 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
       p4[c] = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
     }
 #pragma unroll
-    for (int off = C::COLS; off < 64; off <<= 1) {
-      mx = fmaxf(mx, __shfl_xor(mx, off));
-      large += __shfl_xor(large, off);
-    }
-    if (i8_is_uneven(kin, large, a.n)) sm.uneven = 1;
+    for (int off = C::COLS; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     const int kout = i8_exponent(mx);
     if (m0 == 0 && lane < C::COLS) a.kexp[nx][col0 + lane] = kout;
     tick();
@@ -727,6 +723,9 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
       }
       tick();
     }
+#pragma unroll
+    for (int off = C::COLS; off < 64; off <<= 1) large += __shfl_xor(large, off);
+    if (i8_is_uneven(kin, large, a.n)) sm.uneven = 1;
     while (left > 0) pass();
     q_barrier();  // F is in LDS
   }
@@ -734,23 +733,23 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
   finish(m0, n0);
 }
 
-// One step of this workgroup's tiles.
-template <class C, int WALL>
+// One step of this workgroup's tiles (REC: recording the wall bits).
+template <class C, int WALL, bool REC>
 __device__ __forceinline__ void i8_step(const I8Args &a, const I8Walk<C> &walk, I8Smem<C> &sm) {
   if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < C::NM)
     i8_matrix(a, walk, sm);
   else
-    i8_state<C, WALL>(a, walk, sm);
+    i8_state<C, WALL, REC>(a, walk, sm);
   __syncthreads();
   if (__builtin_expect(sm.uneven, 0)) i8_uneven<C, WALL>(a, walk, sm);
 }
 
-template <class C, int WALL>
+template <class C, int WALL, bool REC>
 __global__ __launch_bounds__(C::NT) void step_i8_kernel(I8Args a) {
   __shared__ I8Smem<C> sm;
   const I8Walk<C> walk(a);
   if (walk.count == 0) return;
-  i8_step<C, WALL>(a, walk, sm);
+  i8_step<C, WALL, REC>(a, walk, sm);
 }
 
 // Resident form: one cooperative launch runs n_steps steps with a grid-wide
@@ -761,7 +760,7 @@ __global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentAr
   const I8Walk<C> walk(a);
   if (walk.count == 0) return;
   for (int s = 0; s < r.n_steps; ++s) {
-    i8_step<C, WALL>(a, walk, sm);
+    i8_step<C, WALL, false>(a, walk, sm);
     a.cur ^= 1;
     a.t += 1;
     if (s + 1 < r.n_steps && !grid_barrier(r.count, (uint32_t)(s + 1), r.err)) return;
@@ -822,7 +821,7 @@ __device__ __forceinline__ void i8_f32_product(const float *__restrict__ J,
   }
 }
 
-template <int FEW_W, int WALL>
+template <int FEW_W, int WALL, bool REC>
 __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
   constexpr int BM = I8_BM_FEW, BN = FEW_BN;
   __shared__ __attribute__((aligned(16))) int sums[FEW_W][2][BN][BM + 4];
@@ -930,45 +929,17 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
     if (m0 == 0) a.kexp[nx][n0 + tid] = kout;
   }
   __syncthreads();
-  floatx4 f = {0.f, 0.f, 0.f, 0.f};
   if (owner) {
+    const float dt = a.dt[a.t], zeta = a.zeta[a.t];
+    const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
+    const int kin = kshared[0][scol], kout = kshared[1][scol];
     intx4 hi = {0, 0, 0, 0}, lo = {0, 0, 0, 0};
 #pragma unroll
     for (int w = 0; w < FEW_W; ++w) {
       hi += *reinterpret_cast<const intx4 *>(&sums[w][0][scol][srow]);
       lo += *reinterpret_cast<const intx4 *>(&sums[w][1][scol][srow]);
     }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      f[v] = ldexpf(fmaf((float)hi[v], 65536.f, (float)lo[v]), -kshared[0][scol]);
-  }
-  if (__builtin_expect(uneven, 0)) {
-    // the uneven columns' products on the FP32 matrix cores, a range of the
-    // contraction per wave, added in the order of the ranges
-    const int K = (a.n + 63) / 64 * 64, klen = (K / 64 + FEW_W - 1) / FEW_W * 64;
-    floatx4 part[2][1];
-    i8_f32_product(a.J + (size_t)(m0 + lrow) * a.ld + (lane >> 4) * 4,
-                   a.q[a.cur] + (size_t)(n0 + lrow) * a.ld + (lane >> 4) * 4, a.ld, wave * klen,
-                   min(K, (wave + 1) * klen), part);
-    __syncthreads();  // the digits' sums have been read
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-      *reinterpret_cast<floatx4 *>(&sums[wave][0][lrow][r * 16 + (lane >> 4) * 4]) = part[r][0];
-    __syncthreads();
-    if (owner && kshared[0][scol] == I8_SPECIAL) {
-      f = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int w = 0; w < FEW_W; ++w)
-        f += *reinterpret_cast<const floatx4 *>(&sums[w][0][scol][srow]);
-#pragma unroll
-      for (int v = 0; v < 4; ++v)  // (infinite positions times the rows' zero padding)
-        if (m0 + srow + v >= a.n) f[v] = 0.f;
-    }
-  }
-  if (owner) {
-    const float dt = a.dt[a.t], zeta = a.zeta[a.t];
-    const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
-    const int kout = kshared[1][scol];
+    floatx4 f;
     float mnext = 0.f;
     floatx4 qn, pn;
     uint32_t dg[4], by[4];
@@ -976,7 +947,7 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       float qv, pv;
-      f[v] += h4[v];
+      f[v] = ldexpf(fmaf((float)hi[v], 65536.f, (float)lo[v]), -kin) + h4[v];
       spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], f[v], dt, zeta, a.k, a.inv_m, a.qmax,
                                           a.pmax, qv, pv);
       qn[v] = fminf(fmaxf(fmaf(dt * a.inv_m, p4[v], q4[v]), -a.qmax), a.qmax);
@@ -987,7 +958,7 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
     }
     *reinterpret_cast<floatx4 *>(a.q[nx] + off) = qn;
     *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
-    if (a.mask_out)
+    if constexpr (REC)
       *reinterpret_cast<uint32_t *>(a.mask_out + off) = i8_wall_bits(a, q4, p4, f, dt, zeta);
     byte_transpose(dg, by);
 #pragma unroll
@@ -1006,6 +977,46 @@ __global__ __launch_bounds__(64 * FEW_W, 4) void step_i8_few_kernel(I8Args a) {
                                 (n0 % 32 + c) * 16) =
         *reinterpret_cast<const uintx4 *>(&dig[d][c][h * 16]);
   }
+  if (__builtin_expect(!uneven, 1)) return;
+  // p' and the maxima of the uneven columns again, from products on the FP32
+  // matrix cores: a range of the contraction per wave, added in the order of the
+  // ranges
+  const int K = (a.n + 63) / 64 * 64, klen = (K / 64 + FEW_W - 1) / FEW_W * 64;
+  floatx4 part[2][1];
+  i8_f32_product(a.J + (size_t)(m0 + lrow) * a.ld + (lane >> 4) * 4,
+                 a.q[a.cur] + (size_t)(n0 + lrow) * a.ld + (lane >> 4) * 4, a.ld, wave * klen,
+                 min(K, (wave + 1) * klen), part);
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+    *reinterpret_cast<floatx4 *>(&sums[wave][0][lrow][r * 16 + (lane >> 4) * 4]) = part[r][0];
+  __syncthreads();
+  if (!owner || kshared[0][scol] != I8_SPECIAL) return;
+  q4 = *reinterpret_cast<const floatx4 *>(a.q[a.cur] + off);
+  p4 = *reinterpret_cast<const floatx4 *>(a.p[a.cur] + off);
+  h4 = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (a.h) h4 = *reinterpret_cast<const floatx4 *>(a.h + m0 + srow);
+  floatx4 f = {0.f, 0.f, 0.f, 0.f}, pn;
+#pragma unroll
+  for (int w = 0; w < FEW_W; ++w) f += *reinterpret_cast<const floatx4 *>(&sums[w][0][scol][srow]);
+  const float dt = a.dt[a.t], zeta = a.zeta[a.t];
+  const float cn = a.dt[a.t + 1 < a.total_steps ? a.t + 1 : a.t] * a.inv_m;
+  float mnext = 0.f;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    float qv, pv;
+    // (an infinite position times the rows' zero padding is not a number)
+    f[v] = (m0 + srow + v < a.n ? f[v] : 0.f) + h4[v];
+    spring_update<SI_ORDER_PAPER, WALL>(q4[v], p4[v], f[v], dt, zeta, a.k, a.inv_m, a.qmax, a.pmax,
+                                        qv, pv);
+    pn[v] = pv;
+    mnext = fmaxf(mnext, fabsf(fminf(fmaxf(fmaf(cn, pv, qv), -a.qmax), a.qmax)));
+  }
+  *reinterpret_cast<floatx4 *>(a.p[nx] + off) = pn;
+  if constexpr (REC)
+    *reinterpret_cast<uint32_t *>(a.mask_out + off) = i8_wall_bits(a, q4, p4, f, dt, zeta);
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) mnext = fmaxf(mnext, __shfl_xor(mnext, o));
+  if ((tid & 7) == 0) a.peak[nx][(size_t)(m0 / BM) * a.r_pad + n0 + scol].mx = mnext;
 }
 
 // Digits, scales, counts and maxima of the FP32 state (t: the next step's index).
@@ -1205,13 +1216,16 @@ int32_t i8_xcd_rows(const I8Args &a) {
   return best;
 }
 
+template <class C>
+static const void *i8_step_of(const I8Args &a) {
+  if (a.wall == SI_WALL_INELASTIC)
+    return reinterpret_cast<const void *>(&step_i8_kernel<C, SI_WALL_INELASTIC, false>);
+  return a.mask_out ? reinterpret_cast<const void *>(&step_i8_kernel<C, SI_WALL_CLAMP, true>)
+                    : reinterpret_cast<const void *>(&step_i8_kernel<C, SI_WALL_CLAMP, false>);
+}
+
 static const void *i8_step_entry(const I8Args &a) {
-  const bool clamp = a.wall == SI_WALL_CLAMP;
-  if (i8_real(a))
-    return clamp ? reinterpret_cast<const void *>(&step_i8_kernel<I8Real, SI_WALL_CLAMP>)
-                 : reinterpret_cast<const void *>(&step_i8_kernel<I8Real, SI_WALL_INELASTIC>);
-  return clamp ? reinterpret_cast<const void *>(&step_i8_kernel<I8Int, SI_WALL_CLAMP>)
-               : reinterpret_cast<const void *>(&step_i8_kernel<I8Int, SI_WALL_INELASTIC>);
+  return i8_real(a) ? i8_step_of<I8Real>(a) : i8_step_of<I8Int>(a);
 }
 
 static const void *i8_resident(const I8Args &a) {
@@ -1223,35 +1237,38 @@ static const void *i8_resident(const I8Args &a) {
                : reinterpret_cast<const void *>(&resident_i8_kernel<I8Int, SI_WALL_INELASTIC>);
 }
 
+template <int FEW_W>
+static const void *i8_few_of(const I8Args &a) {
+  if (a.wall == SI_WALL_INELASTIC)
+    return reinterpret_cast<const void *>(&step_i8_few_kernel<FEW_W, SI_WALL_INELASTIC, false>);
+  return a.mask_out ? reinterpret_cast<const void *>(&step_i8_few_kernel<FEW_W, SI_WALL_CLAMP, true>)
+                    : reinterpret_cast<const void *>(&step_i8_few_kernel<FEW_W, SI_WALL_CLAMP, false>);
+}
+
+static int i8_few_tiles(const I8Args &a) { return a.ld / a.bm * (a.r_pad / FEW_BN); }
+
+// Waves of a workgroup of the 32 x 16 tiles: eight while two workgroups fill a
+// CU and the contraction is long, else four (us per step, eight against four:
+// N = 2000, R = 50 6.8 and 7.1, N = 4000, R = 64 12.0 and 13.3, N = 2000, R =
+// 256 14.2 and 12.4, N = 1000, R = 64 5.6 and 5.3).
+static int i8_few_waves(const I8Args &a) { return i8_few_tiles(a) <= 512 && a.n > 1024 ? 8 : 4; }
+
+// (wall bits are recorded for the adjoint, which takes clamping walls only)
 hipError_t launch_step_i8(const I8Args &a, int num_cus, hipStream_t s) {
-  if (!i8_fits(a)) return hipErrorInvalidValue;
-  if (i8_few(a)) {
-    // eight waves a workgroup while two of them fill a CU and the contraction
-    // is long, else four (us per step, eight against four: N = 2000, R = 50 6.8
-    // and 7.1, N = 4000, R = 64 12.0 and 13.3, N = 2000, R = 256 14.2 and 12.4,
-    // N = 1000, R = 64 5.6 and 5.3)
-    const int grid = a.ld / a.bm * (a.r_pad / FEW_BN);
-    const bool clamp = a.wall == SI_WALL_CLAMP;
-    if (grid <= 512 && a.n > 1024) {
-      if (clamp)
-        step_i8_few_kernel<8, SI_WALL_CLAMP><<<grid, 512, 0, s>>>(a);
-      else
-        step_i8_few_kernel<8, SI_WALL_INELASTIC><<<grid, 512, 0, s>>>(a);
-    } else if (clamp) {
-      step_i8_few_kernel<4, SI_WALL_CLAMP><<<grid, 256, 0, s>>>(a);
-    } else {
-      step_i8_few_kernel<4, SI_WALL_INELASTIC><<<grid, 256, 0, s>>>(a);
-    }
-    return hipGetLastError();
-  }
+  if (!i8_fits(a) || (a.mask_out && a.wall != SI_WALL_CLAMP)) return hipErrorInvalidValue;
   I8Args aa = a;
   void *args[] = {&aa};
+  if (i8_few(a)) {
+    const int waves = i8_few_waves(a);
+    return hipLaunchKernel(waves == 8 ? i8_few_of<8>(a) : i8_few_of<4>(a), dim3(i8_few_tiles(a)),
+                           dim3(64 * waves), args, 0, s);
+  }
   return hipLaunchKernel(i8_step_entry(a), dim3(i8_grid(a, num_cus)), dim3(I8Int::NT), args, 0, s);
 }
 
 const char *i8_kernel_name(const I8Args &a) {
   return i8_real(a)  ? "step_i8x10_128x64_w4_k128_s3"
-         : i8_few(a) ? (a.ld / a.bm * (a.r_pad / FEW_BN) <= 512 && a.n > 1024 ? "step_i8x4_32x16_ks8" : "step_i8x4_32x16_ks4")
+         : i8_few(a) ? (i8_few_waves(a) == 8 ? "step_i8x4_32x16_ks8" : "step_i8x4_32x16_ks4")
                      : "step_i8x4_256x32_w4_k256_s3";
 }
 
