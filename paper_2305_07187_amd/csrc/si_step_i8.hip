@@ -723,10 +723,11 @@ __device__ __forceinline__ void i8_state(const I8Args &a, const I8Walk<C> &walk,
       }
       tick();
     }
+    while (left > 0) pass();
+    // (added up here, where these waves wait: no slab's copies are held up)
 #pragma unroll
     for (int off = C::COLS; off < 64; off <<= 1) large += __shfl_xor(large, off);
     if (i8_is_uneven(kin, large, a.n)) sm.uneven = 1;
-    while (left > 0) pass();
     q_barrier();  // F is in LDS
   }
   left = 0;
