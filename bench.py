@@ -69,6 +69,12 @@ MEASURED_TRAFFIC_BYTES = {
     ("step_bf16_128x128_w4x2_k128_s3", "bf16x_fp8j", 2000, 2048): 146.93e6,
     ("step_bf16_128x256_w2x4_k64_s2_p1", "bf16x_hiloj", 8000, 2048): 1143.93e6,
 }
+# The same of the fixed-point form, which has no tile table to check names against.
+FIXED_POINT_TRAFFIC_BYTES = {
+    ("step_i8x4_256x32_w4_k256_s3", "fp32", 2000, 1024): 80.12e6,
+    ("step_i8x4_256x32_w4_k256_s3", "bf16x3_exactj", 2000, 1024): 80.12e6,
+    ("step_i8x10_128x64_w4_k128_s3", "fp32", 8000, 2048): 2463.0e6,
+}
 
 
 def _cpu_model():
@@ -661,13 +667,17 @@ def main():
                                f"{iters} iterations, paper linear zeta schedule, "
                                f"{args.precision}",
                    "n": n, "replicas": r, "iterations": iters, "precision": args.precision,
-                   "product": ("exact fixed point: FP32 positions as 32-bit integers in four "
-                               "int8 digits, int32 accumulation" if fixed_point
+                   "product": ({"4": "fixed point: FP32 positions as 32-bit integers in four int8 "
+                                     "digits, exact int32 sums, rounded to FP32 in two halves",
+                                "10": "fixed point: FP32 positions and couplings as 32-bit "
+                                      "integers in four int8 digits, ten of sixteen digit "
+                                      "products, int32 sums"}[fixed_point.group(1)] if fixed_point
                                else "floating point"),
                    "kernel": info["kernel_name"]},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
-                     "traffic": MEASURED_TRAFFIC_BYTES.get((info["kernel_name"], args.precision, n, r)),
+                     "traffic": {**MEASURED_TRAFFIC_BYTES, **FIXED_POINT_TRAFFIC_BYTES}.get(
+                         (info["kernel_name"], args.precision, n, r)),
                      "traffic_unit": "bytes per launch",
                      "kernel": info["kernel_name"], "avg_launch_us": kernel_us,
                      "algorithmic_flop_per_launch": flops},

@@ -66,15 +66,18 @@ typedef enum { SI_ORDER_PAPER = 0, SI_ORDER_SYMPLECTIC = 1 } si_order;
  * wall (the perfectly inelastic wall that Methods refers to). */
 typedef enum { SI_WALL_CLAMP = 0, SI_WALL_INELASTIC = 1 } si_wall;
 
-/* Arithmetic of the coupling product J.Q (accumulation is always FP32).
+/* Arithmetic of the coupling product J.Q (accumulation in FP32, in the
+ * fixed-point form in int32).
  *   FP32        : FP32 J and FP32 positions (plain method).  For integer J of
  *                 a complete graph (no zero off the diagonal) with N times the
  *                 largest |J_ij| at most 65281, in the paper order, with tile 0
  *                 and set_ksplit 0 and where it is faster, the product is
  *                 formed in fixed point on the int8 matrix cores: every
- *                 position to 2^-31 of its replica's largest, sums exact,
- *                 the result rounded to FP32.  Other couplings up to N =
- *                 32000 likewise, each to 2^-31 of its row's largest, where
+ *                 position to 2^-31 of its replica's largest, exact int32
+ *                 sums, rounded to FP32 in two halves and their sum.  Other
+ *                 couplings up to N = 32000 likewise, each to 2^-31 of its
+ *                 row's largest and without the lowest six of sixteen digit
+ *                 products (at most 6 x 2^-31 of the largest product), where
  *                 every row is dense and without outliers.  A replica whose
  *                 positions are mostly far below its largest (fewer than half
  *                 of its groups of four hold one of a sixteenth of it) or not

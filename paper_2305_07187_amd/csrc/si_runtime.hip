@@ -493,20 +493,23 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // (Error against 64 bits after 20 steps at N = 2000, R = 1024: 5e-8 against
 // 4.6e-7; N = 512 .. 4000, R = 256 .. 2048, positions scaled by 1 .. 1e-30:
 // 3e-8 .. 6e-8 against 1.3e-7 .. 6.6e-7.)  Two paired digits of the sums must
-// fit 32 bits: N |J| 32896 < 2^31.  The digits' scales need the paper order.
+// fit 32 bits: the diagonal is zero, so a row's sum of the lower pair is at
+// most (N - 1) |J| 32896, and N |J| <= 65281 makes that 65280 x 32896 < 2^31;
+// the upper pair's, whose leading digit is at most 127, is N |J| 32640 < 2^31.
+// The digits' scales need the paper order.
 // A tile or a split asked for by the caller keeps the FP32 matrix cores.
 //
 // Sizes, integer couplings, from sweeps (us per step): the 32 x 16 tiles
 // (i8_few) up to N R = 700000, the 256 x 32 tiles beyond (few against wide: N
 // = 600, R = 1024 11.4 and 11.5, N = 700, R = 1024 13.0 and 11.6, N = 1000, R =
-// 512 10.3 and 13.1, N = 2000, R = 256 12.5 and 19.4, R = 300 15.7 and 19.5, R
-// = 512 24.2 and 19.2, N = 8000, R = 64 35.8 and 47.2, N = 12000, R = 64 75.5
+// 512 10.4 and 13.1, N = 2000, R = 256 12.6 and 19.4, R = 300 15.7 and 19.5, R
+// = 512 24.2 and 19.2, N = 8000, R = 64 36.0 and 47.2, N = 12000, R = 64 75.5
 // and 65.5).  Below, FP32 keeps the small problems (int8 against FP32: N =
 // 300, R = 256 5.2 and 4.9, N = 400, R = 64 5.0 and 4.8, R = 500 6.3 and 8.1, N
 // = 1000, R = 128 5.6 and 6.9, N = 513, R = 8 5.5 and 5.6, N = 1000, R = 64 5.9
-// and 6.5, N = 2000, R = 50 6.9 and 9.3, R = 128 8.7 and 13.2, R = 1024 22.4 and
-// 73.6, N = 4096, R = 64 12.3 and 26.2, N = 8000, R = 64 36.1 and 76.5, R = 2048
-// 475 and 2076).
+// and 6.5, N = 2000, R = 50 6.9 and 9.3, R = 128 9.0 and 13.2, R = 1024 22.4 and
+// 73.6, N = 4096, R = 64 12.3 and 26.2, N = 8000, R = 64 36.0 and 76.5, R = 2048
+// 480 and 2076).
 // The split form of the BF16 matrix cores (BF16X3_EXACTJ: FP32 positions in
 // three planes, FP32 sums) takes the same products, and they are faster here
 // too, with the wide tiles from N = 1000 on (int8 against BF16: N = 600, R =
@@ -514,8 +517,9 @@ static int32_t choose_tile(int32_t n, int32_t r, int num_cus) {
 // 30.8; N = 4000, R = 100 19.2 and 35.7; N = 5000, R = 256 34.0 and 85.7).
 //
 // Real couplings take four digits as well (each to 2^-31 of its row's
-// largest) and ten of the sixteen digit products; those left out lie below
-// 2^-31 of the largest product.  Rows must be dense and without outliers (see
+// largest) and ten of the sixteen digit products; the six left out are together
+// below 3.2e9 units of a product whose largest is 2^60 .. 2^62 of them, at most
+// 6 x 2^-31 of it.  Rows must be dense and without outliers (see
 // i8_rows_kernel).  A tile of ten products is long (8 us and 12 us per 1000
 // spins, even for one), so they pay where N R fills the chip, from N R =
 // 640000 on (us per step, int8 against FP32: N = 600, R = 1024 16.9 against

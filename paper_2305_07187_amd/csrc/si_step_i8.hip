@@ -27,17 +27,18 @@
 // the same launch (i8_uneven): one position of 1.4 among ones of 1e-6, k = 0, N
 // = 1000, R = 704, largest relative error of a momentum 4e-5 (15 in fixed
 // point, 3e-4 on the FP32 tiles).  N = 2000, R = 1024 with every replica uneven
-// 122 us a step (111 with real couplings; the FP32 tiles 74), with none 22.3
-// (22.2 without the counts); the 32 x 16 tiles 11.5 (11.4) at N = 600, R = 1024.
+// 123 us a step (110 with real couplings; the FP32 tiles 74), with none 22.4
+// (22.3 without the counts); the 32 x 16 tiles 11.5 (11.4) at N = 600, R = 1024.
 //
 // Measured (MI355X, us per step, FP32 matrix cores before): N = 2000, R = 1024
-// 22.3 (73.6), R = 2048 42 (141), N = 4000, R = 2048 128 (532), N = 8000,
-// R = 2048 475 (2076).  Bound: four int8 products take 7.6 us of matrix time a
+// 22.4 (73.6), R = 2048 42 (141), N = 4000, R = 2048 128 (532), N = 8000,
+// R = 2048 480 (2076).  Bound: four int8 products take 7.6 us of matrix time a
 // step at N = 2000, R = 1024 (256 tiles, one per CU; 52 us at the FP32 peak);
-// a 256-deep slab of a tile takes 1.4 .. 1.9 us instead of 0.95, because the
-// loads of J and the copies and LDS reads of the digits fill the CU's memory
-// and LDS pipelines as well, and the start and the end of a launch take about
-// 8 us.  Slower: J through LDS too (24.0 at N = 2000, R = 1024; 127 at
+// a 256-deep slab of a tile takes 1.6 us instead of 0.95, because the loads of
+// J and the copies and LDS reads of the digits fill the CU's memory and LDS
+// pipelines as well, and the start and the end of a launch take 10 us (one tile
+// per CU with 4, 8, 16 and 32 slabs: N, R = 1024, 2048 16.4 us, 2048, 1024 23.1,
+// 4096, 512 35.9, 8192, 256 62).  Slower: J through LDS too (24.0 at N = 2000, R = 1024; 127 at
 // N = 4000, R = 2048), eight 32 x 32 matrix waves (23.6; 138), eight waves
 // without state waves (25; 147), counters in LDS for the slab barriers (23.4;
 // 132), J fetched into L2 ahead (23.2; 136).
@@ -778,8 +779,8 @@ __global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentAr
 // of the 256 x 32 tiles bit for bit.
 //
 // Measured (us per step, FP32 one-launch form or 256 x 32 tiles before): N =
-// 2000, R = 50 6.8 (9.3), N = 4000, R = 64 12.0 (26.1), N = 1000, R = 512 10.3
-// (13.1), N = 2000, R = 256 12.5 (19.4), N = 8000, R = 64 35.8 (47.2).  Bound: a
+// 2000, R = 50 6.8 (9.3), N = 4000, R = 64 12.3 (26.1), N = 1000, R = 512 10.4
+// (13.1), N = 2000, R = 256 12.6 (19.4), N = 8000, R = 64 36.0 (47.2).  Bound: a
 // launch, then its loads: 96 N bytes per workgroup (3.3 us at N = 2000, R = 64
 // at 57 bytes a cycle and CU).  Two workgroups per CU and two steps ahead beat
 // one and four (N = 4000, R = 64 12.0 against 15.0, N = 2000, R = 256 14.2
