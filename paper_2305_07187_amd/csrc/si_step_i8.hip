@@ -776,7 +776,7 @@ __global__ __launch_bounds__(C::NT) void resident_i8_kernel(I8Args a, ResidentAr
 // straight from memory into v_mfma_i32_16x16x64_i8's registers, FEW_PD steps
 // ahead; the waves' sums (pairs of digits, exact in 32 bits) are added in LDS,
 // and the update of the tile follows.  Sums are exact, so the result is that
-// of the 256 x 32 tiles bit for bit.
+// of the 256 x 32 tiles bit for bit (uneven replicas' FP32 sums aside).
 //
 // Measured (us per step, FP32 one-launch form or 256 x 32 tiles before): N =
 // 2000, R = 50 6.8 (9.3), N = 4000, R = 64 12.3 (26.1), N = 1000, R = 512 10.4
