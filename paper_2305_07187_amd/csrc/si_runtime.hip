@@ -650,10 +650,12 @@ static hipError_t i8_refresh(si_ctx *c) {
 }
 
 // Gives the int8 form's buffers back: later steps run on the tile that stands
-// by.  (No call allocates between a step's launches or during a capture.)
+// by, so a backward half can no longer recompute what the forward half before
+// it ran.  (No call allocates between a step's launches or during a capture.)
 hipError_t si_ctx::release_i8() {
   hipError_t e = hipStreamSynchronize(stream);
   drop_graphs();
+  epoch++;
   if (e == hipSuccess) e = hipFree(i8_buf);
   i8_buf = nullptr;
   bytes -= i8_bytes;

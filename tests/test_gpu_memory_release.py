@@ -76,6 +76,17 @@ def test_gradient_and_resident(n, r):
     assert abs(float(loss.cpu()[0]) - Lo) <= 1e-5 * abs(Lo)
     assert rel(gd.cpu().numpy(), gdo) <= 1e-4 and rel(gz.cpu().numpy(), gzo) <= 1e-4
     m.close()
+    # between the halves: the recomputation would take other kernels
+    m = si.SpringIsing(to_dev(J), to_dev(x0), total_steps=S)
+    m.relaxed_energy_forward(5)
+    si.spring_ising_debug_fail_allocs(m.ctx, 1)
+    m.update_best()
+    with pytest.raises(si.SpringIsingError) as e:
+        m.relaxed_energy_backward()
+    assert e.value.status == si.SI_ERR_STATE
+    m.set_state(to_dev(x0), None, 0)
+    m.relaxed_energy_grad(5)
+    m.close()
     for call in ("resident", "autotune"):
         m = si.SpringIsing(to_dev(J), to_dev(x0), total_steps=S)
         m.set_resident(2)
